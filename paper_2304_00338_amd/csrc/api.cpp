@@ -38,6 +38,7 @@ struct Off {
 struct PackOff {
   int64_t W1 = -1, W1t = -1, W2 = -1, W2t = -1, W1p = -1, W2p = -1;
   int64_t F1 = -1, F2 = -1, F1t = -1, F2t = -1;  // fp32 edge MLPs (encoder: W2): fragment-major W1e, W2, transposes
+  int64_t S1 = -1, S2 = -1;  // fp32 split products: two-piece fp16 fragments (edge MLPs: W1e, W2)
   int64_t W1sp = -1, W1rp = -1;  // edge MLPs: row-permuted sender / receiver column blocks of W1
   int64_t W1ap = -1;             // node MLPs at width 160: row-permuted agg column block of W1
   // fp32 row-layout node kernels: node MLPs' W1 agg block (F1: its h block),
@@ -54,6 +55,7 @@ struct Model {
   std::vector<PackOff> p_edge, p_node;
   int64_t pack_elems = 0;
   std::vector<PackEnt> ents;
+  std::vector<PackEnt> split_ents;  // modes 4, 5
 };
 
 // Two-layer MLP din -> hid -> dout, parameters in the order W1 [hid][din],
@@ -132,10 +134,17 @@ void add_frag(Model& M, int64_t src, int ld, int n, int mode, int64_t& W) {
   M.ents.push_back(e);
 }
 
+// Two-piece fp16 fragments (mode 4) of the square [n][n] block at float
+// offset src (row stride ld), or of its transpose (mode 5), and their scale.
+void add_split(Model& M, int64_t src, int ld, int n, int mode, int64_t& W) {
+  add_frag(M, src, ld, n, mode, W);
+  M.pack_elems += 1;
+  M.split_ents.push_back(M.ents.back());
+  M.ents.pop_back();
+}
+
 // Parameter layout and packed operand copies of an MGN with m MP steps and
-// latent width lat (both MLP layers of every block are lat wide); fp32
-// models also carry the fragment-major edge-MLP copies of the fp32
-// row-layout edge kernels.
+// latent width lat (both MLP layers of every block are lat wide).
 Model make_model(int m, int lat, bool fp32 = false) {
   const int D = lat;
   Model M;
@@ -150,20 +159,41 @@ Model make_model(int m, int lat, bool fp32 = false) {
   }
   M.dec = mlp_off(o, D, D, 4, false);
   M.total = o;
+  M.p_edge.resize(m);
+  M.p_node.resize(m);
+  if (fp32) {
+    // fp32 row-layout and split-product kernels: fragment copies only
+    add_frag(M, M.enc_edge.W2, D, D, 2, M.p_enc_edge.F2);
+    add_frag(M, M.enc_edge.W2, D, D, 3, M.p_enc_edge.F2t);
+    add_frag(M, M.enc_node.W2, D, D, 2, M.p_enc_node.F2);
+    add_frag(M, M.enc_node.W2, D, D, 3, M.p_enc_node.F2t);
+    for (int i = 0; i < m; ++i) {
+      add_split(M, M.edge[i].W1, 3 * D, D, 4, M.p_edge[i].S1);
+      add_split(M, M.edge[i].W2, D, D, 4, M.p_edge[i].S2);
+      add_frag(M, M.edge[i].W1, 3 * D, D, 2, M.p_edge[i].F1);
+      add_frag(M, M.edge[i].W2, D, D, 2, M.p_edge[i].F2);
+      add_frag(M, M.edge[i].W1, 3 * D, D, 3, M.p_edge[i].F1t);
+      add_frag(M, M.edge[i].W2, D, D, 3, M.p_edge[i].F2t);
+      add_frag(M, M.edge[i].W1 + D, 3 * D, D, 2, M.p_edge[i].F1s);
+      add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 2, M.p_edge[i].F1r);
+      add_frag(M, M.edge[i].W1 + D, 3 * D, D, 3, M.p_edge[i].F1st);
+      add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 3, M.p_edge[i].F1rt);
+      add_frag(M, M.node[i].W1, 2 * D, D, 2, M.p_node[i].F1);
+      add_frag(M, M.node[i].W1 + D, 2 * D, D, 2, M.p_node[i].F1a);
+      add_frag(M, M.node[i].W2, D, D, 2, M.p_node[i].F2);
+      add_frag(M, M.node[i].W1, 2 * D, D, 3, M.p_node[i].F1t);
+      add_frag(M, M.node[i].W1 + D, 2 * D, D, 3, M.p_node[i].F1at);
+      add_frag(M, M.node[i].W2, D, D, 3, M.p_node[i].F2t);
+    }
+    add_frag(M, M.dec.W1, D, D, 2, M.p_dec.F1);
+    add_frag(M, M.dec.W1, D, D, 3, M.p_dec.F1t);
+    return M;
+  }
   const bool rows = lat == kRowsD;  // row-permuted copies for the row-layout kernels
   add_pack(M, M.enc_node.W2, D, D, M.p_enc_node.W2, M.p_enc_node.W2t);
   if (!rows) add_perm(M, M.enc_node.W2, D, M.p_enc_node.W2p, D, D);  // width-160 node encoder backward
   add_pack(M, M.enc_edge.W2, D, D, M.p_enc_edge.W2, M.p_enc_edge.W2t);
   add_perm(M, M.enc_edge.W2, D, M.p_enc_edge.W2p, D, D);  // row-layout edge encoders
-  if (fp32) {
-    // fp32 row-layout encoders: fragment-major W2 and its transpose
-    add_frag(M, M.enc_edge.W2, D, D, 2, M.p_enc_edge.F2);
-    add_frag(M, M.enc_edge.W2, D, D, 3, M.p_enc_edge.F2t);
-    add_frag(M, M.enc_node.W2, D, D, 2, M.p_enc_node.F2);
-    add_frag(M, M.enc_node.W2, D, D, 3, M.p_enc_node.F2t);
-  }
-  M.p_edge.resize(m);
-  M.p_node.resize(m);
   for (int i = 0; i < m; ++i) {
     add_pack(M, M.edge[i].W1, D, 3 * D, M.p_edge[i].W1, M.p_edge[i].W1t);
     add_pack(M, M.edge[i].W2, D, D, M.p_edge[i].W2, M.p_edge[i].W2t);
@@ -188,29 +218,8 @@ Model make_model(int m, int lat, bool fp32 = false) {
     }
     add_pack(M, M.node[i].W1, D, 2 * D, M.p_node[i].W1, M.p_node[i].W1t);
     add_pack(M, M.node[i].W2, D, D, M.p_node[i].W2, M.p_node[i].W2t);
-    if (fp32) {
-      add_frag(M, M.edge[i].W1, 3 * D, D, 2, M.p_edge[i].F1);
-      add_frag(M, M.edge[i].W2, D, D, 2, M.p_edge[i].F2);
-      add_frag(M, M.edge[i].W1, 3 * D, D, 3, M.p_edge[i].F1t);
-      add_frag(M, M.edge[i].W2, D, D, 3, M.p_edge[i].F2t);
-      add_frag(M, M.edge[i].W1 + D, 3 * D, D, 2, M.p_edge[i].F1s);
-      add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 2, M.p_edge[i].F1r);
-      add_frag(M, M.edge[i].W1 + D, 3 * D, D, 3, M.p_edge[i].F1st);
-      add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 3, M.p_edge[i].F1rt);
-      add_frag(M, M.node[i].W1, 2 * D, D, 2, M.p_node[i].F1);
-      add_frag(M, M.node[i].W1 + D, 2 * D, D, 2, M.p_node[i].F1a);
-      add_frag(M, M.node[i].W2, D, D, 2, M.p_node[i].F2);
-      add_frag(M, M.node[i].W1, 2 * D, D, 3, M.p_node[i].F1t);
-      add_frag(M, M.node[i].W1 + D, 2 * D, D, 3, M.p_node[i].F1at);
-      add_frag(M, M.node[i].W2, D, D, 3, M.p_node[i].F2t);
-    }
   }
   add_pack(M, M.dec.W1, D, D, M.p_dec.W1, M.p_dec.W1t);
-  if (fp32) {
-    // fp32 row-layout decoder: fragment-major W1 and its transpose
-    add_frag(M, M.dec.W1, D, D, 2, M.p_dec.F1);
-    add_frag(M, M.dec.W1, D, D, 3, M.p_dec.F1t);
-  }
   return M;
 }
 
@@ -551,6 +560,8 @@ struct Run {
     w.W1t = p.W1t >= 0 ? P(p.W1t) : nullptr;
     w.W2 = p.W2 >= 0 ? P(p.W2) : nullptr;
     w.W2t = p.W2t >= 0 ? P(p.W2t) : nullptr;
+    w.S1 = p.S1 >= 0 ? P(p.S1) : nullptr;
+    w.S2 = p.S2 >= 0 ? P(p.S2) : nullptr;
     w.F1 = p.F1 >= 0 ? (const float*)P(p.F1) : nullptr;
     w.F2 = p.F2 >= 0 ? (const float*)P(p.F2) : nullptr;
     w.F1t = p.F1t >= 0 ? (const float*)P(p.F1t) : nullptr;
@@ -600,6 +611,12 @@ struct Run {
       for (int j = 0; j < L.n; ++j) L.e[j] = M.ents[b + j];
       LAUNCH(K_PACK, launch_pack(prec, params, pack(), L, s));
     }
+    for (size_t b = 0; b < M.split_ents.size(); b += kPackMax) {
+      PackList L;
+      L.n = (int32_t)std::min<size_t>(kPackMax, M.split_ents.size() - b);
+      for (int j = 0; j < L.n; ++j) L.e[j] = M.split_ents[b + j];
+      LAUNCH(K_PACK, launch_pack_split(params, pack(), L, s));
+    }
     return MGN_OK;
   }
 
@@ -629,7 +646,7 @@ struct Run {
       const void* e_in = l == 0 ? e_enc() : e_l(k, l);
       void* e_out = c.save ? (last ? nullptr : e_l(k, l + 1)) : e_l(k, 0);
       if (E > 0 && prec == MGN_FP32)
-        LAUNCH(K_EDGE_FWD, launch_edge_fwd_r32(D, tl, e_in, e_out, last ? 0 : 1, P_l(k, l),
+        LAUNCH(K_EDGE_FWD, launch_edge_fwd_x3(D, tl, e_in, e_out, last ? 0 : 1, P_l(k, l),
                                                W(M.edge[l], M.p_edge[l]), eps, agg_l(k, l), slots(), s));
       else if (E > 0)
         LAUNCH(K_EDGE_FWD, rows() ? launch_edge_fwd_rows(tl, e_in, e_out, last ? 0 : 1, P_l(k, l),

@@ -13,18 +13,6 @@ namespace mgn {
 namespace dev {
 
 
-template <int LD>
-struct __attribute__((aligned(16))) Fwd32Lds {
-  // At width 128 both products' fragment-major weights fit in LDS (64 KB
-  // each) beside an unpadded message staging (exactly 160 KiB); at 160 only
-  // W2 (100 KB) does, and the staging rows are padded.
-  static constexpr bool W1L = LD == 128;
-  static constexpr int SS = W1L ? LD : R32<LD>::SLD;  // staging row stride
-  __attribute__((aligned(16))) float stage[R32_NW][16 * SS];
-  __attribute__((aligned(16))) float w2[LD * LD];
-  __attribute__((aligned(16))) float w1[W1L ? LD * LD : 4];
-};
-
 // In-segment node sums over one staged 16-row half [lo_row, lo_row + 16) of
 // a tile (as in the bf16 forward): node j's rows are [rp(j) - base,
 // rp(j + 1) - base), rp(j) held by lane j of segraw; a chunk tile is the
@@ -58,147 +46,6 @@ __device__ __forceinline__ void seg_pass32(const float* stage, int lane, int seg
     ++j;
   }
 }
-
-// Forward: e' = e + m (when write_e), agg = receiver sums of m, with
-// m = LN(W2 relu(b1 + P_s + P_r + W1e e) + b2) (the node products P = [W1s
-// h, W1r h] of the block come from the node kernels).  The next half's rows
-// are in flight while a half is computed; all global loads are
-// unconditional from clamped indices (rows past a tile's end read a valid
-// row that is never stored or summed).
-template <int LD>
-__global__ void __launch_bounds__(R32_NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_edge_fwd_r32(EdgeTiles tl, const float* __restrict__ e_in, float* __restrict__ e_out, int write_e,
-               const float* __restrict__ Pn, MlpW w, float eps, float* __restrict__ agg, float* __restrict__ slots) {
-  typedef R32<LD> Z;
-  __shared__ __align__(16) Fwd32Lds<LD> S;
-  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  typedef Fwd32Lds<LD> L;
-  for (int idx = tid; idx < LD * LD / 4; idx += R32_NT) {
-    reinterpret_cast<f32x4*>(S.w2)[idx] = reinterpret_cast<const f32x4*>(w.F2)[idx];
-    if (L::W1L) reinterpret_cast<f32x4*>(S.w1)[idx] = reinterpret_cast<const f32x4*>(w.F1)[idx];
-  }
-  __syncthreads();
-  const UnitRange ur = unit_range<R32_NW>(tl.n_tiles, wv);
-  int64_t t = ur.t;
-  const int64_t stride = ur.stride, tend = ur.end;
-  if (t >= tend) return;
-  const int f0 = Z::KL * g;  // first feature of the lane
-
-  const int4* tiles = reinterpret_cast<const int4*>(tl.tiles);
-  auto desc = [&](int64_t tt) -> int4 {
-    const bool ok = tt < tend;
-    const int4 v = tiles[ok ? tt : tend - 1];
-    int4 r;
-    r.x = ok ? v.x : 0;
-    r.y = ok ? v.y : 0;
-    r.z = ok ? v.z : 0;
-    r.w = ok ? v.w : 0;
-    return r;
-  };
-  const int lastE = (int)max(tl.n_edges - 1, (int64_t)0);
-  auto erow = [&](int4 d, int rb) { return min(max(d.z + min(rb * 16 + i, tile_rows(d) - 1), 0), lastE); };
-  struct Half {
-    float e[Z::KL];
-    f32x4 p[Z::NOB];  // b1 + P_s + P_r in the C layout
-  };
-  auto load_half = [&](int4 d, int rb, Half& H) {
-    const int row = erow(d, rb);
-    const int snd = tl.senders[row], rcv = tl.receivers[row];
-    load_row32<LD>(H.e, e_in + (size_t)row * LD + f0);
-    const float* ps = Pn + (size_t)snd * (2 * LD) + f0;
-    const float* pr = Pn + (size_t)rcv * (2 * LD) + LD + f0;
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) {
-      const f32x4 b1 = *reinterpret_cast<const f32x4*>(w.b1 + f0 + 4 * ob);
-      const f32x4 a = *reinterpret_cast<const f32x4*>(ps + 4 * ob);
-      const f32x4 b = *reinterpret_cast<const f32x4*>(pr + 4 * ob);
-      H.p[ob] = (b1 + a) + b;
-    }
-  };
-  float* stage = S.stage[wv];
-
-  auto half = [&](Half& H, int4 d0, int rb, int segraw, bool chunk, int nv, int& j, float2 (&carry)[2]) {
-    const int n = tile_rows(d0);
-    const int row = rb * 16 + i;
-    // ---- z1 = b1 + P_s + P_r + W1e e, a1 = relu(z1)
-    f32x4 acc[Z::NOB];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = H.p[ob];
-    // the weight addresses are opaque per half: otherwise the loop-invariant
-    // fragment loads are hoisted out of the tile loop into registers
-    const int oz = opaque_zero();
-    gemm32<LD>(acc, H.e, (L::W1L ? S.w1 : w.F1) + oz, lane);
-    float a1[Z::KL];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) a1[4 * ob + r] = relu(acc[ob][r]);
-    // ---- z2 = b2 + W2 a1
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = *reinterpret_cast<const f32x4*>(w.b2 + f0 + 4 * ob);
-    gemm32<LD>(acc, a1, S.w2 + oz, lane);
-    // ---- LayerNorm over the row's DR real features (padded ones are 0)
-    float sm = 0.f;
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sm += acc[ob][r];
-    const float mean = sum_q(sm) * (1.0f / Z::DR);
-    float sq = 0.f;
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float dlt = acc[ob][r] - mean;
-        acc[ob][r] = dlt;
-        if (Z::DR == LD || f0 + 4 * ob + r < Z::DR) sq += dlt * dlt;
-      }
-    const float rstd = __builtin_amdgcn_rsqf(sum_q(sq) * (1.0f / Z::DR) + eps);
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) {
-      const f32x4 ga = *reinterpret_cast<const f32x4*>(w.gamma + f0 + 4 * ob);
-      const f32x4 be = *reinterpret_cast<const f32x4*>(w.beta + f0 + 4 * ob);
-      acc[ob] = ga * (acc[ob] * rstd) + be;  // message m
-    }
-    store_row32<LD>(stage + i * L::SS + f0, acc);
-    // ---- e_out = e + m
-    if (write_e && row < n) {
-      f32x4 o[Z::NOB];
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[ob][r] = H.e[4 * ob + r] + acc[ob][r];
-      store_row32<LD>(e_out + ((size_t)d0.z + row) * LD + f0, o);
-    }
-    wave_lds_sync();
-    seg_pass32<LD>(stage, lane, segraw, d0.z, chunk, n, nv, rb * 16, j, carry, [&](int jj, float2 (&v)[2]) {
-      float* dst = !chunk ? agg + (size_t)(d0.x + jj) * LD : slots + (size_t)(-1 - d0.y) * LD;
-      *reinterpret_cast<float2*>(dst + 2 * lane) = v[0];
-      if (LD / 2 > 64 && lane + 64 < LD / 2) *reinterpret_cast<float2*>(dst + 2 * (lane + 64)) = v[1];
-    }, L::SS);
-    wave_lds_sync();
-  };
-
-  int4 d0 = desc(t), d1 = desc(t + stride);
-  Half A, B;
-  load_half(d0, 0, A);
-  for (; t < tend; t += stride) {
-    const bool chunk = d0.y < 0;
-    const int nv = chunk ? 1 : d0.y - d0.x;
-    const int segraw = tl.rowptr[min(d0.x + lane, max(d0.x, d0.y))];
-    const int4 d2 = desc(t + 2 * stride);
-    load_half(d0, 1, B);
-    float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};
-    int j = 0;
-    half(A, d0, 0, segraw, chunk, nv, j, carry);
-    load_half(d1, 0, A);
-    half(B, d0, 1, segraw, chunk, nv, j, carry);
-    d0 = d1;
-    d1 = d2;
-  }
-}
-
 
 // ================================================================= reverse
 // fp32 edge reverse with its weight gradients in one pass (width 128): per
@@ -1374,21 +1221,6 @@ k_edge_enc_bwd_r32(int64_t E, const float* __restrict__ f_in, const float* __res
 using namespace dev;
 
 static constexpr int kRows32Blocks = 256;
-
-hipError_t launch_edge_fwd_r32(int lat, const EdgeTiles& t, const void* e_in, void* e_out, int write_e,
-                               const void* Pn, const MlpW& w, float eps, float* agg, float* slots, hipStream_t s) {
-  if (t.n_tiles <= 0) return hipSuccess;
-  if (t.n_edges <= 0 || !w.F1 || !w.F2) return hipErrorInvalidValue;
-  const int64_t need = (t.n_tiles + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, kRows32Blocks);
-  if (g >= 8) g &= ~7;
-#define F(LD)                                                                                                      \
-  hipLaunchKernelGGL(k_edge_fwd_r32<LD>, dim3(g), dim3(R32_NT), 0, s, t, (const float*)e_in, (float*)e_out, write_e, \
-                     (const float*)Pn, w, eps, agg, slots)
-  MGN_BY_WIDTH(lat, F);
-#undef F
-  return hipGetLastError();
-}
 
 hipError_t launch_edge_bwd_r32(int lat, const EdgeTiles& t, const void* e, const float* ebar_in, int have_ebar,
                                float* ebar_out, const void* Pn, const float* aggbar, const MlpW& w, float eps,

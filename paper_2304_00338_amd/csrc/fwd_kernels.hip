@@ -10,6 +10,7 @@
 // fp32 summation order differs.
 #include "dev_common.hpp"
 #include "launch.hpp"
+#include "split32_common.hpp"
 
 namespace mgn {
 namespace dev {
@@ -44,6 +45,45 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ params, 
     pack[pe.dst + idx] = v;
     if (pe.dstt >= 0) pack[pe.dstt + c * pe.rows + r] = v;
   }
+}
+
+// Two-piece fp16 fragments for the fp32 split products (square n x n matrix M
+// = W, or W^T when perm == 5; n a multiple of 32): M[o][k] with o = KL oh + 16
+// ob + r and k = KL kh + 8 ks + t (KL = n / 2) is element t of lane m + 32 kh,
+// m = r % 4 + 8 (r / 4) + 4 oh, of the fragments (ks, ob, piece), scaled by the
+// power of two that brings the largest |M| into [2^14, 2^15); its exponent
+// follows the fragments.  Every block forms the maximum itself (a matrix is at
+// most 100 KB, read once from L2) and then writes its share: a separate
+// launch for the maxima would cost a small call more than the packing.
+__global__ void __launch_bounds__(1024) k_pack_split(const float* __restrict__ params, float* __restrict__ pack,
+                                                     PackList L) {
+  __shared__ float wm[16];
+  const PackEnt pe = L.e[blockIdx.y];
+  const int tid = threadIdx.x, n = pe.rows * pe.rows;
+  float mx = 0.f;
+#pragma unroll 8
+  for (int idx = tid; idx < n; idx += 1024)
+    mx = fmaxf(mx, fabsf(params[pe.src + (int64_t)(idx / pe.rows) * pe.ld + idx % pe.rows]));
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+  if ((tid & 63) == 0) wm[tid >> 6] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) mx = fmaxf(mx, wm[k]);
+  const int e = scale_exp(mx);
+  const float s = scale_of(e);
+  const int KL = pe.rows / 2, NOB = pe.rows / 32;
+  _Float16* dst = reinterpret_cast<_Float16*>(pack + pe.dst);
+  for (int idx = blockIdx.x * 1024 + tid; idx < n; idx += gridDim.x * 1024) {
+    const int t = idx & 7, l = (idx >> 3) & 63, rest = idx >> 9, ob = rest % NOB, ks = rest / NOB, m = l & 31;
+    const int64_t o = KL * ((m >> 2) & 1) + 16 * ob + (m & 3) + 4 * (m >> 3), k = KL * (l >> 5) + 8 * ks + t;
+    const float v = s * params[pe.perm == 4 ? pe.src + o * pe.ld + k : pe.src + k * pe.ld + o];
+    const _Float16 h = (_Float16)v;
+    _Float16* q = dst + (int64_t)rest * 2 * 512 + l * 8 + t;
+    q[0] = h;
+    q[512] = (_Float16)(v - (float)h);
+  }
+  if (blockIdx.x == 0 && tid == 0) *reinterpret_cast<int*>(pack + pe.dst + n) = e;
 }
 
 // Node products for the next block's edge MLP: P[v] = [W1s h_v, W1r h_v].
@@ -207,6 +247,12 @@ int part_grid(int64_t n_tiles, int max_blocks) {
 }
 
 static constexpr int kFwdBlocks = 1024;
+
+hipError_t launch_pack_split(const float* params, void* pack, const PackList& L, hipStream_t s) {
+  if (L.n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_pack_split, dim3(8, L.n), dim3(1024), 0, s, params, (float*)pack, L);
+  return hipGetLastError();
+}
 
 hipError_t launch_pack(int prec, const float* params, void* pack, const PackList& L, hipStream_t s) {
   if (L.n <= 0) return hipSuccess;

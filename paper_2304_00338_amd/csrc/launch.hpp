@@ -30,6 +30,8 @@ struct MlpW {
   const float* F1r;   // (the node products P = [W1s h, W1r h]) and their transposes
   const float* F1st;
   const float* F1rt;
+  const void* S1;    // fp32 split products (pack modes 4, 5): two-piece fp16
+  const void* S2;    // fragments of the edge MLP's W1e and W2
   const float* W1f;  // float32 first-layer weights (encoders: K = 4 / 8 on VALU)
   const float* W2f;  // float32 second-layer weights (decoder: 4 outputs on VALU)
   const float* b1;
@@ -45,7 +47,9 @@ struct PackEnt {
   int32_t rows, cols;
   int32_t ld;    // source row stride (floats)
   int32_t perm;  // 1: copy row perm_row(p) of the source into row p; 2 / 3: the
-                 // fp32 fragment-major copy of the square matrix / of its transpose
+                 // fp32 fragment-major copy of the square matrix / of its transpose;
+                 // 4 / 5 (launch_pack_split): the two-piece fp16
+                 // fragments of it / of its transpose
 };
 
 // Output-row order of the weights used by the row-per-wave edge kernels:
@@ -90,6 +94,8 @@ int grid_for(int64_t n_tiles, int max_blocks);
 int part_grid(int64_t n_tiles, int max_blocks);
 
 hipError_t launch_pack(int prec, const float* params, void* pack, const PackList& L, hipStream_t s);
+// Entries of mode 4 / 5 (n^2 + 1 floats at dst: the fragments, then the scale's exponent).
+hipError_t launch_pack_split(const float* params, void* pack, const PackList& L, hipStream_t s);
 
 // Feature-split kernels: lat is the kernel width (128, or 160 for the
 // latent 150 padded with zero columns).  bf16 at width 128 runs on the
@@ -149,11 +155,12 @@ hipError_t launch_edge_enc_bwd_r32(int lat, int64_t E, const float* f, const voi
 // (nullable) receives the first-layer activations of every edge.
 hipError_t launch_edge_fwd_rows(const EdgeTiles& t, const void* e_in, void* e_out, int write_e, const void* P,
                                 const MlpW& w, float eps, float* agg, float* slots, void* a1_out, hipStream_t s);
-// fp32 edge forward with one wave per 16-row half of a tile at width lat
-// (128 or 160; uses MlpW::F1 / F2, the fragment-major W1e and W2, and the
-// fp32 vectors): e_out = e_in + m (write_e), agg / slots = receiver sums of m.
-hipError_t launch_edge_fwd_r32(int lat, const EdgeTiles& t, const void* e_in, void* e_out, int write_e,
-                               const void* Pn, const MlpW& w, float eps, float* agg, float* slots, hipStream_t s);
+// fp32 edge forward with one wave per tile at width lat (128 or 160; uses
+// MlpW::S1 / S2, the split fragments of W1e and W2, and the fp32 vectors):
+// e_out = e_in + m (write_e; in place allowed), agg / slots = receiver sums of
+// m.
+hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& t, const void* e_in, void* e_out, int write_e, const void* Pn,
+                              const MlpW& w, float eps, float* agg, float* slots, hipStream_t s);
 // fp32 edge backward at width 128 with its weight gradients in one pass (one
 // wave per row block, four waves per block in lockstep rounds; recomputes
 // the first layer from e and P; uses MlpW::F1, F2, F1t, F2t): writes zbar,
