@@ -38,7 +38,8 @@ struct Off {
 struct PackOff {
   int64_t W1 = -1, W1t = -1, W2 = -1, W2t = -1, W1p = -1, W2p = -1;
   int64_t F1 = -1, F2 = -1, F1t = -1, F2t = -1;  // fp32 edge MLPs (encoder: W2): fragment-major W1e, W2, transposes
-  int64_t S1 = -1, S2 = -1;  // fp32 split products: two-piece fp16 fragments (edge MLPs: W1e, W2)
+  // fp32 split products: two-piece fp16 fragments (edge MLPs: W1e, W2 and their transposes)
+  int64_t S1 = -1, S2 = -1, S1t = -1, S2t = -1;
   int64_t W1sp = -1, W1rp = -1;  // edge MLPs: row-permuted sender / receiver column blocks of W1
   int64_t W1ap = -1;             // node MLPs at width 160: row-permuted agg column block of W1
   // fp32 row-layout node kernels: node MLPs' W1 agg block (F1: its h block),
@@ -170,10 +171,8 @@ Model make_model(int m, int lat, bool fp32 = false) {
     for (int i = 0; i < m; ++i) {
       add_split(M, M.edge[i].W1, 3 * D, D, 4, M.p_edge[i].S1);
       add_split(M, M.edge[i].W2, D, D, 4, M.p_edge[i].S2);
-      add_frag(M, M.edge[i].W1, 3 * D, D, 2, M.p_edge[i].F1);
-      add_frag(M, M.edge[i].W2, D, D, 2, M.p_edge[i].F2);
-      add_frag(M, M.edge[i].W1, 3 * D, D, 3, M.p_edge[i].F1t);
-      add_frag(M, M.edge[i].W2, D, D, 3, M.p_edge[i].F2t);
+      add_split(M, M.edge[i].W1, 3 * D, D, 5, M.p_edge[i].S1t);
+      add_split(M, M.edge[i].W2, D, D, 5, M.p_edge[i].S2t);
       add_frag(M, M.edge[i].W1 + D, 3 * D, D, 2, M.p_edge[i].F1s);
       add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 2, M.p_edge[i].F1r);
       add_frag(M, M.edge[i].W1 + D, 3 * D, D, 3, M.p_edge[i].F1st);
@@ -562,6 +561,8 @@ struct Run {
     w.W2t = p.W2t >= 0 ? P(p.W2t) : nullptr;
     w.S1 = p.S1 >= 0 ? P(p.S1) : nullptr;
     w.S2 = p.S2 >= 0 ? P(p.S2) : nullptr;
+    w.S1t = p.S1t >= 0 ? P(p.S1t) : nullptr;
+    w.S2t = p.S2t >= 0 ? P(p.S2t) : nullptr;
     w.F1 = p.F1 >= 0 ? (const float*)P(p.F1) : nullptr;
     w.F2 = p.F2 >= 0 ? (const float*)P(p.F2) : nullptr;
     w.F1t = p.F1t >= 0 ? (const float*)P(p.F1t) : nullptr;
@@ -726,7 +727,7 @@ struct Run {
       float* dz1 = (float*)(ws + c.L.nstr);
       LAUNCH(K_DECODER_BWD, launch_decoder_bwd_r32(D, N, h_l(k, m), gout, W(M.dec, M.p_dec), hb_cur, dz1, pt, &nb, s));
       if ((rc = reduce(nb, 0, 1, 5 * D + 4, grad, M.dec.b1, 0)) != MGN_OK) return rc;
-      LAUNCH(K_DECODER_BWD, launch_wgrad_r32(D, N, dz1, h_l(k, m), pt, &nb, s));
+      LAUNCH(K_DECODER_BWD, launch_wgrad_x3(D, N, dz1, h_l(k, m), pt, &nb, s));
       if ((rc = reduce(nb, 0, D, D, grad, M.dec.W1, D)) != MGN_OK) return rc;
     } else {
       LAUNCH(K_DECODER_BWD, launch_decoder_bwd(prec, D, N, h_l(k, m), gout, W(M.dec, M.p_dec), hb_cur, pt, &nb, s));
@@ -765,13 +766,13 @@ struct Run {
         if ((rc = job(nb, 0, D, 1, D, grad, on.b2, 0)) != MGN_OK) return rc;
         if ((rc = job(nb, 0, 2 * D, 1, 2 * D, grad, on.g, 0)) != MGN_OK) return rc;
         Partials q = P1;
-        LAUNCH(K_WGRAD_NODE, launch_wgrad_r32(D, N, ns + 2 * nd, h_l(k, l), q, &nb, s));
+        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, N, ns + 2 * nd, h_l(k, l), q, &nb, s));
         if ((rc = job(nb, 1, 0, D, D, grad, on.W1, 2 * D)) != MGN_OK) return rc;
         q.buf += (size_t)D * D;
-        LAUNCH(K_WGRAD_NODE, launch_wgrad_r32(D, N, ns + 2 * nd, agg_l(k, l), q, &nb, s));
+        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, N, ns + 2 * nd, agg_l(k, l), q, &nb, s));
         if ((rc = job(nb, 1, (int64_t)D * D, D, D, grad, on.W1 + D, 2 * D)) != MGN_OK) return rc;
         q.buf += (size_t)D * D;
-        LAUNCH(K_WGRAD_NODE, launch_wgrad_r32(D, N, ns + nd, ns, q, &nb, s));
+        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, N, ns + nd, ns, q, &nb, s));
         if ((rc = job(nb, 1, 2 * (int64_t)D * D, D, D, grad, on.W2, D)) != MGN_OK) return rc;
       }
       if (E == 0) {
@@ -797,24 +798,14 @@ struct Run {
         LAUNCH(K_WGRAD, launch_wgrad2_w160(E, zbar, e_l(k, l), dz, a1_l(k, l), P3, &nb, s));
         if ((rc = job(nb, 3, 0, D, D, grad, oe.W1, 3 * D)) != MGN_OK) return rc;
         if ((rc = job(nb, 3, (int64_t)D * D, D, D, grad, oe.W2, D)) != MGN_OK) return rc;
-      } else if (D == kRowsD) {
-        // fp32, width 128: one wave per row block, the reverse and the edge
-        // MLP's weight gradients in one pass
-        LAUNCH(K_EDGE_BWD, launch_edge_bwd_r32(D, tl, e_l(k, l), (float*)ebar, l < m - 1 ? 1 : 0, (float*)ebar,
-                                               P_l(k, l), aggbar, W(oe, M.p_edge[l]), eps, zbar, R, slots(), P2, &nb,
-                                               s));
-        if ((rc = job(nb, 2, 0, D, D, grad, oe.W1, 3 * D)) != MGN_OK) return rc;
-        if ((rc = job(nb, 2, 16384, 1, D, grad, oe.b1, 0)) != MGN_OK) return rc;
-        if ((rc = job(nb, 2, 16512, 1, D * D + D, grad, oe.W2, 0)) != MGN_OK) return rc;
-        if ((rc = job(nb, 2, 33024, 1, 2 * D, grad, oe.g, 0)) != MGN_OK) return rc;
       } else {
-        // fp32, width 160: one wave per row block (dW2 and the vectors in the
-        // pass), then dW1e = sum zbar^T e over the two streams
-        LAUNCH(K_EDGE_BWD, launch_edge_bwd_r32(D, tl, e_l(k, l), (float*)ebar, l < m - 1 ? 1 : 0, (float*)ebar,
-                                               P_l(k, l), aggbar, W(oe, M.p_edge[l]), eps, zbar, R, slots(), P2, &nb,
-                                               s));
+        // fp32: one wave per tile (dW2 and the vectors in the pass), then
+        // dW1e = sum zbar^T e over the two streams
+        LAUNCH(K_EDGE_BWD, launch_edge_bwd_x3(D, tl, e_l(k, l), (float*)ebar, l < m - 1 ? 1 : 0, (float*)ebar,
+                                              P_l(k, l), aggbar, W(oe, M.p_edge[l]), eps, zbar, R, slots(), P2, &nb,
+                                              s));
         if ((rc = job(nb, 2, (int64_t)D * D, 1, (int)(oe.size - 3 * D * D), grad, oe.b1, 0)) != MGN_OK) return rc;
-        LAUNCH(K_WGRAD, launch_wgrad_r32(D, E, (const float*)zbar, (const float*)e_l(k, l), P3, &nb, s));
+        LAUNCH(K_WGRAD, launch_wgrad_x3(D, E, (const float*)zbar, (const float*)e_l(k, l), P3, &nb, s));
         if ((rc = job(nb, 3, 0, D, D, grad, oe.W1, 3 * D)) != MGN_OK) return rc;
       }
       if (g.n_long > 0) LAUNCH(K_FIXUP, launch_slot_fixup(D, g.long_nodes, g.n_long, slots(), R, s));
@@ -830,10 +821,10 @@ struct Run {
         LAUNCH(K_SRCSUM, launch_node_srcsum_r32(D, N, g.rowptr, g.rev, (const float*)zbar, R, hb_part,
                                                 W(oe, M.p_edge[l]), hb_cur, Sv, s));
         Partials q = P4;
-        LAUNCH(K_SRCSUM, launch_wgrad_r32(D, N, Sv, h_l(k, l), q, &nb, s));
+        LAUNCH(K_SRCSUM, launch_wgrad_x3(D, N, Sv, h_l(k, l), q, &nb, s));
         if ((rc = job(nb, 4, 0, D, D, grad, oe.W1 + D, 3 * D)) != MGN_OK) return rc;
         q.buf += (size_t)D * D;
-        LAUNCH(K_SRCSUM, launch_wgrad_r32(D, N, R, h_l(k, l), q, &nb, s));
+        LAUNCH(K_SRCSUM, launch_wgrad_x3(D, N, R, h_l(k, l), q, &nb, s));
         if ((rc = job(nb, 4, (int64_t)D * D, D, D, grad, oe.W1 + 2 * D, 3 * D)) != MGN_OK) return rc;
       } else {
         LAUNCH(K_SRCSUM, launch_node_srcsum(prec, D, N, g.rowptr, g.rev, zbar, R, h_l(k, l), hb_part, W(oe, M.p_edge[l]),
@@ -872,7 +863,7 @@ struct Run {
       LAUNCH(K_NODE_ENC_BWD, launch_node_enc_bwd_r32(D, N, node_in, hb_cur, W(o, M.p_enc_node), eps, gin, ns, pt, &nb, s));
       if ((rc = reduce(nb, 0, 1, 9 * D, grad, o.W1, 0)) != MGN_OK) return rc;
       if ((rc = reduce(nb, 9 * D, 1, 3 * D, grad, o.b2, 0)) != MGN_OK) return rc;
-      LAUNCH(K_NODE_ENC_BWD, launch_wgrad_r32(D, N, ns + (size_t)N * D, ns, pt, &nb, s));
+      LAUNCH(K_NODE_ENC_BWD, launch_wgrad_x3(D, N, ns + (size_t)N * D, ns, pt, &nb, s));
       if ((rc = reduce(nb, 0, D, D, grad, o.W2, D)) != MGN_OK) return rc;
     } else {
       LAUNCH(K_NODE_ENC_BWD, launch_node_enc_bwd(prec, D, N, node_in, hb_cur, W(M.enc_node, M.p_enc_node), eps, gin, pt,

@@ -30,7 +30,10 @@ __device__ __forceinline__ uint32_t segment_ends(int row, int n, int rcv, bool c
 // m = LN(W2 relu(b1 + P_s + P_r + W1e e) + b2) (the node products P = [W1s
 // h, W1r h] of the block come from the node kernels).  Two blocks per CU, so
 // one block's loads, LayerNorm and barriers lie under the other's MFMAs; that
-// leaves 256 registers, hence e is read again for the residual.  Rows past a
+// leaves 256 registers, hence e is read again for the residual.  Measured per
+// launch: 434,558 edges at width 128 0.360 -> 0.190 ms (fp32 MFMA version ->
+// this; 0.125 ms without its memory traffic, which alone takes 0.095 ms at the
+// copy rate), the eight-patch batch at width 160 1.11 -> 0.52 ms.  Rows past a
 // tile's end, and tiles past the block's range, read a valid row that is
 // never stored or summed.
 template <int LD>
@@ -42,7 +45,7 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
   __shared__ Lds S;
   const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, hh = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int f0 = Z::KL * hh;
+  const int f0 = 8 * hh;  // the lane's first feature
   const u32x4 *W1 = (const u32x4*)w.S1, *W2 = (const u32x4*)w.S2;
   const BlockRange br = block_range(tl.n_tiles);
   if (br.tb >= br.tend) return;
@@ -67,32 +70,31 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
   for (int64_t t = br.tb; t < br.tend; t += br.stride) {
     const int4 dn = desc(t + br.stride + wv);
     const int n = tile_rows(d);
-    const size_t grow = (size_t)erow(d);
+    const TileRow<LD> tr(d, lastE, row, hh);
     const bool chunk = d.y < 0;
     // ---- z1 = W1e e + ((b1 + P_s) + P_r), a1 = relu(z1); the gathered node
     // products are requested while the product runs
     f32x16 acc[Z::NOB];
     float x[Z::KL];
-    load_row_x3<LD>(x, e_in + grow * LD + f0);
-    // P_s and P_r of the features that chunk c has freed x's registers of,
-    // summed one chunk later
-    constexpr int Q = Z::KL / 4 / Z::NC;
-    f32x4 p[Z::KL / 4], ps[Q], pr[Q];
-    auto add_p = [&](int c) {
+    load_row_x3<LD>(x, tr.at(e_in));
+    // P_s and P_r of the features that K step ks has freed x's registers of,
+    // summed one step later
+    f32x4 p[Z::KL / 4], ps[2], pr[2];
+    auto add_p = [&](int ks) {
 #pragma unroll
-      for (int k = 0; k < Q; ++k)
-        p[c * Q + k] = (*reinterpret_cast<const f32x4*>(S.vec[0] + f0 + 4 * (c * Q + k)) + ps[k]) + pr[k];
+      for (int k = 0; k < 2; ++k)
+        p[2 * ks + k] = (*reinterpret_cast<const f32x4*>(S.vec[0] + f0 + 16 * ks + 4 * k) + ps[k]) + pr[k];
     };
-    gemm_x3<LD, 0>(acc, x, W1, W2, S.w, tid, [&](int c) {
-      if (c > 0) add_p(c - 1);
-      const float* q = Pn + f0 + 4 * c * Q;
+    gemm_x3<LD, 0>(acc, x, W1, W2, S.w, tid, [&](int ks) {
+      if (ks > 0) add_p(ks - 1);
+      const float* q = Pn + f0 + 16 * ks;
 #pragma unroll
-      for (int k = 0; k < Q; ++k) {
+      for (int k = 0; k < 2; ++k) {
         ps[k] = *reinterpret_cast<const f32x4*>(q + (size_t)snd * (2 * LD) + 4 * k);
         pr[k] = *reinterpret_cast<const f32x4*>(q + (size_t)rcv * (2 * LD) + LD + 4 * k);
       }
     });
-    add_p(Z::NC - 1);
+    add_p(Z::KS - 1);
 #pragma unroll
     for (int c = 0; c < Z::KL / 4; ++c)
 #pragma unroll
@@ -101,46 +103,48 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
     gemm_x3<LD, Z::NC & 1>(acc, x, W2, W1, S.w, tid);
 #pragma unroll
     for (int c = 0; c < Z::KL / 4; ++c) {
-      const f32x4 b2 = *reinterpret_cast<const f32x4*>(S.vec[1] + f0 + 4 * c);
+      const f32x4 b2 = *reinterpret_cast<const f32x4*>(S.vec[1] + f0 + Z::pf(c));
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[c >> 2][4 * (c & 3) + r] += b2[r];
     }
-    // the next tile's ids and the residual's e, in flight during the LayerNorm
+    // the next tile's ids, in flight during the LayerNorm
     const int snd_n = tl.senders[erow(dn)], rcv_n = tl.receivers[erow(dn)];
-    if (write_e) load_row_x3<LD>(x, e_in + grow * LD + f0);
-    ln_x3<LD>(acc, f0, eps);
+    ln_x3<LD>(acc, hh, eps);
 #pragma unroll
     for (int c = 0; c < Z::KL / 4; ++c) {
-      const f32x4 ga = *reinterpret_cast<const f32x4*>(S.vec[2] + f0 + 4 * c);
-      const f32x4 be = *reinterpret_cast<const f32x4*>(S.vec[3] + f0 + 4 * c);
+      const f32x4 ga = *reinterpret_cast<const f32x4*>(S.vec[2] + f0 + Z::pf(c));
+      const f32x4 be = *reinterpret_cast<const f32x4*>(S.vec[3] + f0 + Z::pf(c));
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[c >> 2][4 * (c & 3) + r] = ga[r] * acc[c >> 2][4 * (c & 3) + r] + be[r];  // m
     }
-    // ---- e_out = e + m
-    if (write_e && row < n) {
-      float* op = e_out + grow * LD + f0;
-#pragma unroll
-      for (int c = 0; c < Z::KL / 4; ++c) {
-        f32x4 o;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = x[4 * c + r] + acc[c >> 2][4 * (c & 3) + r];
-        *reinterpret_cast<f32x4*>(op + 4 * c) = o;
-      }
-    }
-    // ---- receiver sums, SR rows at a time
+    // ---- receiver sums, SR rows at a time, and e_out = e + m: read and
+    // written as whole rows here, where the messages lie row by row
     const uint32_t ends = segment_ends(row, n, rcv, chunk);
-    float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};
+    float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}}, tot[2] = {{0.f, 0.f}, {0.f, 0.f}};
     float* stage = S.stage[wv];
 #pragma unroll
     for (int r0 = 0; r0 < 32; r0 += Lds::SR) {
       if (row / Lds::SR == r0 / Lds::SR)
 #pragma unroll
         for (int c = 0; c < Z::KL / 4; ++c)
-          *reinterpret_cast<f32x4*>(stage + (row - r0) * Lds::SL + f0 + 4 * c) =
+          *reinterpret_cast<f32x4*>(stage + (row - r0) * Lds::SL + f0 + Z::pf(c)) =
               f32x4{acc[c >> 2][4 * (c & 3)], acc[c >> 2][4 * (c & 3) + 1], acc[c >> 2][4 * (c & 3) + 2],
                     acc[c >> 2][4 * (c & 3) + 3]};
       wave_lds_sync();
-      seg_sums<LD, Lds::SL, Lds::SR>(stage, lane, ends, r0, rcv, chunk, slots + (size_t)(-1 - d.y) * LD, agg, carry);
+      seg_sums<LD, Lds::SL, Lds::SR>(stage, lane, ends, r0, rcv, chunk, slots + (size_t)(-1 - d.y) * LD, agg, carry,
+                                     tot, [&](const float2 (&v)[Lds::SR], int p, bool on) {
+        if (!write_e) return;
+        float2 e[Lds::SR];
+        const uint32_t o = 2 * (on ? p : lane);
+#pragma unroll
+        for (int u = 0; u < Lds::SR; ++u)
+          e[u] = *reinterpret_cast<const float2*>(e_in + tr.base + (size_t)max(min(r0 + u, n - 1), 0) * LD + o);
+#pragma unroll
+        for (int u = 0; u < Lds::SR; ++u)
+          if (r0 + u < n && on)
+            *reinterpret_cast<float2*>(e_out + tr.base + (size_t)(r0 + u) * LD + o) =
+                float2{e[u].x + v[u].x, e[u].y + v[u].y};
+      });
       wave_lds_sync();
     }
     if (!chunk && d.y > d.x) zero_empty<LD>(d, tl.rowptr, lane, agg);
@@ -148,6 +152,250 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
     snd = snd_n;
     rcv = rcv_n;
   }
+}
+
+// ================================================================= reverse
+// Edge reverse with dW2 in the same pass: per tile, from the block's input
+// edge latents e, the node products P (the first layer is recomputed as in
+// the forward) and the incoming gradients (ebar_in, aggbar at the receiver),
+// it writes zbar = dL/dz1 (for the sender sums and dW1e), the receiver sums R
+// of zbar and ebar_out = ebar_in + W1e^T zbar, and accumulates dW2 = sum dz2^T
+// a1 (DwAcc), db2, dgamma, dbeta (column sums) and db1 (the sum of the
+// receiver sums).  dW1e = sum zbar^T e is a pass of its own over the two
+// streams (k_wgrad_x3).  One block per CU.  At width 128 it has eight waves,
+// two per SIMD: in 256 registers a wave holds the pieces of a1 and dz2, one
+// product and an eighth of dW2 (ebar_in is read twice instead of being kept).
+// At width 160 that does not fit, and the block has four waves of 512.
+//   Measured per launch: 434,558 edges at width 128 1.11 -> 0.57 ms (fp32 MFMA
+// version, dW1e included, -> this; its dW1e pass takes 0.11 ms), the eight-patch
+// batch (0.9M edges) at width 160 2.62 -> 1.78 ms.  With its loads and stores
+// taken away it still takes 0.49 ms of 0.62: the arithmetic of the phases that
+// the eight waves enter together is what bounds it, not memory.
+// Partials per block: db1 at LD^2, dW2, db2, dgamma, dbeta.
+template <int LD>
+struct EdgeBwd {
+  static constexpr int NW = LD == 128 ? 8 : 4;
+  static constexpr int NT = 64 * NW;
+  static constexpr int SL = LD + 4;
+  static constexpr int SR = LD == 128 ? 8 : 16;  // rows staged for the receiver sums at a time
+};
+template <int LD>
+struct __attribute__((aligned(16))) EdgeBwdLds {
+  typedef EdgeBwd<LD> K;
+  u32x4 w[2][X3<LD>::CH];
+  __attribute__((aligned(16))) float vec[3][LD];  // b1, b2, gamma
+  __attribute__((aligned(16))) float stage[K::NW][K::SR * K::SL];
+  DwLds<LD, K::NW> dw;
+};
+
+template <int LD>
+__global__ void __launch_bounds__(EdgeBwd<LD>::NT)
+    __attribute__((amdgpu_waves_per_eu(EdgeBwd<LD>::NW / 4, EdgeBwd<LD>::NW / 4)))
+k_edge_bwd_x3(EdgeTiles tl, const float* __restrict__ e_in, const float* ebar_in, int have_ebar, float* ebar_out,
+              const float* __restrict__ Pn, const float* __restrict__ aggbar, MlpW w, float eps, float* zbar,
+              float* __restrict__ R, float* __restrict__ slots, Partials part) {
+  typedef X3<LD> Z;
+  typedef EdgeBwd<LD> K;
+  constexpr int NW = K::NW, NT = K::NT;
+  __shared__ EdgeBwdLds<LD> S;
+  const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, hh = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int f0 = 8 * hh;  // the lane's first feature
+  const u32x4 *W1 = (const u32x4*)w.S1, *W2 = (const u32x4*)w.S2, *W2t = (const u32x4*)w.S2t, *W1t = (const u32x4*)w.S1t;
+  const BlockRange br = block_range<NW>(tl.n_tiles);
+  gemm_x3_start<LD, NT>(W1, S.w, tid);
+  for (int f = tid; f < LD; f += NT) {
+    S.vec[0][f] = w.b1[f];
+    S.vec[1][f] = w.b2[f];
+    S.vec[2][f] = w.gamma[f];
+  }
+  const int lastE = (int)(tl.n_edges - 1);
+  const int64_t tlast = max(br.tend - 1, (int64_t)0);
+  auto desc = [&](int64_t t) -> int4 {
+    const bool ok = t < br.tend;
+    const int4 v = tile_desc(tl.tiles, ok ? t : tlast);
+    return ok ? v : make_int4(0, 0, 0, 0);
+  };
+  auto erow = [&](int4 d) { return min(max(d.z + min(row, tile_rows(d) - 1), 0), lastE); };
+  DwAcc<LD, NW> dw2;
+  dw2.clear();
+  ColSumX3<LD> db2, dga, dbe;
+  float2 db1[2] = {{0.f, 0.f}, {0.f, 0.f}};
+  int4 d = desc(br.tb + wv);
+  int snd = tl.senders[erow(d)], rcv = tl.receivers[erow(d)];
+  __syncthreads();
+  for (int64_t t = br.tb; t < br.tend; t += br.stride) {
+    const int4 dn = desc(t + br.stride + wv);
+    const int n = tile_rows(d);
+    const TileRow<LD> tr(d, lastE, row, hh);
+    const bool chunk = d.y < 0, live = row < n;
+    // ---- z1 and a1 as in the forward; the mask z1 > 0
+    f32x16 acc[Z::NOB];
+    float x[Z::KL];
+    load_row_x3<LD>(x, tr.at(e_in));
+    float a1[Z::KL];
+    uint32_t mask[(Z::KL + 31) / 32] = {};
+    {
+      f32x4 p[Z::KL / 4], ps[2], pr[2];
+      auto add_p = [&](int ks) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          p[2 * ks + k] = (*reinterpret_cast<const f32x4*>(S.vec[0] + f0 + 16 * ks + 4 * k) + ps[k]) + pr[k];
+      };
+      gemm_x3<LD, 0, NT>(acc, x, W1, W2, S.w, tid, [&](int ks) {
+        if (ks > 0) add_p(ks - 1);
+        const float* q = Pn + f0 + 16 * ks;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          ps[k] = *reinterpret_cast<const f32x4*>(q + (size_t)snd * (2 * LD) + 4 * k);
+          pr[k] = *reinterpret_cast<const f32x4*>(q + (size_t)rcv * (2 * LD) + LD + 4 * k);
+        }
+      });
+      add_p(Z::KS - 1);
+#pragma unroll
+      for (int v = 0; v < Z::KL; ++v) {
+        const float z = acc[v >> 4][v & 15] + p[v >> 2][v & 3];
+        a1[v] = relu(z);
+        if (z > 0.f) mask[v >> 5] |= 1u << (v & 31);
+      }
+      // pinned: the compiler would keep every z1 instead, to compare it later
+#pragma unroll
+      for (int k = 0; k < (Z::KL + 31) / 32; ++k) asm volatile("" : "+v"(mask[k]));
+    }
+    // ---- z2 = b2 + W2 a1 and its LayerNorm
+    RowPieces<LD> A1;
+    float g[Z::KL];
+    gemm_keep<LD, Z::NC & 1, NT>(acc, a1, A1, W2, W2t, S.w, tid, [](int) {});
+#pragma unroll
+    for (int v = 0; v < Z::KL; ++v) acc[v >> 4][v & 15] += S.vec[1][Z::feat(hh, v)];
+    const float rstd = ln_x3<LD>(acc, hh, eps);
+    // ---- mbar = ebar_in + aggbar[receiver]; dbeta, dgamma; the LayerNorm
+    // reverse (padded features: gamma = 0 and xhat is left out, dz2 zero)
+#pragma unroll
+    for (int c = 0; c < Z::KL / 4; ++c) {
+      f32x4 u = *reinterpret_cast<const f32x4*>(aggbar + (size_t)rcv * LD + f0 + Z::pf(c));
+      const f32x4 e = *reinterpret_cast<const f32x4*>(tr.at(ebar_in) + Z::pf(c));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) g[4 * c + r] = (have_ebar ? e[r] : 0.f) + u[r];
+      if ((c & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // sixteen values' loads at a time
+    }
+#pragma unroll
+    for (int v = 0; v < Z::KL; ++v) g[v] = live ? g[v] : 0.f;
+    dbe.add([&](int v) { return g[v]; }, lane & 15);
+    dga.add([&](int v) { return g[v] * acc[v >> 4][v & 15]; }, lane & 15);
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int v = 0; v < Z::KL; ++v) {
+      g[v] *= S.vec[2][Z::feat(hh, v)];
+      s1 += g[v];
+      s2 += g[v] * acc[v >> 4][v & 15];
+    }
+    const float m1 = sum_hh(s1) * (1.0f / Z::DR), m2 = sum_hh(s2) * (1.0f / Z::DR);
+#pragma unroll
+    for (int v = 0; v < Z::KL; ++v)
+      g[v] = live && (Z::DR == LD || Z::feat(hh, v) < Z::DR) ? rstd * (g[v] - m1 - acc[v >> 4][v & 15] * m2) : 0.f;  // dz2
+    db2.add([&](int v) { return g[v]; }, lane & 15);
+    // ---- dW2 += dz2^T a1
+    RowPieces<LD> G;
+    split_row<LD>(G, g, live);
+    dw2.add(G, A1, live, S.dw, tid);
+    // the next tile's ids
+    const int snd_n = tl.senders[erow(dn)], rcv_n = tl.receivers[erow(dn)];
+    // ---- zbar = W2^T dz2 where z1 > 0
+    gemm_pieces<LD, 0, NT>(acc, [&](int ks) { return G.p[ks]; }, G.e, W2t, W1t, S.w, tid, [](int) {});
+#pragma unroll
+    for (int v = 0; v < Z::KL; ++v) g[v] = (mask[v >> 5] >> (v & 31)) & 1u ? acc[v >> 4][v & 15] : 0.f;
+    // ---- zbar's rows and their receiver sums
+    const uint32_t ends = segment_ends(row, n, rcv, chunk);
+    float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};
+    float* stage = S.stage[wv];
+#pragma unroll
+    for (int r0 = 0; r0 < 32; r0 += K::SR) {
+      if (row / K::SR == r0 / K::SR)
+#pragma unroll
+        for (int c = 0; c < Z::KL / 4; ++c)
+          *reinterpret_cast<f32x4*>(stage + (row - r0) * K::SL + f0 + Z::pf(c)) =
+              f32x4{g[4 * c], g[4 * c + 1], g[4 * c + 2], g[4 * c + 3]};
+      wave_lds_sync();
+      seg_sums<LD, K::SL, K::SR>(stage, lane, ends, r0, rcv, chunk, slots + (size_t)(-1 - d.y) * LD, R, carry, db1,
+                                 [&](const float2 (&v)[K::SR], int p, bool on) {
+#pragma unroll
+        for (int u = 0; u < K::SR; ++u)
+          if (r0 + u < n && on) *reinterpret_cast<float2*>(zbar + tr.base + (size_t)(r0 + u) * LD + 2 * p) = v[u];
+      });
+      wave_lds_sync();
+    }
+    if (!chunk && d.y > d.x) zero_empty<LD>(d, tl.rowptr, lane, R);
+    // ---- ebar_out = ebar_in + W1e^T zbar
+    gemm_x3<LD, Z::NC & 1, NT>(acc, g, W1t, W1, S.w, tid);
+    {
+      const float* q = tr.at(ebar_in);
+      float* o = tr.at(ebar_out);
+#pragma unroll
+      for (int c = 0; c < Z::KL / 4; ++c) {
+        f32x4 u = have_ebar ? *reinterpret_cast<const f32x4*>(q + Z::pf(c)) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) u[r] += acc[c >> 2][4 * (c & 3) + r];
+        if (live) *reinterpret_cast<f32x4*>(o + Z::pf(c)) = u;
+      }
+    }
+    d = dn;
+    snd = snd_n;
+    rcv = rcv_n;
+  }
+  // ---- block partials: dW2 from the owning waves, the vectors summed over
+  // the waves in wave order
+  float* base = part.buf + (size_t)blockIdx.x * part.stride + (size_t)LD * LD;
+  dw2.store(base + LD, tid);
+  __syncthreads();
+  float* red = &S.stage[0][0];  // [4][NW][LD]: db1, db2, dgamma, dbeta
+  *reinterpret_cast<float2*>(red + wv * LD + 2 * lane) = db1[0];
+  if (LD / 2 > 64 && lane + 64 < LD / 2) *reinterpret_cast<float2*>(red + wv * LD + 2 * (lane + 64)) = db1[1];
+  db2.put(red + (NW + wv) * LD, lane);
+  dga.put(red + (2 * NW + wv) * LD, lane);
+  dbe.put(red + (3 * NW + wv) * LD, lane);
+  __syncthreads();
+  for (int idx = tid; idx < 4 * LD; idx += NT) {
+    const int k = idx / LD, f = idx % LD;
+    float v = 0.f;
+#pragma unroll
+    for (int u = 0; u < NW; ++u) v += red[(k * NW + u) * LD + f];
+    base[k == 0 ? f : LD + LD * LD + (k - 1) * LD + f] = v;
+  }
+}
+
+// ======================================================= weight gradient
+// dW[o][n] = sum over rows of G[row][o] X[row][n] for two row-major fp32
+// [M][LD] streams (DwAcc), 128 rows per round, the next round's rows in flight
+// while one is added.  Bound by reading the two streams.
+template <int LD>
+__global__ void __launch_bounds__(X3_NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_wgrad_x3(int64_t M, const float* __restrict__ Gm, const float* __restrict__ Xm, Partials part) {
+  typedef X3<LD> Z;
+  __shared__ DwLds<LD, X3_NW> S;
+  const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, f0 = 8 * (lane >> 5);
+  const int wv = tid >> 6;
+  DwAcc<LD, X3_NW> dw;
+  dw.clear();
+  const int64_t nr = (M + 32 * X3_NW - 1) / (32 * X3_NW);
+  float g[Z::KL], x[Z::KL];
+  auto at = [&](int64_t r) { return r * (32 * X3_NW) + 32 * wv + row; };
+  auto load = [&](int64_t r) {
+    const int64_t u = min(at(r), M - 1);
+    load_row_x3<LD>(g, Gm + (size_t)u * LD + f0);
+    load_row_x3<LD>(x, Xm + (size_t)u * LD + f0);
+  };
+  int64_t r = blockIdx.x;
+  if (r < nr) load(r);
+  for (; r < nr; r += gridDim.x) {
+    const bool live = at(r) < M;
+    RowPieces<LD> G, X;
+    split_row<LD>(G, g, live);
+    split_row<LD>(X, x, live);
+    if (r + gridDim.x < nr) load(r + gridDim.x);
+    dw.add(G, X, live, S, tid);
+  }
+  dw.store(part.buf + (size_t)blockIdx.x * part.stride, tid);
 }
 
 }  // namespace dev
@@ -166,6 +414,42 @@ hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& t, const void* e_in, voi
 #define F(LD)                                                                                                     \
   hipLaunchKernelGGL(k_edge_fwd_x3<LD>, dim3(g), dim3(X3_NT), 0, s, t, (const float*)e_in, (float*)e_out, write_e, \
                      (const float*)Pn, w, eps, agg, slots)
+  MGN_BY_WIDTH(lat, F);
+#undef F
+  return hipGetLastError();
+}
+
+// one block per CU
+static constexpr int kSplitPartBlocks = 256;
+
+hipError_t launch_edge_bwd_x3(int lat, const EdgeTiles& t, const void* e, const float* ebar_in, int have_ebar,
+                              float* ebar_out, const void* Pn, const float* aggbar, const MlpW& w, float eps,
+                              void* zbar, float* R, float* slots, const Partials& part, int* nblocks, hipStream_t s) {
+  *nblocks = 0;
+  if (t.n_tiles <= 0) return hipSuccess;
+  if (t.n_edges <= 0 || part.stride < 2LL * lat * lat + 4 * lat || !w.S1 || !w.S2 || !w.S1t || !w.S2t)
+    return hipErrorInvalidValue;
+  const int nw = lat == 128 ? EdgeBwd<128>::NW : EdgeBwd<160>::NW;
+  int g = (int)std::min<int64_t>((t.n_tiles + nw - 1) / nw, std::min(kSplitPartBlocks, part.max_blocks));
+  if (g >= 8) g &= ~7;
+  *nblocks = g;
+#define F(LD)                                                                                                  \
+  hipLaunchKernelGGL(k_edge_bwd_x3<LD>, dim3(g), dim3(EdgeBwd<LD>::NT), 0, s, t, (const float*)e, ebar_in, have_ebar,    \
+                     ebar_out, (const float*)Pn, aggbar, w, eps, (float*)zbar, R, slots, part)
+  MGN_BY_WIDTH(lat, F);
+#undef F
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad_x3(int lat, int64_t M, const float* G, const float* X, const Partials& part, int* nblocks,
+                           hipStream_t s) {
+  *nblocks = 0;
+  if (M <= 0) return hipSuccess;
+  if (part.stride < (int64_t)lat * lat) return hipErrorInvalidValue;
+  const int64_t need = (M + 32 * X3_NW - 1) / (32 * X3_NW);
+  const int g = (int)std::min<int64_t>(need, std::min(kSplitPartBlocks, part.max_blocks));
+  *nblocks = g;
+#define F(LD) hipLaunchKernelGGL(k_wgrad_x3<LD>, dim3(g), dim3(X3_NT), 0, s, M, G, X, part)
   MGN_BY_WIDTH(lat, F);
 #undef F
   return hipGetLastError();

@@ -48,11 +48,11 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ params, 
 }
 
 // Two-piece fp16 fragments for the fp32 split products (square n x n matrix M
-// = W, or W^T when perm == 5; n a multiple of 32): M[o][k] with o = KL oh + 16
-// ob + r and k = KL kh + 8 ks + t (KL = n / 2) is element t of lane m + 32 kh,
-// m = r % 4 + 8 (r / 4) + 4 oh, of the fragments (ks, ob, piece), scaled by the
-// power of two that brings the largest |M| into [2^14, 2^15); its exponent
-// follows the fragments.  Every block forms the maximum itself (a matrix is at
+// = W, or W^T when perm == 5; n a multiple of 32): M[o][k] with o = feature of
+// value 16 ob + r of lane half oh and k = that of value 8 ks + t of half kh
+// (X3::feat) is element t of lane m + 32 kh, m = r % 4 + 8 (r / 4) + 4 oh, of the
+// fragments (ks, ob, piece), scaled by the power of two that brings the
+// largest |M| into [2^14, 2^15); its exponent follows the fragments.  Every block forms the maximum itself (a matrix is at
 // most 100 KB, read once from L2) and then writes its share: a separate
 // launch for the maxima would cost a small call more than the packing.
 __global__ void __launch_bounds__(1024) k_pack_split(const float* __restrict__ params, float* __restrict__ pack,
@@ -72,11 +72,11 @@ __global__ void __launch_bounds__(1024) k_pack_split(const float* __restrict__ p
   for (int k = 0; k < 16; ++k) mx = fmaxf(mx, wm[k]);
   const int e = scale_exp(mx);
   const float s = scale_of(e);
-  const int KL = pe.rows / 2, NOB = pe.rows / 32;
+  const int NOB = pe.rows / 32;
   _Float16* dst = reinterpret_cast<_Float16*>(pack + pe.dst);
   for (int idx = blockIdx.x * 1024 + tid; idx < n; idx += gridDim.x * 1024) {
     const int t = idx & 7, l = (idx >> 3) & 63, rest = idx >> 9, ob = rest % NOB, ks = rest / NOB, m = l & 31;
-    const int64_t o = KL * ((m >> 2) & 1) + 16 * ob + (m & 3) + 4 * (m >> 3), k = KL * (l >> 5) + 8 * ks + t;
+    const int64_t o = X3<128>::feat((m >> 2) & 1, 16 * ob + (m & 3) + 4 * (m >> 3)), k = X3<128>::feat(l >> 5, 8 * ks + t);
     const float v = s * params[pe.perm == 4 ? pe.src + o * pe.ld + k : pe.src + k * pe.ld + o];
     const _Float16 h = (_Float16)v;
     _Float16* q = dst + (int64_t)rest * 2 * 512 + l * 8 + t;

@@ -31,7 +31,9 @@ struct MlpW {
   const float* F1st;
   const float* F1rt;
   const void* S1;    // fp32 split products (pack modes 4, 5): two-piece fp16
-  const void* S2;    // fragments of the edge MLP's W1e and W2
+  const void* S2;    // fragments of the edge MLP's W1e and W2, and of their
+  const void* S1t;   // transposes
+  const void* S2t;
   const float* W1f;  // float32 first-layer weights (encoders: K = 4 / 8 on VALU)
   const float* W2f;  // float32 second-layer weights (decoder: 4 outputs on VALU)
   const float* b1;
@@ -118,7 +120,7 @@ hipError_t launch_node_fwd_r32(int lat, int64_t N, const float* h_in, const floa
                                const MlpW* nx, float eps, float* h_out, float* P_out, hipStream_t s);
 // Its reverse: hbar_part = hbar_in + W1h^T dz1, aggbar = W1a^T dz1, the
 // rows of a1, dz2, dz1 into streams ([3][N][lat] fp32, for the weight
-// gradients by launch_wgrad_r32), and per-block [4][lat] partials of db1,
+// gradients by launch_wgrad_x3), and per-block [4][lat] partials of db1,
 // db2, dgamma, dbeta (needs F1t, F1at, F2t too).
 hipError_t launch_node_bwd_r32(int lat, int64_t N, const float* h, const float* agg, const float* hbar_in,
                                const MlpW& w, float eps, float* hbar_part, float* aggbar, float* streams,
@@ -131,7 +133,7 @@ hipError_t launch_node_srcsum_r32(int lat, int64_t N, const int32_t* rowptr, con
                                   float* S_out, hipStream_t s);
 // fp32 decoder in the row layout (needs the decoder's fragment-major F1 and,
 // for the reverse, F1t): out = W2 relu(W1 h + b1) + b2 ([N][4]); the
-// reverse writes hbar = W1^T dz1, the dz1 rows (for dW1 by launch_wgrad_r32)
+// reverse writes hbar = W1^T dz1, the dz1 rows (for dW1 by launch_wgrad_x3)
 // and per-block partials [lat] db1, [4][lat] dW2, [4] db2.
 hipError_t launch_decoder_r32(int lat, int64_t N, const float* h, const MlpW& w, float* out, hipStream_t s);
 hipError_t launch_decoder_bwd_r32(int lat, int64_t N, const float* h, const float* gout, const MlpW& w, float* hbar,
@@ -141,7 +143,7 @@ hipError_t launch_decoder_bwd_r32(int lat, int64_t N, const float* h, const floa
 // LN(W2 relu(W1 x + b1) + b2) from the 8 node inputs, with nx also the node
 // products of the first MP block.  The reverse writes gin = dL/dx (when
 // given), the a1 and dz2 rows into streams ([2][N][lat], for dW2 by
-// launch_wgrad_r32) and per-block partials [lat][8] dW1, [lat] db1, db2,
+// launch_wgrad_x3) and per-block partials [lat][8] dW1, [lat] db1, db2,
 // dgamma, dbeta.
 hipError_t launch_node_enc_r32(int lat, int64_t N, const float* x, const MlpW& w, const MlpW* nx, float eps,
                                float* h_out, float* P_out, hipStream_t s);
@@ -161,15 +163,14 @@ hipError_t launch_edge_fwd_rows(const EdgeTiles& t, const void* e_in, void* e_ou
 // m.
 hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& t, const void* e_in, void* e_out, int write_e, const void* Pn,
                               const MlpW& w, float eps, float* agg, float* slots, hipStream_t s);
-// fp32 edge backward at width 128 with its weight gradients in one pass (one
-// wave per row block, four waves per block in lockstep rounds; recomputes
-// the first layer from e and P; uses MlpW::F1, F2, F1t, F2t): writes zbar,
-// R / slots, ebar_out (in place allowed) and per-block partials dW1e (0),
-// db1 (16384), dW2 (16512), db2 (32896), dgamma (33024), dbeta (33152).
-hipError_t launch_edge_bwd_r32(int lat, const EdgeTiles& t, const void* e, const float* ebar_in, int have_ebar,
-                               float* ebar_out, const void* Pn, const float* aggbar, const MlpW& w, float eps,
-                               void* zbar, float* R, float* slots, const Partials& part, int* nblocks,
-                               hipStream_t s);
+// fp32 edge backward at width lat (128 or 160) with one wave per tile (uses
+// MlpW::S1, S2, S1t, S2t; recomputes the first layer from e and P): writes
+// zbar, R / slots, ebar_out (in place allowed) and per-block partials db1 (at
+// lat^2), dW2, db2, dgamma, dbeta; dW1e = sum zbar^T e is left to
+// launch_wgrad_x3.
+hipError_t launch_edge_bwd_x3(int lat, const EdgeTiles& t, const void* e, const float* ebar_in, int have_ebar,
+                              float* ebar_out, const void* Pn, const float* aggbar, const MlpW& w, float eps,
+                              void* zbar, float* R, float* slots, const Partials& part, int* nblocks, hipStream_t s);
 // bf16 edge backward with its weight gradients in one pass (four waves per
 // block in lockstep rounds): from the saved a1, the block's input edge
 // latents e and ebar_in (in place allowed), writes zbar, R / slots,
@@ -249,10 +250,10 @@ hipError_t launch_decoder(int prec, int lat, int64_t N, const float* h, const Ml
 hipError_t launch_decoder_bwd(int prec, int lat, int64_t N, const float* h, const float* gout, const MlpW& w,
                               float* hbar, const Partials& part, int* nblocks, hipStream_t s);
 // dW[o][i] = sum_rows G[row][o] X[row][i] for fp32 [M][lat] streams (lat
-// 128 or 160), in the fp32 row layout, written as per-block [lat][lat]
+// 128 or 160), written as per-block [lat][lat]
 // partials.
-hipError_t launch_wgrad_r32(int lat, int64_t M, const float* G, const float* X, const Partials& part, int* nblocks,
-                            hipStream_t s);
+hipError_t launch_wgrad_x3(int lat, int64_t M, const float* G, const float* X, const Partials& part, int* nblocks,
+                           hipStream_t s);
 hipError_t launch_node_srcsum(int prec, int lat, int64_t N, const int32_t* rowptr, const int32_t* rev, const void* zbar,
                               const float* R, const float* h, const float* hbar_part, const MlpW& w,
                               float* hbar_out, const Partials& part, int* nblocks, hipStream_t s);

@@ -23,11 +23,15 @@
 // needs six products, measured 0.23 ms for an edge forward of 393k edges.
 //
 // Lane layout.  Lane l (row = l & 31, hh = l >> 5) holds one row of a 32-row
-// block and the KL = LD / 2 features [KL hh, KL hh + KL) of it.  The products
-// run transposed, C[feature][row] = W x^T: at K step s lane half hh supplies
-// its values 8s .. 8s + 7 as the B operand, and the weights' output rows are
-// ordered so that the C fragment of output block ob hands the lane its own
-// features f0 + 16 ob + r (r < 16): a product's output is the next one's B
+// block and KL = LD / 2 values of it, value v being feature 16 (v / 8) + 8 hh +
+// v % 8: the two lanes of a row read or write 64 contiguous bytes in two
+// instructions.  (Every 16-byte access of a wave still spans 32 cache lines,
+// and the L1 takes one a cycle: with a contiguous half row per lane it was 64,
+// and the address traffic of an edge forward took as long as its arithmetic.)
+// The products run transposed, C[feature][row] = W x^T: at K step s lane half
+// hh supplies its values 8s .. 8s + 7 as the B operand, and the weights' output
+// rows are ordered so that the C fragment of output block ob hands the lane
+// its own values 16 ob + r (r < 16): a product's output is the next one's B
 // operand without leaving registers, and a row's scale is one value per lane.
 //
 // The weights (pack modes 4 and 5: fragment-major, K step by K step, both
@@ -39,6 +43,7 @@
 // (read from L2 per wave they would need all of the L1 bandwidth).
 #pragma once
 #include "rows_common.hpp"
+#include "w160_common.hpp"
 
 namespace mgn {
 namespace dev {
@@ -46,7 +51,7 @@ namespace dev {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int X3_NW = 4;  // waves per block
+constexpr int X3_NW = 4;  // waves per block (unless a kernel says otherwise)
 constexpr int X3_NT = 64 * X3_NW;
 
 template <int LD>
@@ -57,8 +62,10 @@ struct X3 {
   static constexpr int NC = KS / 2;         // chunks of two K steps
   static constexpr int DR = Width<LD>::DR;  // real latent width
   static constexpr int CH = 2 * NOB * 2 * 64;  // 16-byte pieces of one chunk's weights
-  static constexpr int NL = CH / X3_NT;
-  static_assert(CH % X3_NT == 0, "every thread moves the same number of pieces");
+  // feature of value v of lane half hh; pf(c): the part that four values c of
+  // any half share (feature of value 4c minus 8 hh)
+  static constexpr __host__ __device__ int feat(int hh, int v) { return 16 * (v >> 3) + 8 * hh + (v & 7); }
+  static constexpr __host__ __device__ int pf(int c) { return 16 * (c >> 1) + 4 * (c & 1); }
 };
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -100,18 +107,21 @@ __device__ __forceinline__ float max_hh(float s) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// One chunk's weight fragments on their way from L2 to LDS.
-template <int LD>
+// One chunk's weight fragments on their way from L2 to LDS: each of the NT
+// threads moves the same number of pieces.
+template <int LD, int NT>
 struct WStream {
-  u32x4 r[X3<LD>::NL];
+  static constexpr int NL = X3<LD>::CH / NT;
+  static_assert(X3<LD>::CH % NT == 0, "");
+  u32x4 r[NL];
   __device__ __forceinline__ void load(const u32x4* p, int tid) {
 #pragma unroll
-    for (int j = 0; j < X3<LD>::NL; ++j)
-      r[j] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p) + 16u * (uint32_t)(tid + X3_NT * j));
+    for (int j = 0; j < NL; ++j)
+      r[j] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p) + 16u * (uint32_t)(tid + NT * j));
   }
   __device__ __forceinline__ void store(u32x4* dst, int tid) const {
 #pragma unroll
-    for (int j = 0; j < X3<LD>::NL; ++j) dst[tid + X3_NT * j] = r[j];
+    for (int j = 0; j < NL; ++j) dst[tid + NT * j] = r[j];
   }
 };
 
@@ -122,39 +132,53 @@ __device__ __forceinline__ int weight_exp(const u32x4* W) {
   return *(ConstInt*)(W + X3<LD>::NC * X3<LD>::CH);
 }
 
-// acc = W x for the lane's KL values x.  W is the product's packed matrix,
-// whose first chunk is in buf[PAR]; next (the following product's, or any
-// valid matrix) leaves its first chunk in buf[(PAR + NC) % 2].  All waves of
-// the block call it together.  mid(c) runs after the products of chunk c (for
-// loads that the caller needs after the product).
-template <int LD, int PAR, class F>
-__device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float* x, const u32x4* W, const u32x4* next,
-                                        u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
+// Exponent of the lane's row's scale (scale_exp of its largest value).  The
+// result is pinned where it is formed: left to itself, the compiler spread the
+// maximum over the following product's barriers and with it delayed every
+// MFMA.
+template <int LD>
+__device__ __forceinline__ int row_exp(const float* x) {
+  float m = 0.f;
+#pragma unroll
+  for (int t = 0; t < X3<LD>::KL; ++t) m = fmaxf(m, fabsf(x[t]));
+  int e = scale_exp(max_hh(m));
+  asm volatile("" : "+v"(e));
+  return e;
+}
+
+// A row's pieces and its scale's exponent.
+template <int LD>
+struct RowPieces {
+  Pieces p[X3<LD>::KS];
+  int e;
+};
+
+// acc = W x.  get(ks) gives the pieces of the lane's values 8 ks .. 8 ks + 7,
+// scaled by 2^e.  W is the product's packed matrix, whose first chunk is in
+// buf[PAR]; next (the following product's, or any valid matrix) leaves its
+// first chunk in buf[(PAR + NC) % 2].  All NT threads of the block call it
+// together.  mid(ks) runs after the products of K step ks (for loads that
+// the caller needs after the product).
+template <int LD, int PAR, int NT, class G, class F>
+__device__ __forceinline__ void gemm_pieces(f32x16 (&acc)[X3<LD>::NOB], G&& get, int e, const u32x4* W,
+                                            const u32x4* next, u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
   typedef X3<LD> Z;
   const int lane = tid & 63;
   const int ot = tid + opaque_zero();  // keeps the loads' addresses out of the callers' loops
-  float m = 0.f;
-#pragma unroll
-  for (int t = 0; t < Z::KL; ++t) m = fmaxf(m, fabsf(x[t]));
-  const int e = scale_exp(max_hh(m));
-  float s = scale_of(e);
-  // the scale is formed here; left to itself, the compiler spread the maximum
-  // over the chunks' barriers and with it delayed every product
-  asm volatile("" : "+v"(s));
 #pragma unroll
   for (int ob = 0; ob < Z::NOB; ++ob)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[ob][r] = 0.f;
 #pragma unroll
   for (int c = 0; c < Z::NC; ++c) {
-    WStream<LD> ws;
+    WStream<LD, NT> ws;
     ws.load(c + 1 < Z::NC ? W + (c + 1) * Z::CH : next, ot);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       // the loads stay above, a whole chunk ahead of their use, and the steps
       // apart (fragments of both at once do not fit in the registers)
       __builtin_amdgcn_sched_barrier(0);
-      const Pieces b = split8(x + 16 * c + 8 * k, s);
+      const Pieces b = get(2 * c + k);
       const f16x8* A = reinterpret_cast<const f16x8*>(buf[(PAR + c) & 1]) + k * Z::NOB * 128 + lane;
       f16x8 a[Z::NOB];
 #pragma unroll
@@ -167,8 +191,8 @@ __device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float*
       for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ob], b.l, acc[ob], 0, 0, 0);
 #pragma unroll
       for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ob], b.h, acc[ob], 0, 0, 0);
+      mid(2 * c + k);
     }
-    mid(c);
     ws.store(buf[(PAR + c + 1) & 1], tid);
     __syncthreads();
   }
@@ -178,26 +202,60 @@ __device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float*
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[ob][r] = __builtin_amdgcn_ldexpf(acc[ob][r], k);
 }
-template <int LD, int PAR>
+
+// acc = W x for the lane's KL values x, which are split as the product goes.
+template <int LD, int PAR, int NT = X3_NT, class F>
+__device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float* x, const u32x4* W, const u32x4* next,
+                                        u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
+  const int e = row_exp<LD>(x);
+  const float s = scale_of(e);
+  gemm_pieces<LD, PAR, NT>(acc, [&](int ks) { return split8(x + 8 * ks, s); }, e, W, next, buf, tid, mid);
+}
+template <int LD, int PAR, int NT = X3_NT>
 __device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float* x, const u32x4* W, const u32x4* next,
                                         u32x4 (*buf)[X3<LD>::CH], int tid) {
-  gemm_x3<LD, PAR>(acc, x, W, next, buf, tid, [](int) {});
+  gemm_x3<LD, PAR, NT>(acc, x, W, next, buf, tid, [](int) {});
+}
+// The same, keeping the pieces in row.
+template <int LD, int PAR, int NT, class F>
+__device__ __forceinline__ void gemm_keep(f32x16 (&acc)[X3<LD>::NOB], const float* x, RowPieces<LD>& row, const u32x4* W,
+                                          const u32x4* next, u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
+  row.e = row_exp<LD>(x);
+  const float s = scale_of(row.e);
+  gemm_pieces<LD, PAR, NT>(acc, [&](int ks) { return row.p[ks] = split8(x + 8 * ks, s); }, row.e, W, next, buf, tid, mid);
 }
 
 // The first chunk of the first product into buf[0] (a barrier must follow).
-template <int LD>
+template <int LD, int NT = X3_NT>
 __device__ __forceinline__ void gemm_x3_start(const u32x4* W, u32x4 (*buf)[X3<LD>::CH], int tid) {
-  WStream<LD> ws;
+  WStream<LD, NT> ws;
   ws.load(W, tid);
   ws.store(buf[0], tid);
 }
 
-// The lane's KL contiguous floats of a row starting at p.
+// Rows of a tile in an [E][LD] stream: the tile's first row as a scalar base
+// and the lane's own slice as a 32-bit offset from it.  Rows past the tile's
+// end are clamped to its last one (an empty tile reads a valid row).
+template <int LD>
+struct TileRow {
+  int64_t base;
+  uint32_t off;
+  __device__ __forceinline__ TileRow(int4 d, int64_t last, int row, int hh) {
+    base = min((int64_t)d.z, last) * LD;
+    off = (uint32_t)(max(min(row, tile_rows(d) - 1), 0) * LD + 8 * hh);
+  }
+  template <class T>
+  __device__ __forceinline__ T* at(T* p) const {
+    return p + base + off;
+  }
+};
+
+// The lane's KL values of a row; p points at feature 8 hh of it.
 template <int LD>
 __device__ __forceinline__ void load_row_x3(float* x, const float* __restrict__ p) {
 #pragma unroll
   for (int c = 0; c < X3<LD>::KL / 4; ++c) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(p + 4 * c);
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + X3<LD>::pf(c));
 #pragma unroll
     for (int t = 0; t < 4; ++t) x[4 * c + t] = v[t];
   }
@@ -206,7 +264,7 @@ __device__ __forceinline__ void load_row_x3(float* x, const float* __restrict__ 
 // z -> (z - mean) rstd over the row's DR real features (the padded ones are
 // 0 on entry and are left out of the biased variance); returns rstd.
 template <int LD>
-__device__ __forceinline__ float ln_x3(f32x16 (&z)[X3<LD>::NOB], int f0, float eps) {
+__device__ __forceinline__ float ln_x3(f32x16 (&z)[X3<LD>::NOB], int hh, float eps) {
   typedef X3<LD> Z;
   float sm = 0.f;
 #pragma unroll
@@ -221,7 +279,7 @@ __device__ __forceinline__ float ln_x3(f32x16 (&z)[X3<LD>::NOB], int f0, float e
     for (int r = 0; r < 16; ++r) {
       const float d = z[ob][r] - mean;
       z[ob][r] = d;
-      if (Z::DR == LD || f0 + 16 * ob + r < Z::DR) sq += d * d;
+      if (Z::DR == LD || Z::feat(hh, 16 * ob + r) < Z::DR) sq += d * d;
     }
   const float rstd = __builtin_amdgcn_rsqf(sum_hh(sq) * (1.0f / Z::DR) + eps);
 #pragma unroll
@@ -237,17 +295,18 @@ __device__ __forceinline__ float ln_x3(f32x16 (&z)[X3<LD>::NOB], int f0, float e
 struct BlockRange {
   int64_t tb, stride, tend;
 };
+template <int NW = X3_NW>
 __device__ __forceinline__ BlockRange block_range(int64_t n_units) {
   const int G = gridDim.x;
   BlockRange u;
   if ((G & 7) == 0) {
     const int64_t chunk = (n_units + 7) >> 3, lo = (blockIdx.x & 7) * chunk;
     u.tend = min(n_units, lo + chunk);
-    u.tb = lo + (int64_t)(blockIdx.x >> 3) * X3_NW;
-    u.stride = (int64_t)(G >> 3) * X3_NW;
+    u.tb = lo + (int64_t)(blockIdx.x >> 3) * NW;
+    u.stride = (int64_t)(G >> 3) * NW;
   } else {
-    u.tb = (int64_t)blockIdx.x * X3_NW;
-    u.stride = (int64_t)G * X3_NW;
+    u.tb = (int64_t)blockIdx.x * NW;
+    u.stride = (int64_t)G * NW;
     u.tend = n_units;
   }
   return u;
@@ -258,10 +317,11 @@ __device__ __forceinline__ BlockRange block_range(int64_t n_units) {
 // pairs lane and lane + 64 (below LD / 2) of the rows in ascending order from
 // 0.0 and stores a segment's sum at its last row (bit u of ends: row u ends
 // a segment), to node rcv's row of dst, or, for a chunk of a long segment, to
-// its slot.  All of the staged rows are read at once, before the sums.
-template <int LD, int SL, int SR>
+// its slot, and adds it to tot.  All of the staged rows are read at once, before
+// the sums; rows(v, p, on) sees them first (v[u]: the pair p of row r0 + u).
+template <int LD, int SL, int SR, class F>
 __device__ __forceinline__ void seg_sums(const float* stage, int lane, uint32_t ends, int r0, int rcv, bool chunk,
-                                         float* slot, float* dst, float2 (&carry)[2]) {
+                                         float* slot, float* dst, float2 (&carry)[2], float2 (&tot)[2], F&& rows) {
   constexpr int NP = LD / 2;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -271,6 +331,7 @@ __device__ __forceinline__ void seg_sums(const float* stage, int lane, uint32_t 
     float2 v[SR];
 #pragma unroll
     for (int u = 0; u < SR; ++u) v[u] = *reinterpret_cast<const float2*>(stage + u * SL + 2 * (on ? p : lane));
+    rows(v, p, on);
 #pragma unroll
     for (int u = 0; u < SR; ++u) {
       carry[k].x += v[u].x;
@@ -278,6 +339,8 @@ __device__ __forceinline__ void seg_sums(const float* stage, int lane, uint32_t 
       if ((ends >> (r0 + u)) & 1u) {
         float* q = chunk ? slot : dst + (size_t)__builtin_amdgcn_readlane(rcv, r0 + u) * LD;
         if (on) *reinterpret_cast<float2*>(q + 2 * p) = carry[k];
+        tot[k].x += carry[k].x;
+        tot[k].y += carry[k].y;
         carry[k] = float2{0.f, 0.f};
       }
     }
@@ -295,6 +358,185 @@ __device__ __forceinline__ void zero_empty(int4 d, const int32_t* __restrict__ r
     float* q = dst + (size_t)(d.x + j) * LD;
     for (int f = lane; f < LD; f += 64) q[f] = 0.f;
   }
+}
+
+// Column sums over the 32 rows of a block of the lanes' KL values, added up
+// block after block: a permlane16 swap and then DPP butterflies halve the
+// values held at every step, which leaves lane i + 16 k of half hh with the
+// features KL hh + (KL / 2) k + 2i + {0, 1} (v) and, at width 160, one more for
+// even i (t).  put() writes a wave's sums into its row of an LDS array [LD].
+template <int LD>
+struct ColSumX3 {
+  static constexpr int H = X3<LD>::KL / 2;
+  float2 v = {0.f, 0.f};
+  float t = 0.f;
+  // get(k): the lane's value k.  The first two halvings run value by value, so
+  // that few are held at a time.
+  template <class F>
+  __device__ __forceinline__ void add(F&& get, int i) {
+    auto pair = [&](int k) {
+      const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(get(k)), __float_as_uint(get(k + H)), false, false);
+      return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+    };
+    float c[16];
+    const bool hi = (i >> 3) & 1;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const float a = pair(k), b = pair(k + 16);
+      c[k] = (hi ? b : a) + dpp_mov<0x140>(hi ? a : b);
+    }
+    bfly_step<8, 0x141>(c, (i >> 2) & 1);
+    bfly_step<4, 0x1B>(c, (i >> 1) & 1);
+    bfly_step<2, 0xB1>(c, i & 1);
+    v.x += c[0];
+    v.y += c[1];
+    if constexpr (H == 40) {
+      f32x4 q[10];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) q[8 + (k >> 2)][k & 3] = pair(32 + k);
+      t += w160::colsum16_tail(q, i);
+    }
+  }
+  __device__ __forceinline__ void put(float* red, int lane) const {
+    const int i = lane & 15, hh = lane >> 5, k = H * ((lane >> 4) & 1);
+    *reinterpret_cast<float2*>(red + X3<LD>::feat(hh, k + 2 * i)) = v;
+    if constexpr (H == 40)
+      if ((i & 1) == 0)
+        red[X3<LD>::feat(hh, k + 32 + ((((i >> 3) & 1) << 2) | (((i >> 2) & 1) << 1) | ((i >> 1) & 1)))] = t;
+  }
+};
+
+// Weight gradients dW[o][n] += sum over rows of G[row][o] X[row][n], with the
+// rows as K, from the rows' pieces.  A row of G carries its own power of two
+// 2^eg and the row of X its 2^ex; X's pieces are scaled further, by 2^(c - eg -
+// ex) <= 1, so that every product carries 2^c: c is the smallest eg + ex of the
+// rows so far.  Rows whose products are far below the largest lose bits only
+// below 2^-39 of it.  When a block of rows lowers c, the accumulators follow.
+//   Each of the NW waves holds 32 rows (lane layout as above) and owns TU x TV
+// of the 16 x 16 tiles of dW.  The rows are staged row-major, SR rows at a time
+// (SR / NW of every wave), and read back transposed.  Rows that are not live
+// must have zero pieces in G.
+template <int LD, int NW>
+struct DwShape {
+  static constexpr int SL = LD + 16;                 // staged row stride (fp16)
+  static constexpr int SR = NW == 8 ? 64 : 32;       // rows staged at a time
+  static constexpr int TU = NW == 8 ? LD / 64 : LD / 32, TV = LD / 32;
+  static_assert(TU * TV * NW * 256 == LD * LD, "");
+};
+template <int LD, int NW>
+struct __attribute__((aligned(16))) DwLds {
+  _Float16 g[2][DwShape<LD, NW>::SR * DwShape<LD, NW>::SL];
+  _Float16 x[2][DwShape<LD, NW>::SR * DwShape<LD, NW>::SL];
+  int c[NW];
+};
+
+// Eight fp16 values times 2^k, k <= 0 (below 2^-24 they vanish).
+__device__ __forceinline__ f16x8 scale_f16(f16x8 v, _Float16 s) {
+  return v * f16x8{s, s, s, s, s, s, s, s};
+}
+
+template <int LD, int NW>
+struct DwAcc {
+  typedef DwShape<LD, NW> Sh;
+  static constexpr int TU = Sh::TU, TV = Sh::TV;
+  f32x4 a[TU * TV];
+  int c = 1 << 20;  // no rows yet
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int t = 0; t < TU * TV; ++t) a[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  static __device__ __forceinline__ f16x8 frag(const _Float16* S, int r0, int col0, int i, int q) {
+    const bf16* p = reinterpret_cast<const bf16*>(S) + (r0 + q * 8 + (i >> 2)) * Sh::SL + col0 + 4 * (i & 3);
+    return __builtin_bit_cast(f16x8, cat8(lds_tr(p), lds_tr(p + 4 * Sh::SL)));
+  }
+  __device__ __forceinline__ void add(const RowPieces<LD>& G, RowPieces<LD>& X, bool live, DwLds<LD, NW>& S, int tid) {
+    typedef X3<LD> Z;
+    constexpr int RW = Sh::SR / NW;  // rows of a wave staged at a time
+    const int lane = tid & 63, row = lane & 31, hh = lane >> 5, wv = tid >> 6, i = lane & 15, q = lane >> 4;
+    // the smallest eg + ex of the block's rows
+    int m = live ? G.e + X.e : 1 << 20;
+    m = min(m, __builtin_amdgcn_mov_dpp(m, 0x140, 0xf, 0xf, false));
+    m = min(m, __builtin_amdgcn_mov_dpp(m, 0x141, 0xf, 0xf, false));
+    m = min(m, __builtin_amdgcn_mov_dpp(m, 0x1B, 0xf, 0xf, false));
+    m = min(m, __builtin_amdgcn_mov_dpp(m, 0xB1, 0xf, 0xf, false));
+    const auto w = __builtin_amdgcn_permlane16_swap((uint32_t)m, (uint32_t)m, false, false);
+    m = min((int)w[0], (int)w[1]);
+    if (lane == 0) S.c[wv] = m;
+    __syncthreads();  // also: the products of the previous call are done
+    int cn = S.c[0];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) cn = min(cn, S.c[k]);
+    cn = __builtin_amdgcn_readfirstlane(cn);
+    if (cn < c) {
+#pragma unroll
+      for (int t = 0; t < TU * TV; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[t][r] = __builtin_amdgcn_ldexpf(a[t][r], cn - c);
+      c = cn;
+    }
+    const _Float16 sx = (_Float16)__builtin_amdgcn_ldexpf(1.f, live ? max(c - G.e - X.e, -100) : -100);
+#pragma unroll
+    for (int k = 0; k < Z::KS; ++k) {
+      X.p[k].h = scale_f16(X.p[k].h, sx);
+      X.p[k].l = scale_f16(X.p[k].l, sx);
+    }
+    const int at = (RW * wv + row % RW) * Sh::SL + 8 * hh;
+    const int u0 = 16 * TU * (wv / (LD / 16 / TV)), v0 = 16 * TV * (wv % (LD / 16 / TV));
+#pragma unroll 1
+    for (int r = 0; r < 32 / RW; ++r) {
+      if (r > 0) __syncthreads();  // the previous rows' products are done
+      if (row / RW == r)
+#pragma unroll
+        for (int k = 0; k < Z::KS; ++k) {
+          *reinterpret_cast<f16x8*>(S.g[0] + at + 16 * k) = G.p[k].h;
+          *reinterpret_cast<f16x8*>(S.g[1] + at + 16 * k) = G.p[k].l;
+          *reinterpret_cast<f16x8*>(S.x[0] + at + 16 * k) = X.p[k].h;
+          *reinterpret_cast<f16x8*>(S.x[1] + at + 16 * k) = X.p[k].l;
+        }
+      __syncthreads();
+#pragma unroll
+      for (int r0 = 0; r0 < Sh::SR; r0 += 32) {
+        f16x8 ah[TU], al[TU];
+#pragma unroll
+        for (int u = 0; u < TU; ++u) {
+          ah[u] = frag(S.g[0], r0, u0 + 16 * u, i, q);
+          al[u] = frag(S.g[1], r0, u0 + 16 * u, i, q);
+        }
+#pragma unroll
+        for (int v = 0; v < TV; ++v) {
+          const f16x8 bh = frag(S.x[0], r0, v0 + 16 * v, i, q);
+          const f16x8 bl = frag(S.x[1], r0, v0 + 16 * v, i, q);
+#pragma unroll
+          for (int u = 0; u < TU; ++u) a[u * TV + v] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[u], bh, a[u * TV + v], 0, 0, 0);
+#pragma unroll
+          for (int u = 0; u < TU; ++u) a[u * TV + v] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[u], bl, a[u * TV + v], 0, 0, 0);
+#pragma unroll
+          for (int u = 0; u < TU; ++u) a[u * TV + v] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[u], bh, a[u * TV + v], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // the block's dW [LD][LD]
+  __device__ __forceinline__ void store(float* base, int tid) const {
+    const int lane = tid & 63, wv = tid >> 6, i = lane & 15, q = lane >> 4;
+    const int u0 = 16 * TU * (wv / (LD / 16 / TV)), v0 = 16 * TV * (wv % (LD / 16 / TV));
+#pragma unroll
+    for (int u = 0; u < TU; ++u)
+#pragma unroll
+      for (int v = 0; v < TV; ++v)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          base[(size_t)(u0 + 16 * u + 4 * q + r) * LD + v0 + 16 * v + i] = __builtin_amdgcn_ldexpf(a[u * TV + v][r], -c);
+  }
+};
+
+// The pieces of a whole row of values (zero when not live).
+template <int LD>
+__device__ __forceinline__ void split_row(RowPieces<LD>& r, const float* x, bool live) {
+  r.e = row_exp<LD>(x);
+  const float s = live ? scale_of(r.e) : 0.f;
+#pragma unroll
+  for (int k = 0; k < X3<LD>::KS; ++k) r.p[k] = split8(x + 8 * k, s);
 }
 
 }  // namespace dev
