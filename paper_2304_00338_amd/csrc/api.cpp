@@ -40,11 +40,10 @@ struct PackOff {
   int64_t F1 = -1, F2 = -1, F1t = -1, F2t = -1;  // fp32 edge MLPs (encoder: W2): fragment-major W1e, W2, transposes
   // fp32 split products: two-piece fp16 fragments (edge MLPs: W1e, W2 and their transposes)
   int64_t S1 = -1, S2 = -1, S1t = -1, S2t = -1;
+  int64_t S1a = -1, S1at = -1, S1s = -1, S1r = -1;  // node MLPs: agg block (S1: h block); edge MLPs: sender, receiver block
   int64_t W1sp = -1, W1rp = -1;  // edge MLPs: row-permuted sender / receiver column blocks of W1
   int64_t W1ap = -1;             // node MLPs at width 160: row-permuted agg column block of W1
-  // fp32 row-layout node kernels: node MLPs' W1 agg block (F1: its h block),
-  // edge MLPs' W1 sender and receiver blocks, fragment-major and transposed
-  int64_t F1a = -1, F1at = -1, F1s = -1, F1r = -1, F1st = -1, F1rt = -1;
+  int64_t F1st = -1, F1rt = -1;  // fp32 sender sums: edge MLPs' W1 sender / receiver blocks, transposed
 };
 
 struct Model {
@@ -166,6 +165,7 @@ Model make_model(int m, int lat, bool fp32 = false) {
     // fp32 row-layout and split-product kernels: fragment copies only
     add_frag(M, M.enc_edge.W2, D, D, 2, M.p_enc_edge.F2);
     add_frag(M, M.enc_edge.W2, D, D, 3, M.p_enc_edge.F2t);
+    add_split(M, M.enc_node.W2, D, D, 4, M.p_enc_node.S2);
     add_frag(M, M.enc_node.W2, D, D, 2, M.p_enc_node.F2);
     add_frag(M, M.enc_node.W2, D, D, 3, M.p_enc_node.F2t);
     for (int i = 0; i < m; ++i) {
@@ -173,16 +173,16 @@ Model make_model(int m, int lat, bool fp32 = false) {
       add_split(M, M.edge[i].W2, D, D, 4, M.p_edge[i].S2);
       add_split(M, M.edge[i].W1, 3 * D, D, 5, M.p_edge[i].S1t);
       add_split(M, M.edge[i].W2, D, D, 5, M.p_edge[i].S2t);
-      add_frag(M, M.edge[i].W1 + D, 3 * D, D, 2, M.p_edge[i].F1s);
-      add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 2, M.p_edge[i].F1r);
+      add_split(M, M.edge[i].W1 + D, 3 * D, D, 4, M.p_edge[i].S1s);
+      add_split(M, M.edge[i].W1 + 2 * D, 3 * D, D, 4, M.p_edge[i].S1r);
       add_frag(M, M.edge[i].W1 + D, 3 * D, D, 3, M.p_edge[i].F1st);
       add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 3, M.p_edge[i].F1rt);
-      add_frag(M, M.node[i].W1, 2 * D, D, 2, M.p_node[i].F1);
-      add_frag(M, M.node[i].W1 + D, 2 * D, D, 2, M.p_node[i].F1a);
-      add_frag(M, M.node[i].W2, D, D, 2, M.p_node[i].F2);
-      add_frag(M, M.node[i].W1, 2 * D, D, 3, M.p_node[i].F1t);
-      add_frag(M, M.node[i].W1 + D, 2 * D, D, 3, M.p_node[i].F1at);
-      add_frag(M, M.node[i].W2, D, D, 3, M.p_node[i].F2t);
+      add_split(M, M.node[i].W1, 2 * D, D, 4, M.p_node[i].S1);
+      add_split(M, M.node[i].W1 + D, 2 * D, D, 4, M.p_node[i].S1a);
+      add_split(M, M.node[i].W2, D, D, 4, M.p_node[i].S2);
+      add_split(M, M.node[i].W1, 2 * D, D, 5, M.p_node[i].S1t);
+      add_split(M, M.node[i].W1 + D, 2 * D, D, 5, M.p_node[i].S1at);
+      add_split(M, M.node[i].W2, D, D, 5, M.p_node[i].S2t);
     }
     add_frag(M, M.dec.W1, D, D, 2, M.p_dec.F1);
     add_frag(M, M.dec.W1, D, D, 3, M.p_dec.F1t);
@@ -563,14 +563,14 @@ struct Run {
     w.S2 = p.S2 >= 0 ? P(p.S2) : nullptr;
     w.S1t = p.S1t >= 0 ? P(p.S1t) : nullptr;
     w.S2t = p.S2t >= 0 ? P(p.S2t) : nullptr;
+    w.S1a = p.S1a >= 0 ? P(p.S1a) : nullptr;
+    w.S1at = p.S1at >= 0 ? P(p.S1at) : nullptr;
+    w.S1s = p.S1s >= 0 ? P(p.S1s) : nullptr;
+    w.S1r = p.S1r >= 0 ? P(p.S1r) : nullptr;
     w.F1 = p.F1 >= 0 ? (const float*)P(p.F1) : nullptr;
     w.F2 = p.F2 >= 0 ? (const float*)P(p.F2) : nullptr;
     w.F1t = p.F1t >= 0 ? (const float*)P(p.F1t) : nullptr;
     w.F2t = p.F2t >= 0 ? (const float*)P(p.F2t) : nullptr;
-    w.F1a = p.F1a >= 0 ? (const float*)P(p.F1a) : nullptr;
-    w.F1at = p.F1at >= 0 ? (const float*)P(p.F1at) : nullptr;
-    w.F1s = p.F1s >= 0 ? (const float*)P(p.F1s) : nullptr;
-    w.F1r = p.F1r >= 0 ? (const float*)P(p.F1r) : nullptr;
     w.F1st = p.F1st >= 0 ? (const float*)P(p.F1st) : nullptr;
     w.F1rt = p.F1rt >= 0 ? (const float*)P(p.F1rt) : nullptr;
     w.W1f = params + o.W1;
@@ -629,7 +629,7 @@ struct Run {
     MlpW e0;
     if (m > 0) e0 = W(M.edge[0], M.p_edge[0]);
     if (prec == MGN_FP32)
-      LAUNCH(K_NODE_ENC, launch_node_enc_r32(D, N, node_in, W(M.enc_node, M.p_enc_node), m > 0 ? &e0 : nullptr, eps,
+      LAUNCH(K_NODE_ENC, launch_node_enc_x3(D, N, node_in, W(M.enc_node, M.p_enc_node), m > 0 ? &e0 : nullptr, eps,
                                              h_l(k, 0), m > 0 ? (float*)P_l(k, 0) : nullptr, s));
     else
       LAUNCH(K_NODE_ENC, launch_node_enc(prec, D, N, node_in, W(M.enc_node, M.p_enc_node), m > 0 ? &e0 : nullptr, eps,
@@ -668,7 +668,7 @@ struct Run {
         LAUNCH(K_NODE_FWD, launch_node_fwd_w160(N, h_l(k, l), agg_l(k, l), W(M.node[l], M.p_node[l]), eps, h_l(k, l + 1), s));
         if (!last) LAUNCH(K_EMIT, launch_emit_w160(N, h_l(k, l + 1), nx, P_l(k, l + 1), s));
       } else {
-        LAUNCH(K_NODE_FWD, launch_node_fwd_r32(D, N, h_l(k, l), agg_l(k, l), W(M.node[l], M.p_node[l]),
+        LAUNCH(K_NODE_FWD, launch_node_fwd_x3(D, N, h_l(k, l), agg_l(k, l), W(M.node[l], M.p_node[l]),
                                                last ? nullptr : &nx, eps, h_l(k, l + 1),
                                                last ? nullptr : (float*)P_l(k, l + 1), s));
       }
@@ -688,6 +688,13 @@ struct Run {
     if (rq.n > 0) LAUNCH(K_REDUCE, launch_reduce_batch(part(), (int64_t)kPartBlocks * part_stride(D), rq, grad, s));
     rq.n = 0;
     return MGN_OK;
+  }
+  // The weight gradient G^T X of M rows into region r at float offset off,
+  // queued for the next launch_wgrad_x3 (wq).
+  WgradJobs wq{};
+  void wgrad(const float* G, const float* X, int64_t M, int r, int64_t off) {
+    const Partials p = partr(r);
+    wq.j[wq.n++] = WgradJob{G, X, M, p.buf + off, p.stride, 0, 0};
   }
   int job(int nb, int r, int64_t src, int rows, int cols, float* grad, int64_t dst, int64_t ld) {
     if (nb <= 0 || rows <= 0 || cols <= 0) return MGN_OK;
@@ -727,8 +734,10 @@ struct Run {
       float* dz1 = (float*)(ws + c.L.nstr);
       LAUNCH(K_DECODER_BWD, launch_decoder_bwd_r32(D, N, h_l(k, m), gout, W(M.dec, M.p_dec), hb_cur, dz1, pt, &nb, s));
       if ((rc = reduce(nb, 0, 1, 5 * D + 4, grad, M.dec.b1, 0)) != MGN_OK) return rc;
-      LAUNCH(K_DECODER_BWD, launch_wgrad_x3(D, N, dz1, h_l(k, m), pt, &nb, s));
-      if ((rc = reduce(nb, 0, D, D, grad, M.dec.W1, D)) != MGN_OK) return rc;
+      wq.n = 0;
+      wgrad(dz1, h_l(k, m), N, 0, 0);
+      LAUNCH(K_DECODER_BWD, launch_wgrad_x3(D, wq, pt, s));
+      if ((rc = reduce(wq.j[0].nb, 0, D, D, grad, M.dec.W1, D)) != MGN_OK) return rc;
     } else {
       LAUNCH(K_DECODER_BWD, launch_decoder_bwd(prec, D, N, h_l(k, m), gout, W(M.dec, M.p_dec), hb_cur, pt, &nb, s));
       if ((rc = reduce(nb, 0, 1, (int)M.dec.size, grad, M.dec.W1, 0)) != MGN_OK) return rc;
@@ -760,20 +769,19 @@ struct Run {
         // streams: dW1 by its h and agg column blocks, and dW2
         float* ns = (float*)(ws + c.L.nstr);
         const size_t nd = (size_t)N * D;
-        LAUNCH(K_NODE_BWD, launch_node_bwd_r32(D, N, h_l(k, l), agg_l(k, l), hb_cur, W(on, M.p_node[l]), eps,
+        LAUNCH(K_NODE_BWD, launch_node_bwd_x3(D, N, h_l(k, l), agg_l(k, l), hb_cur, W(on, M.p_node[l]), eps,
                                                hb_part, aggbar, ns, P0, &nb, s));
         if ((rc = job(nb, 0, 0, 1, D, grad, on.b1, 0)) != MGN_OK) return rc;
         if ((rc = job(nb, 0, D, 1, D, grad, on.b2, 0)) != MGN_OK) return rc;
         if ((rc = job(nb, 0, 2 * D, 1, 2 * D, grad, on.g, 0)) != MGN_OK) return rc;
-        Partials q = P1;
-        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, N, ns + 2 * nd, h_l(k, l), q, &nb, s));
-        if ((rc = job(nb, 1, 0, D, D, grad, on.W1, 2 * D)) != MGN_OK) return rc;
-        q.buf += (size_t)D * D;
-        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, N, ns + 2 * nd, agg_l(k, l), q, &nb, s));
-        if ((rc = job(nb, 1, (int64_t)D * D, D, D, grad, on.W1 + D, 2 * D)) != MGN_OK) return rc;
-        q.buf += (size_t)D * D;
-        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, N, ns + nd, ns, q, &nb, s));
-        if ((rc = job(nb, 1, 2 * (int64_t)D * D, D, D, grad, on.W2, D)) != MGN_OK) return rc;
+        wq.n = 0;
+        wgrad(ns + 2 * nd, h_l(k, l), N, 1, 0);
+        wgrad(ns + 2 * nd, agg_l(k, l), N, 1, (int64_t)D * D);
+        wgrad(ns + nd, ns, N, 1, 2 * (int64_t)D * D);
+        LAUNCH(K_WGRAD_NODE, launch_wgrad_x3(D, wq, P1, s));
+        if ((rc = job(wq.j[0].nb, 1, 0, D, D, grad, on.W1, 2 * D)) != MGN_OK) return rc;
+        if ((rc = job(wq.j[1].nb, 1, (int64_t)D * D, D, D, grad, on.W1 + D, 2 * D)) != MGN_OK) return rc;
+        if ((rc = job(wq.j[2].nb, 1, 2 * (int64_t)D * D, D, D, grad, on.W2, D)) != MGN_OK) return rc;
       }
       if (E == 0) {
         // no edges: the edge MLP gets no gradient and every R is zero
@@ -799,14 +807,12 @@ struct Run {
         if ((rc = job(nb, 3, 0, D, D, grad, oe.W1, 3 * D)) != MGN_OK) return rc;
         if ((rc = job(nb, 3, (int64_t)D * D, D, D, grad, oe.W2, D)) != MGN_OK) return rc;
       } else {
-        // fp32: one wave per tile (dW2 and the vectors in the pass), then
-        // dW1e = sum zbar^T e over the two streams
+        // fp32: one wave per tile (dW2 and the vectors in the pass); dW1e =
+        // sum zbar^T e follows with the sender sums' weight gradients
         LAUNCH(K_EDGE_BWD, launch_edge_bwd_x3(D, tl, e_l(k, l), (float*)ebar, l < m - 1 ? 1 : 0, (float*)ebar,
                                               P_l(k, l), aggbar, W(oe, M.p_edge[l]), eps, zbar, R, slots(), P2, &nb,
                                               s));
         if ((rc = job(nb, 2, (int64_t)D * D, 1, (int)(oe.size - 3 * D * D), grad, oe.b1, 0)) != MGN_OK) return rc;
-        LAUNCH(K_WGRAD, launch_wgrad_x3(D, E, (const float*)zbar, (const float*)e_l(k, l), P3, &nb, s));
-        if ((rc = job(nb, 3, 0, D, D, grad, oe.W1, 3 * D)) != MGN_OK) return rc;
       }
       if (g.n_long > 0) LAUNCH(K_FIXUP, launch_slot_fixup(D, g.long_nodes, g.n_long, slots(), R, s));
       if (prec == MGN_BF16 && !rows())
@@ -816,16 +822,19 @@ struct Run {
                                             ws + c.L.nstr, P4, &nb, s));
       else if (prec == MGN_FP32) {
         // fp32: S into the node-stream scratch (its streams are consumed by
-        // now), then dW1s = sum S h^T and dW1r = sum R h^T from the rows
+        // now), then dW1s = sum S h^T and dW1r = sum R h^T from the rows, and
+        // dW1e
         float* Sv = (float*)(ws + c.L.nstr);
         LAUNCH(K_SRCSUM, launch_node_srcsum_r32(D, N, g.rowptr, g.rev, (const float*)zbar, R, hb_part,
                                                 W(oe, M.p_edge[l]), hb_cur, Sv, s));
-        Partials q = P4;
-        LAUNCH(K_SRCSUM, launch_wgrad_x3(D, N, Sv, h_l(k, l), q, &nb, s));
-        if ((rc = job(nb, 4, 0, D, D, grad, oe.W1 + D, 3 * D)) != MGN_OK) return rc;
-        q.buf += (size_t)D * D;
-        LAUNCH(K_SRCSUM, launch_wgrad_x3(D, N, R, h_l(k, l), q, &nb, s));
-        if ((rc = job(nb, 4, (int64_t)D * D, D, D, grad, oe.W1 + 2 * D, 3 * D)) != MGN_OK) return rc;
+        wq.n = 0;
+        wgrad(Sv, h_l(k, l), N, 4, 0);
+        wgrad(R, h_l(k, l), N, 4, (int64_t)D * D);
+        if (E > 0) wgrad((const float*)zbar, (const float*)e_l(k, l), E, 3, 0);
+        LAUNCH(K_WGRAD, launch_wgrad_x3(D, wq, P4, s));
+        if ((rc = job(wq.j[0].nb, 4, 0, D, D, grad, oe.W1 + D, 3 * D)) != MGN_OK) return rc;
+        if ((rc = job(wq.j[1].nb, 4, (int64_t)D * D, D, D, grad, oe.W1 + 2 * D, 3 * D)) != MGN_OK) return rc;
+        if (E > 0 && (rc = job(wq.j[2].nb, 3, 0, D, D, grad, oe.W1, 3 * D)) != MGN_OK) return rc;
       } else {
         LAUNCH(K_SRCSUM, launch_node_srcsum(prec, D, N, g.rowptr, g.rev, zbar, R, h_l(k, l), hb_part, W(oe, M.p_edge[l]),
                                             hb_cur, P4, &nb, s));
@@ -863,8 +872,10 @@ struct Run {
       LAUNCH(K_NODE_ENC_BWD, launch_node_enc_bwd_r32(D, N, node_in, hb_cur, W(o, M.p_enc_node), eps, gin, ns, pt, &nb, s));
       if ((rc = reduce(nb, 0, 1, 9 * D, grad, o.W1, 0)) != MGN_OK) return rc;
       if ((rc = reduce(nb, 9 * D, 1, 3 * D, grad, o.b2, 0)) != MGN_OK) return rc;
-      LAUNCH(K_NODE_ENC_BWD, launch_wgrad_x3(D, N, ns + (size_t)N * D, ns, pt, &nb, s));
-      if ((rc = reduce(nb, 0, D, D, grad, o.W2, D)) != MGN_OK) return rc;
+      wq.n = 0;
+      wgrad(ns + (size_t)N * D, ns, N, 0, 0);
+      LAUNCH(K_NODE_ENC_BWD, launch_wgrad_x3(D, wq, pt, s));
+      if ((rc = reduce(wq.j[0].nb, 0, D, D, grad, o.W2, D)) != MGN_OK) return rc;
     } else {
       LAUNCH(K_NODE_ENC_BWD, launch_node_enc_bwd(prec, D, N, node_in, hb_cur, W(M.enc_node, M.p_enc_node), eps, gin, pt,
                                                  &nb, s));

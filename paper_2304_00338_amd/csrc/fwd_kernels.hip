@@ -71,13 +71,13 @@ __global__ void __launch_bounds__(1024) k_pack_split(const float* __restrict__ p
 #pragma unroll
   for (int k = 0; k < 16; ++k) mx = fmaxf(mx, wm[k]);
   const int e = scale_exp(mx);
-  const float s = scale_of(e);
   const int NOB = pe.rows / 32;
   _Float16* dst = reinterpret_cast<_Float16*>(pack + pe.dst);
   for (int idx = blockIdx.x * 1024 + tid; idx < n; idx += gridDim.x * 1024) {
     const int t = idx & 7, l = (idx >> 3) & 63, rest = idx >> 9, ob = rest % NOB, ks = rest / NOB, m = l & 31;
     const int64_t o = X3<128>::feat((m >> 2) & 1, 16 * ob + (m & 3) + 4 * (m >> 3)), k = X3<128>::feat(l >> 5, 8 * ks + t);
-    const float v = s * params[pe.perm == 4 ? pe.src + o * pe.ld + k : pe.src + k * pe.ld + o];
+    const float v =
+        __builtin_amdgcn_ldexpf(params[pe.perm == 4 ? pe.src + o * pe.ld + k : pe.src + k * pe.ld + o], e);
     const _Float16 h = (_Float16)v;
     _Float16* q = dst + (int64_t)rest * 2 * 512 + l * 8 + t;
     q[0] = h;

@@ -20,20 +20,20 @@ struct MlpW {
   const void* W1t;
   const void* W2;
   const void* W2t;
-  const float* F1;   // fp32 row-layout kernels: fragment-major copies of the edge
-  const float* F2;   // MLP's W1e (first layer, edge-latent block) and W2, and of
-  const float* F1t;  // their transposes (node MLPs: F1 is W1's h block)
+  const float* F1;   // fp32 row-layout kernels: fragment-major copies of the
+  const float* F2;   // decoder's W1 and the encoders' W2, and of their transposes
+  const float* F1t;
   const float* F2t;
-  const float* F1a;   // fp32 node MLPs: fragment-major agg block of W1 and its transpose
-  const float* F1at;
-  const float* F1s;   // fp32 edge MLPs: fragment-major sender / receiver blocks of W1
-  const float* F1r;   // (the node products P = [W1s h, W1r h]) and their transposes
-  const float* F1st;
+  const float* F1st;  // fp32 edge MLPs: transposed sender / receiver blocks of W1
   const float* F1rt;
   const void* S1;    // fp32 split products (pack modes 4, 5): two-piece fp16
-  const void* S2;    // fragments of the edge MLP's W1e and W2, and of their
+  const void* S2;    // fragments of the MLP's W1 (edge: W1e) and W2, and of their
   const void* S1t;   // transposes
   const void* S2t;
+  const void* S1a;   // node MLPs: W1's agg block (S1, S1t: its h block) and its transpose
+  const void* S1at;
+  const void* S1s;   // edge MLPs: W1's sender and receiver blocks
+  const void* S1r;
   const float* W1f;  // float32 first-layer weights (encoders: K = 4 / 8 on VALU)
   const float* W2f;  // float32 second-layer weights (decoder: 4 outputs on VALU)
   const float* b1;
@@ -112,17 +112,17 @@ hipError_t launch_node_enc(int prec, int lat, int64_t N, const float* node_in, c
 // fragment-major W2 and, for the reverse, its transpose): e = LN(W2 relu(W1
 // f + b1) + b2), and all encoder parameter gradients from ebar as per-block
 // partials in the encoder's parameter order.
-// fp32 node phase in the row layout (width 128 or 160; needs the node MLP's
-// fragment-major F1, F1a, F2 and, with nx, the next edge MLP's F1s, F1r):
+// fp32 node phase (width 128 or 160; needs the node MLP's S1, S1a, S2 and,
+// with nx, the next edge MLP's S1s, S1r):
 // h_out = h + LN(W2 relu(W1 [h, agg] + b1) + b2), and with nx the next
 // block's node products P_out = [W1s h_out, W1r h_out] ([N][2 lat] fp32).
-hipError_t launch_node_fwd_r32(int lat, int64_t N, const float* h_in, const float* agg, const MlpW& w,
+hipError_t launch_node_fwd_x3(int lat, int64_t N, const float* h_in, const float* agg, const MlpW& w,
                                const MlpW* nx, float eps, float* h_out, float* P_out, hipStream_t s);
 // Its reverse: hbar_part = hbar_in + W1h^T dz1, aggbar = W1a^T dz1, the
 // rows of a1, dz2, dz1 into streams ([3][N][lat] fp32, for the weight
 // gradients by launch_wgrad_x3), and per-block [4][lat] partials of db1,
-// db2, dgamma, dbeta (needs F1t, F1at, F2t too).
-hipError_t launch_node_bwd_r32(int lat, int64_t N, const float* h, const float* agg, const float* hbar_in,
+// db2, dgamma, dbeta (needs S1t, S1at, S2t too).
+hipError_t launch_node_bwd_x3(int lat, int64_t N, const float* h, const float* agg, const float* hbar_in,
                                const MlpW& w, float eps, float* hbar_part, float* aggbar, float* streams,
                                const Partials& part, int* nblocks, hipStream_t s);
 // fp32 sender-side sums in the row layout (needs the edge MLP's F1st, F1rt):
@@ -138,14 +138,14 @@ hipError_t launch_node_srcsum_r32(int lat, int64_t N, const int32_t* rowptr, con
 hipError_t launch_decoder_r32(int lat, int64_t N, const float* h, const MlpW& w, float* out, hipStream_t s);
 hipError_t launch_decoder_bwd_r32(int lat, int64_t N, const float* h, const float* gout, const MlpW& w, float* hbar,
                                   float* dz1s, const Partials& part, int* nblocks, hipStream_t s);
-// fp32 node encoder in the row layout (needs the encoder's fragment-major F2
-// and, for the reverse, F2t; with nx the first edge MLP's F1s, F1r): h0 =
+// fp32 node encoder (needs the encoder's S2, for the reverse its
+// fragment-major F2 and F2t; with nx the first edge MLP's S1s, S1r): h0 =
 // LN(W2 relu(W1 x + b1) + b2) from the 8 node inputs, with nx also the node
 // products of the first MP block.  The reverse writes gin = dL/dx (when
 // given), the a1 and dz2 rows into streams ([2][N][lat], for dW2 by
 // launch_wgrad_x3) and per-block partials [lat][8] dW1, [lat] db1, db2,
 // dgamma, dbeta.
-hipError_t launch_node_enc_r32(int lat, int64_t N, const float* x, const MlpW& w, const MlpW* nx, float eps,
+hipError_t launch_node_enc_x3(int lat, int64_t N, const float* x, const MlpW& w, const MlpW* nx, float eps,
                                float* h_out, float* P_out, hipStream_t s);
 hipError_t launch_node_enc_bwd_r32(int lat, int64_t N, const float* x, const float* ybar, const MlpW& w, float eps,
                                    float* gin, float* streams, const Partials& part, int* nblocks, hipStream_t s);
@@ -249,11 +249,23 @@ hipError_t launch_decoder(int prec, int lat, int64_t N, const float* h, const Ml
 
 hipError_t launch_decoder_bwd(int prec, int lat, int64_t N, const float* h, const float* gout, const MlpW& w,
                               float* hbar, const Partials& part, int* nblocks, hipStream_t s);
-// dW[o][i] = sum_rows G[row][o] X[row][i] for fp32 [M][lat] streams (lat
-// 128 or 160), written as per-block [lat][lat]
-// partials.
-hipError_t launch_wgrad_x3(int lat, int64_t M, const float* G, const float* X, const Partials& part, int* nblocks,
-                           hipStream_t s);
+// Up to three weight gradients dW[o][i] = sum_rows G[row][o] X[row][i] of fp32
+// [M][lat] streams (M > 0, lat 128 or 160) in one launch, written as nb
+// per-block [lat][lat] partials, stride floats apart, at part (the launcher sets
+// nb and b0; nb <= part.max_blocks of the partial region).
+struct WgradJob {
+  const float* G;
+  const float* X;
+  int64_t M;
+  float* part;
+  int64_t stride;
+  int32_t nb, b0;
+};
+struct WgradJobs {
+  WgradJob j[3];
+  int32_t n;
+};
+hipError_t launch_wgrad_x3(int lat, WgradJobs& jobs, const Partials& part, hipStream_t s);
 hipError_t launch_node_srcsum(int prec, int lat, int64_t N, const int32_t* rowptr, const int32_t* rev, const void* zbar,
                               const float* R, const float* h, const float* hbar_part, const MlpW& w,
                               float* hbar_out, const Partials& part, int* nblocks, hipStream_t s);
@@ -271,7 +283,7 @@ struct ReduceJob {
   int64_t src, dst, ld, blk0;  // blk0: first launch block of the job (set by the launcher)
   int32_t rows, cols, nblocks, region;
 };
-constexpr int kMaxReduceJobs = 8;
+constexpr int kMaxReduceJobs = 12;
 struct ReduceBatch {
   ReduceJob j[kMaxReduceJobs];
   int32_t n;

@@ -13,19 +13,6 @@
 namespace mgn {
 namespace dev {
 
-// z1 = (b1 + W1h h) + W1a agg for the lane's features (the C layout of
-// gemm32: acc[ob][r] is feature f0 + 4 ob + r).  Shared by the forward and
-// the reverse, so the reverse's recompute equals the forward bitwise.
-template <int LD>
-__device__ __forceinline__ void node_z1_r32(f32x4 (&acc)[R32<LD>::NOB], const float (&h)[R32<LD>::KL],
-                                            const float (&a)[R32<LD>::KL], const MlpW& w, int f0, int lane,
-                                            int oz) {
-#pragma unroll
-  for (int ob = 0; ob < R32<LD>::NOB; ++ob) acc[ob] = *reinterpret_cast<const f32x4*>(w.b1 + f0 + 4 * ob);
-  gemm32<LD>(acc, h, w.F1 + oz, lane);
-  gemm32<LD>(acc, a, w.F1a + oz, lane);
-}
-
 // LayerNorm statistics of a row over its DR real features (padded features
 // hold 0 and are left out of the variance): acc becomes acc - mean.
 template <int LD>
@@ -48,220 +35,6 @@ __device__ __forceinline__ float ln_center_r32(f32x4 (&acc)[R32<LD>::NOB], int f
     }
   return __builtin_amdgcn_rsqf(sum_q(sq) * (1.0f / Z::DR) + eps);
 }
-
-// Forward: h_out = h + LN(W2 relu(z1) + b2); with EMIT, also the next
-// block's node products P_out = [W1s h_out, W1r h_out] ([N][2 LD]) from the
-// next edge MLP nx.  The next unit's agg row is requested after the first
-// layer, its h row after the residual (single buffers: each is dead by
-// then); rows past N read row N - 1 and store nothing.
-template <int LD, bool EMIT>
-__global__ void __launch_bounds__(R32_NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_node_fwd_r32(int64_t N, const float* __restrict__ h_in, const float* __restrict__ agg, MlpW w, MlpW nx, float eps,
-               float* __restrict__ h_out, float* __restrict__ P_out) {
-  typedef R32<LD> Z;
-  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t nu = (N + 15) >> 4;
-  const UnitRange ur = unit_range<R32_NW>(nu, wv);
-  if (ur.t >= ur.end) return;
-  const int f0 = Z::KL * g;
-  auto rowp = [&](int64_t u) { return (size_t)min(u * 16 + i, N - 1) * LD + f0; };
-  float h[Z::KL], a[Z::KL];
-  load_row32<LD>(h, h_in + rowp(ur.t));
-  load_row32<LD>(a, agg + rowp(ur.t));
-  for (int64_t u = ur.t; u < ur.end; u += ur.stride) {
-    const int64_t un = u + ur.stride;
-    const bool live = u * 16 + i < N;
-    // the weight addresses are opaque per unit: otherwise the loop-invariant
-    // fragment loads are hoisted out of the loop into registers
-    const int oz = opaque_zero();
-    f32x4 acc[Z::NOB];
-    node_z1_r32<LD>(acc, h, a, w, f0, lane, oz);
-    load_row32<LD>(a, agg + rowp(un));
-    float a1[Z::KL];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) a1[4 * ob + r] = relu(acc[ob][r]);
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = *reinterpret_cast<const f32x4*>(w.b2 + f0 + 4 * ob);
-    gemm32<LD>(acc, a1, w.F2 + oz, lane);
-    const float rstd = ln_center_r32<LD>(acc, f0, eps);
-    float y[Z::KL];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) {
-      const f32x4 ga = *reinterpret_cast<const f32x4*>(w.gamma + f0 + 4 * ob);
-      const f32x4 be = *reinterpret_cast<const f32x4*>(w.beta + f0 + 4 * ob);
-      const f32x4 m = ga * (acc[ob] * rstd) + be;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) y[4 * ob + r] = m[r] + h[4 * ob + r];
-    }
-    if (live) {
-      float* p = h_out + (size_t)(u * 16 + i) * LD + f0;
-#pragma unroll
-      for (int c = 0; c < Z::KC; ++c)
-        *reinterpret_cast<f32x4*>(p + 4 * c) = f32x4{y[4 * c], y[4 * c + 1], y[4 * c + 2], y[4 * c + 3]};
-    }
-    load_row32<LD>(h, h_in + rowp(un));
-    if (EMIT) {
-      f32x4 ps[Z::NOB];
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = ps[ob] = f32x4{0.f, 0.f, 0.f, 0.f};
-      gemm32<LD>(ps, y, nx.F1s + oz, lane);
-      gemm32<LD>(acc, y, nx.F1r + oz, lane);
-      if (live) {
-        float* p = P_out + (size_t)(u * 16 + i) * (2 * LD) + f0;
-        store_row32<LD>(p, ps);
-        store_row32<LD>(p + LD, acc);
-      }
-    }
-  }
-}
-
-// Reverse of the node phase for the rows of hbar_in = dL/dh_out: the
-// forward recomputed (z1 bitwise as in the forward), the LayerNorm reverse
-// (padded features of dz2 zeroed), da1 = W2^T dz2, dz1 = da1 where z1 > 0,
-// hbar_part = hbar_in + W1h^T dz1 and aggbar = W1a^T dz1.  The rows of a1,
-// dz2 and dz1 go to the streams (fp32 [N][LD] each) for the weight-gradient
-// passes (dW1 = sum dz1^T [h, agg], dW2 = sum dz2^T a1); db1, db2, dgamma
-// and dbeta are DPP column sums, written per block as [4][LD] partials (db1,
-// db2, dgamma, dbeta).  Each input row is requested again for the next unit
-// once its last use is issued.
-template <int LD>
-__global__ void __launch_bounds__(R32_NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_node_bwd_r32(int64_t N, const float* __restrict__ h_in, const float* __restrict__ agg,
-               const float* __restrict__ hbar_in, MlpW w, float eps, float* __restrict__ hbar_part,
-               float* __restrict__ aggbar, float* __restrict__ a1s, float* __restrict__ dz2s,
-               float* __restrict__ dz1s, Partials part) {
-  typedef R32<LD> Z;
-  __shared__ __align__(16) float red[4][R32_NW][LD];
-  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t nu = (N + 15) >> 4;
-  const UnitRange ur = unit_range<R32_NW>(nu, wv);
-  const int f0 = Z::KL * g;
-  ColSum32<LD> cs[4];  // db1, db2, dgamma, dbeta
-  if (ur.t < ur.end) {
-    auto rowp = [&](int64_t u) { return (size_t)min(u * 16 + i, N - 1) * LD + f0; };
-    float h[Z::KL], a[Z::KL], yb[Z::KL];
-    load_row32<LD>(h, h_in + rowp(ur.t));
-    load_row32<LD>(a, agg + rowp(ur.t));
-    load_row32<LD>(yb, hbar_in + rowp(ur.t));
-    for (int64_t u = ur.t; u < ur.end; u += ur.stride) {
-      const int64_t un = u + ur.stride;
-      const bool live = u * 16 + i < N;
-      const size_t orow = (size_t)(u * 16 + i) * LD + f0;
-      const int oz = opaque_zero();
-      // ---- the forward: z1, its ReLU mask, a1, z2 and its LayerNorm
-      f32x4 acc[Z::NOB];
-      node_z1_r32<LD>(acc, h, a, w, f0, lane, oz);
-      load_row32<LD>(h, h_in + rowp(un));
-      load_row32<LD>(a, agg + rowp(un));
-      float a1[Z::KL];
-      uint64_t mask = 0;
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          a1[4 * ob + r] = relu(acc[ob][r]);
-          if (acc[ob][r] > 0.f) mask |= 1ull << (4 * ob + r);
-        }
-      if (live) {
-        float* p = a1s + orow;
-#pragma unroll
-        for (int c = 0; c < Z::KC; ++c)
-          *reinterpret_cast<f32x4*>(p + 4 * c) = f32x4{a1[4 * c], a1[4 * c + 1], a1[4 * c + 2], a1[4 * c + 3]};
-      }
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = *reinterpret_cast<const f32x4*>(w.b2 + f0 + 4 * ob);
-      gemm32<LD>(acc, a1, w.F2 + oz, lane);
-      const float rstd = ln_center_r32<LD>(acc, f0, eps);
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] *= rstd;  // xhat
-      // ---- dbeta, dgamma (live rows); the LayerNorm reverse
-      f32x4 t[Z::NOB];
-      {
-        f32x4 p[Z::NOB];
-#pragma unroll
-        for (int ob = 0; ob < Z::NOB; ++ob) {
-          t[ob] = f32x4{yb[4 * ob], yb[4 * ob + 1], yb[4 * ob + 2], yb[4 * ob + 3]};
-          p[ob] = live ? t[ob] : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        cs[3].add(p, i);
-#pragma unroll
-        for (int ob = 0; ob < Z::NOB; ++ob) p[ob] = live ? t[ob] * acc[ob] : f32x4{0.f, 0.f, 0.f, 0.f};
-        cs[2].add(p, i);
-      }
-      float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) {
-        t[ob] *= *reinterpret_cast<const f32x4*>(w.gamma + f0 + 4 * ob);  // dxh
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          s1 += t[ob][r];
-          s2 += t[ob][r] * acc[ob][r];
-        }
-      }
-      const float m1 = sum_q(s1) * (1.0f / Z::DR), m2 = sum_q(s2) * (1.0f / Z::DR);
-      float dz[Z::KL];
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          dz[4 * ob + r] = (Z::DR == LD || f0 + 4 * ob + r < Z::DR) ? rstd * (t[ob][r] - m1 - acc[ob][r] * m2) : 0.f;
-      {
-        f32x4 p[Z::NOB];
-#pragma unroll
-        for (int ob = 0; ob < Z::NOB; ++ob)
-          p[ob] = live ? f32x4{dz[4 * ob], dz[4 * ob + 1], dz[4 * ob + 2], dz[4 * ob + 3]} : f32x4{0.f, 0.f, 0.f, 0.f};
-        cs[1].add(p, i);
-        if (live) store_row32<LD>(dz2s + orow, p);
-      }
-      // ---- da1 = W2^T dz2, dz1 = da1 where z1 > 0
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = f32x4{0.f, 0.f, 0.f, 0.f};
-      gemm32<LD>(acc, dz, w.F2t + oz, lane);
-      float d1[Z::KL];
-      {
-        f32x4 p[Z::NOB];
-#pragma unroll
-        for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float v = (mask >> (4 * ob + r)) & 1ull ? acc[ob][r] : 0.f;
-            d1[4 * ob + r] = v;
-            p[ob][r] = live ? v : 0.f;
-          }
-        cs[0].add(p, i);
-        if (live) store_row32<LD>(dz1s + orow, p);
-      }
-      // ---- hbar_part = hbar_in + W1h^T dz1, aggbar = W1a^T dz1
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob)
-        acc[ob] = f32x4{yb[4 * ob], yb[4 * ob + 1], yb[4 * ob + 2], yb[4 * ob + 3]};
-      gemm32<LD>(acc, d1, w.F1t + oz, lane);
-      if (live) store_row32<LD>(hbar_part + orow, acc);
-      load_row32<LD>(yb, hbar_in + rowp(un));
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = f32x4{0.f, 0.f, 0.f, 0.f};
-      gemm32<LD>(acc, d1, w.F1at + oz, lane);
-      if (live) store_row32<LD>(aggbar + orow, acc);
-    }
-  }
-  // ---- block partials [4][LD]: the waves' column sums added in wave order
-#pragma unroll
-  for (int k = 0; k < 4; ++k) cs[k].put(red[k][wv], f0, i);
-  __syncthreads();
-  float* base = part.buf + (size_t)blockIdx.x * part.stride;
-  for (int idx = tid; idx < 4 * LD; idx += R32_NT) {
-    const int k = idx / LD, c = idx % LD;
-    float v = 0.f;
-#pragma unroll
-    for (int u = 0; u < R32_NW; ++u) v += red[k][u][c];
-    base[idx] = v;
-  }
-}
-
 
 // Sender-side sums and the node gradient through the edge MLP's sender and
 // receiver blocks: S_v = sum of zbar over the reverses of v's in-edges (the
@@ -543,72 +316,6 @@ __device__ __forceinline__ void node_enc_z1(const NodeEncVec<LD>& V, float4 xa, 
   }
 }
 
-template <int LD>
-struct __attribute__((aligned(16))) NodeEncFwdLds {
-  NodeEncVec<LD> V;
-  __attribute__((aligned(16))) float w2[LD * LD];  // fragment-major W2
-};
-
-// Forward (with EMIT the node products of the first MP block from the
-// first edge MLP nx, as the node phase does).
-template <int LD, bool EMIT>
-__global__ void __launch_bounds__(R32_NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_node_enc_r32(int64_t N, const float* __restrict__ x_in, MlpW w, MlpW nx, float eps, float* __restrict__ h_out,
-               float* __restrict__ P_out) {
-  typedef R32<LD> Z;
-  __shared__ __align__(16) NodeEncFwdLds<LD> S;
-  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int idx = tid; idx < LD * LD / 4; idx += R32_NT)
-    reinterpret_cast<f32x4*>(S.w2)[idx] = reinterpret_cast<const f32x4*>(w.F2)[idx];
-  stage_node_enc_vec<LD>(S.V, w, tid);
-  __syncthreads();
-  const int64_t nu = (N + 15) >> 4;
-  const UnitRange ur = unit_range<R32_NW>(nu, wv);
-  const int f0 = Z::KL * g;
-  for (int64_t u = ur.t; u < ur.end; u += ur.stride) {
-    const bool live = u * 16 + i < N;
-    const int64_t v = min(u * 16 + i, N - 1);
-    const float4 xa = *reinterpret_cast<const float4*>(x_in + v * NK);
-    const float4 xb = *reinterpret_cast<const float4*>(x_in + v * NK + 4);
-    // LDS reads through an opaque reference: otherwise the loop-invariant
-    // weight reads are hoisted out of the loop into registers
-    const NodeEncFwdLds<LD>& L = fresh(S);
-    float a1[Z::KL];
-    node_enc_z1<LD>(L.V, xa, xb, f0, a1);
-#pragma unroll
-    for (int s2 = 0; s2 < Z::KL; ++s2) a1[s2] = relu(a1[s2]);
-    f32x4 acc[Z::NOB];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = *reinterpret_cast<const f32x4*>(L.V.b2 + f0 + 4 * ob);
-    gemm32<LD>(acc, a1, L.w2, lane);
-    const float rstd = ln_center_r32<LD>(acc, f0, eps);
-    float y[Z::KL];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) {
-      const f32x4 m = *reinterpret_cast<const f32x4*>(L.V.g + f0 + 4 * ob) * (acc[ob] * rstd) +
-                      *reinterpret_cast<const f32x4*>(L.V.bt + f0 + 4 * ob);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) y[4 * ob + r] = m[r];
-      acc[ob] = m;
-    }
-    if (live) store_row32<LD>(h_out + (size_t)v * LD + f0, acc);
-    if (EMIT) {
-      const int oz = opaque_zero();
-      f32x4 ps[Z::NOB];
-#pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = ps[ob] = f32x4{0.f, 0.f, 0.f, 0.f};
-      gemm32<LD>(ps, y, nx.F1s + oz, lane);
-      gemm32<LD>(acc, y, nx.F1r + oz, lane);
-      if (live) {
-        float* p = P_out + (size_t)v * (2 * LD) + f0;
-        store_row32<LD>(p, ps);
-        store_row32<LD>(p + LD, acc);
-      }
-    }
-  }
-}
-
 // Reverse from ybar = dL/dh0: the forward recomputed (z1 bitwise), the
 // LayerNorm reverse, dz1 = (W2^T dz2) where z1 > 0, gin = W1^T dz1 (when gin
 // is given, [N][8]); the a1 and dz2 rows go to a1s / dz2s for dW2 (by
@@ -772,50 +479,6 @@ using namespace dev;
 
 static constexpr int kNodeRows32Blocks = 256;
 
-hipError_t launch_node_fwd_r32(int lat, int64_t N, const float* h_in, const float* agg, const MlpW& w,
-                               const MlpW* nx, float eps, float* h_out, float* P_out, hipStream_t s) {
-  if (N <= 0) return hipSuccess;
-  if ((lat != 128 && lat != 160) || !w.F1 || !w.F1a || !w.F2 || (nx && (!nx->F1s || !nx->F1r || !P_out)))
-    return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, kNodeRows32Blocks);
-  if (g >= 8) g &= ~7;
-  const MlpW nn = nx ? *nx : w;
-#define F(L)                                                                                                     \
-  if (nx)                                                                                                        \
-    hipLaunchKernelGGL((k_node_fwd_r32<L, true>), dim3(g), dim3(R32_NT), 0, s, N, h_in, agg, w, nn, eps, h_out, \
-                       P_out);                                                                                   \
-  else                                                                                                           \
-    hipLaunchKernelGGL((k_node_fwd_r32<L, false>), dim3(g), dim3(R32_NT), 0, s, N, h_in, agg, w, nn, eps, h_out, \
-                       P_out)
-  MGN_BY_WIDTH(lat, F);
-#undef F
-  return hipGetLastError();
-}
-
-hipError_t launch_node_bwd_r32(int lat, int64_t N, const float* h, const float* agg, const float* hbar_in,
-                               const MlpW& w, float eps, float* hbar_part, float* aggbar, float* streams,
-                               const Partials& part, int* nblocks, hipStream_t s) {
-  *nblocks = 0;
-  if (N <= 0) return hipSuccess;
-  if ((lat != 128 && lat != 160) || !w.F1 || !w.F1a || !w.F2 || !w.F1t || !w.F1at || !w.F2t ||
-      part.stride < 4LL * lat)
-    return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, std::min(kNodeRows32Blocks, part.max_blocks));
-  if (g >= 8) g &= ~7;
-  *nblocks = g;
-  float* a1s = streams;
-  float* dz2s = streams + (size_t)N * lat;
-  float* dz1s = streams + (size_t)2 * N * lat;
-#define F(L)                                                                                                    \
-  hipLaunchKernelGGL(k_node_bwd_r32<L>, dim3(g), dim3(R32_NT), 0, s, N, h, agg, hbar_in, w, eps, hbar_part,     \
-                     aggbar, a1s, dz2s, dz1s, part)
-  MGN_BY_WIDTH(lat, F);
-#undef F
-  return hipGetLastError();
-}
-
 hipError_t launch_node_srcsum_r32(int lat, int64_t N, const int32_t* rowptr, const int32_t* rev, const float* zbar,
                                   const float* R, const float* hbar_part, const MlpW& w, float* hbar_out,
                                   float* S_out, hipStream_t s) {
@@ -854,24 +517,6 @@ hipError_t launch_decoder_bwd_r32(int lat, int64_t N, const float* h, const floa
   if (g >= 8) g &= ~7;
   *nblocks = g;
 #define F(L) hipLaunchKernelGGL(k_decoder_bwd_r32<L>, dim3(g), dim3(R32_NT), 0, s, N, h, gout, w, hbar, dz1s, part)
-  MGN_BY_WIDTH(lat, F);
-#undef F
-  return hipGetLastError();
-}
-
-hipError_t launch_node_enc_r32(int lat, int64_t N, const float* x, const MlpW& w, const MlpW* nx, float eps,
-                               float* h_out, float* P_out, hipStream_t s) {
-  if (N <= 0) return hipSuccess;
-  if ((lat != 128 && lat != 160) || !w.F2 || (nx && (!nx->F1s || !nx->F1r || !P_out))) return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, kNodeRows32Blocks);
-  if (g >= 8) g &= ~7;
-  const MlpW nn = nx ? *nx : w;
-#define F(L)                                                                                                  \
-  if (nx)                                                                                                     \
-    hipLaunchKernelGGL((k_node_enc_r32<L, true>), dim3(g), dim3(R32_NT), 0, s, N, x, w, nn, eps, h_out, P_out); \
-  else                                                                                                        \
-    hipLaunchKernelGGL((k_node_enc_r32<L, false>), dim3(g), dim3(R32_NT), 0, s, N, x, w, nn, eps, h_out, P_out)
   MGN_BY_WIDTH(lat, F);
 #undef F
   return hipGetLastError();

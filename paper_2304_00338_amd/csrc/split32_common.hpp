@@ -72,15 +72,15 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// The two pieces of eight values scaled by the power of two s.
+// The two pieces of eight values scaled by 2^e.
 struct Pieces {
   f16x8 h, l;
 };
-__device__ __forceinline__ Pieces split8(const float* x, float s) {
+__device__ __forceinline__ Pieces split8(const float* x, int e) {
   Pieces p;
 #pragma unroll
   for (int t = 0; t < 8; t += 2) {
-    const float a = x[t] * s, b = x[t + 1] * s;
+    const float a = __builtin_amdgcn_ldexpf(x[t], e), b = __builtin_amdgcn_ldexpf(x[t + 1], e);
     const f16x2 h = __builtin_convertvector(f32x2{a, b}, f16x2);
     const f16x2 l = __builtin_convertvector(f32x2{a - (float)h[0], b - (float)h[1]}, f16x2);
     p.h[t] = h[0];
@@ -92,10 +92,8 @@ __device__ __forceinline__ Pieces split8(const float* x, float s) {
 }
 
 // Exponent e of the scale 2^e that brings a largest value m >= 0 into [2^14,
-// 2^15) (at most 2^126: smaller rows than 2^-112 keep what is left), and the
-// scale itself.
+// 2^15) (at most 2^126: smaller rows than 2^-112 keep what is left).
 __device__ __forceinline__ int scale_exp(float m) { return min(141 - (int)(__float_as_uint(m) >> 23), 126); }
-__device__ __forceinline__ float scale_of(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
 
 // Sum and maximum over the two lanes that hold a row.
 __device__ __forceinline__ float sum_hh(float s) {
@@ -153,18 +151,19 @@ struct RowPieces {
   int e;
 };
 
-// acc = W x.  get(ks) gives the pieces of the lane's values 8 ks .. 8 ks + 7,
-// scaled by 2^e.  W is the product's packed matrix, whose first chunk is in
-// buf[PAR]; next (the following product's, or any valid matrix) leaves its
-// first chunk in buf[(PAR + NC) % 2].  All NT threads of the block call it
+// acc (+)= 2^(e + W's exponent) W x, where get(ks) gives the pieces of the
+// lane's values 8 ks .. 8 ks + 7 scaled by 2^e; ADD keeps what acc holds.  W is the product's packed matrix, whose first chunk is in
+// buf[par & 1]; next (the following product's, or any valid matrix) leaves its
+// first chunk in buf[(par + NC) & 1].  All NT threads of the block call it
 // together.  mid(ks) runs after the products of K step ks (for loads that
 // the caller needs after the product).
-template <int LD, int PAR, int NT, class G, class F>
-__device__ __forceinline__ void gemm_pieces(f32x16 (&acc)[X3<LD>::NOB], G&& get, int e, const u32x4* W,
-                                            const u32x4* next, u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
+template <int LD, int NT, bool ADD, class G, class F>
+__device__ __forceinline__ void gemm_raw(f32x16 (&acc)[X3<LD>::NOB], G&& get, const u32x4* W, const u32x4* next,
+                                         u32x4 (*buf)[X3<LD>::CH], int par, int tid, F&& mid) {
   typedef X3<LD> Z;
   const int lane = tid & 63;
   const int ot = tid + opaque_zero();  // keeps the loads' addresses out of the callers' loops
+  if (!ADD)
 #pragma unroll
   for (int ob = 0; ob < Z::NOB; ++ob)
 #pragma unroll
@@ -179,7 +178,7 @@ __device__ __forceinline__ void gemm_pieces(f32x16 (&acc)[X3<LD>::NOB], G&& get,
       // apart (fragments of both at once do not fit in the registers)
       __builtin_amdgcn_sched_barrier(0);
       const Pieces b = get(2 * c + k);
-      const f16x8* A = reinterpret_cast<const f16x8*>(buf[(PAR + c) & 1]) + k * Z::NOB * 128 + lane;
+      const f16x8* A = reinterpret_cast<const f16x8*>(buf[(par + c) & 1]) + k * Z::NOB * 128 + lane;
       f16x8 a[Z::NOB];
 #pragma unroll
       for (int ob = 0; ob < Z::NOB; ++ob) a[ob] = A[(2 * ob + 1) * 64];
@@ -193,36 +192,46 @@ __device__ __forceinline__ void gemm_pieces(f32x16 (&acc)[X3<LD>::NOB], G&& get,
       for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ob], b.h, acc[ob], 0, 0, 0);
       mid(2 * c + k);
     }
-    ws.store(buf[(PAR + c + 1) & 1], tid);
+    ws.store(buf[(par + c + 1) & 1], tid);
     __syncthreads();
   }
-  const int k = -(e + weight_exp<LD>(W));
+}
+
+// acc *= 2^k
+template <int LD>
+__device__ __forceinline__ void scale_acc(f32x16 (&acc)[X3<LD>::NOB], int k) {
 #pragma unroll
-  for (int ob = 0; ob < Z::NOB; ++ob)
+  for (int ob = 0; ob < X3<LD>::NOB; ++ob)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[ob][r] = __builtin_amdgcn_ldexpf(acc[ob][r], k);
 }
 
-// acc = W x for the lane's KL values x, which are split as the product goes.
-template <int LD, int PAR, int NT = X3_NT, class F>
-__device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float* x, const u32x4* W, const u32x4* next,
-                                        u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
-  const int e = row_exp<LD>(x);
-  const float s = scale_of(e);
-  gemm_pieces<LD, PAR, NT>(acc, [&](int ks) { return split8(x + 8 * ks, s); }, e, W, next, buf, tid, mid);
+// acc = W x from the row's pieces.
+template <int LD, int NT, class G, class F>
+__device__ __forceinline__ void gemm_pieces(f32x16 (&acc)[X3<LD>::NOB], G&& get, int e, const u32x4* W,
+                                            const u32x4* next, u32x4 (*buf)[X3<LD>::CH], int par, int tid, F&& mid) {
+  gemm_raw<LD, NT, false>(acc, get, W, next, buf, par, tid, mid);
+  scale_acc<LD>(acc, -(e + weight_exp<LD>(W)));
 }
-template <int LD, int PAR, int NT = X3_NT>
+
+// acc = W x for the lane's KL values x, which are split as the product goes.
+template <int LD, int NT = X3_NT, class F>
 __device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float* x, const u32x4* W, const u32x4* next,
-                                        u32x4 (*buf)[X3<LD>::CH], int tid) {
-  gemm_x3<LD, PAR, NT>(acc, x, W, next, buf, tid, [](int) {});
+                                        u32x4 (*buf)[X3<LD>::CH], int par, int tid, F&& mid) {
+  const int e = row_exp<LD>(x);
+  gemm_pieces<LD, NT>(acc, [&](int ks) { return split8(x + 8 * ks, e); }, e, W, next, buf, par, tid, mid);
+}
+template <int LD, int NT = X3_NT>
+__device__ __forceinline__ void gemm_x3(f32x16 (&acc)[X3<LD>::NOB], const float* x, const u32x4* W, const u32x4* next,
+                                        u32x4 (*buf)[X3<LD>::CH], int par, int tid) {
+  gemm_x3<LD, NT>(acc, x, W, next, buf, par, tid, [](int) {});
 }
 // The same, keeping the pieces in row.
-template <int LD, int PAR, int NT, class F>
+template <int LD, int NT, class F>
 __device__ __forceinline__ void gemm_keep(f32x16 (&acc)[X3<LD>::NOB], const float* x, RowPieces<LD>& row, const u32x4* W,
-                                          const u32x4* next, u32x4 (*buf)[X3<LD>::CH], int tid, F&& mid) {
+                                          const u32x4* next, u32x4 (*buf)[X3<LD>::CH], int par, int tid, F&& mid) {
   row.e = row_exp<LD>(x);
-  const float s = scale_of(row.e);
-  gemm_pieces<LD, PAR, NT>(acc, [&](int ks) { return row.p[ks] = split8(x + 8 * ks, s); }, row.e, W, next, buf, tid, mid);
+  gemm_pieces<LD, NT>(acc, [&](int ks) { return row.p[ks] = split8(x + 8 * ks, row.e); }, row.e, W, next, buf, par, tid, mid);
 }
 
 // The first chunk of the first product into buf[0] (a barrier must follow).
@@ -358,6 +367,14 @@ __device__ __forceinline__ void zero_empty(int4 d, const int32_t* __restrict__ r
     float* q = dst + (size_t)(d.x + j) * LD;
     for (int f = lane; f < LD; f += 64) q[f] = 0.f;
   }
+}
+
+// Stores the lane's KL values of a row; p points at feature 8 hh of it.
+template <int LD, class F>
+__device__ __forceinline__ void store_row_x3(float* p, F&& get) {
+#pragma unroll
+  for (int c = 0; c < X3<LD>::KL / 4; ++c)
+    *reinterpret_cast<f32x4*>(p + X3<LD>::pf(c)) = f32x4{get(4 * c), get(4 * c + 1), get(4 * c + 2), get(4 * c + 3)};
 }
 
 // Column sums over the 32 rows of a block of the lanes' KL values, added up
@@ -534,10 +551,22 @@ struct DwAcc {
 template <int LD>
 __device__ __forceinline__ void split_row(RowPieces<LD>& r, const float* x, bool live) {
   r.e = row_exp<LD>(x);
-  const float s = live ? scale_of(r.e) : 0.f;
+  const int e = live ? r.e : -10000;
 #pragma unroll
-  for (int k = 0; k < X3<LD>::KS; ++k) r.p[k] = split8(x + 8 * k, s);
+  for (int k = 0; k < X3<LD>::KS; ++k) r.p[k] = split8(x + 8 * k, e);
 }
 
 }  // namespace dev
+
+// Blocks for n units of one wave each: as many as the fullest XCD needs (the
+// units are dealt to the XCDs in eighths, see block_range), at most `most`.
+// Rounding n / nw down to a multiple of 8 instead left a few units for a second
+// round, which doubled the time of inputs of about one round (184 tiles: edge
+// forward 26 -> 16 us, reverse 113 -> 66 us; 17,800 nodes: node forward 49 -> 30
+// us).
+inline int split_blocks(int64_t n, int nw, int most) {
+  const int64_t g = 8 * (((n + 7) / 8 + nw - 1) / nw);
+  return (int)std::min<int64_t>(g, most & ~7);
+}
+
 }  // namespace mgn
