@@ -70,24 +70,15 @@ k_edge_fwd_rows(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
   __shared__ __align__(16) RowsLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  {
-    stage_weights<D>(S.W1, (const bf16*)w.W1p, tid);
-    stage_weights<D>(S.W2, (const bf16*)w.W2p, tid);
-    if (tid < D) {
-      S.b1[tid] = w.b1[tid];
-      S.b2[tid] = w.b2[tid];
-      S.g[tid] = w.gamma[tid];
-      S.bt[tid] = w.beta[tid];
-    }
-  }
-  __syncthreads();
+  WeightStage<D> w1, w2;
+  w1.load(w.W1p, tid);
+  w2.load(w.W2p, tid);
 
   // XCD-contiguous tile ranges: the node products gathered by one XCD's
   // waves then mostly share that XCD's L2.
   const UnitRange ur = unit_range(tl.n_tiles, wv);
   int64_t t = ur.t;
   const int64_t stride = ur.stride, tend = ur.end;
-  if (t >= tend) return;
 
   const bf16x8 sel0 = select_frag(0, i, q), sel1 = select_frag(1, i, q);
   auto desc = [&](int64_t tt) -> int4 {
@@ -235,6 +226,15 @@ k_edge_fwd_rows(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
   load_sr(d0, sc, rc);
   HalfF A, B;
   issue_half(d0, 0, sc[0], rc[0], A);
+  w1.store(S.W1, tid);
+  w2.store(S.W2, tid);
+  if (tid < D) {
+    S.b1[tid] = w.b1[tid];
+    S.b2[tid] = w.b2[tid];
+    S.g[tid] = w.gamma[tid];
+    S.bt[tid] = w.beta[tid];
+  }
+  __syncthreads();
   for (; t < tend; t += stride) {
     const bool chunk = d0.y < 0;
     const int nv = chunk ? 1 : d0.y - d0.x;
@@ -346,8 +346,11 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   {
-    stage_weights<D>(S.W1, (const bf16*)w.W1p, tid);
-    stage_weights<D>(S.W2, (const bf16*)w.W2p, tid);
+    WeightStage<D> w1, w2;
+    w1.load(w.W1p, tid);
+    w2.load(w.W2p, tid);
+    w1.store(S.W1, tid);
+    w2.store(S.W2, tid);
     if (tid < D) {
       S.b2[tid] = w.b2[tid];
       S.g[tid] = w.gamma[tid];
@@ -729,10 +732,7 @@ using namespace dev;
 static constexpr int kRowsBlocks = 256;
 
 static int rows_grid(int64_t n_tiles, int max_blocks) {
-  const int64_t need = (n_tiles + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, max_blocks);
-  if (g >= 8) g &= ~7;
-  return g;
+  return unit_blocks(n_tiles, NW, max_blocks);
 }
 
 hipError_t launch_edge_fwd_rows(const EdgeTiles& t, const void* e_in, void* e_out, int write_e, const void* Pn,
@@ -755,9 +755,7 @@ hipError_t launch_edge_bwd_fused(const EdgeTiles& t, const void* a1, const void*
   *nblocks = 0;
   if (t.n_tiles <= 0) return hipSuccess;
   if (t.n_edges <= 0 || part.stride < 33280) return hipErrorInvalidValue;
-  const int64_t need = (t.n_tiles + FB_RW - 1) / FB_RW;
-  int g = (int)std::min<int64_t>(need, std::min(kFusedBlocks, part.max_blocks));
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks(t.n_tiles, FB_RW, std::min(kFusedBlocks, part.max_blocks));
   *nblocks = g;
   if (have_ebar)
     hipLaunchKernelGGL(k_edge_bwd_fused<true>, dim3(g), dim3(FB_NT), 0, s, t, (const bf16*)a1, (const bf16*)e,

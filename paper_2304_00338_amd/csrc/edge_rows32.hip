@@ -398,9 +398,7 @@ hipError_t launch_edge_enc_r32(int lat, int64_t E, const float* f, const MlpW& w
                                hipStream_t s) {
   if (E <= 0) return hipSuccess;
   if (!w.F2) return hipErrorInvalidValue;
-  const int64_t need = ((E + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, kRows32Blocks);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((E + 15) / 16, R32_NW, kRows32Blocks);
 #define F(LD) \
   hipLaunchKernelGGL(k_edge_enc_r32<LD>, dim3(g), dim3(R32_NT), 0, s, E, f, w, eps, (float*)e_out)
   MGN_BY_WIDTH(lat, F);
@@ -413,9 +411,7 @@ hipError_t launch_edge_enc_bwd_r32(int lat, int64_t E, const float* f, const voi
   *nblocks = 0;
   if (E <= 0) return hipSuccess;
   if (!w.F2 || !w.F2t || part.stride < (int64_t)lat * lat + (EK + 4) * lat) return hipErrorInvalidValue;
-  const int64_t need = ((E + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, std::min(kRows32Blocks, part.max_blocks));
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((E + 15) / 16, R32_NW, std::min(kRows32Blocks, part.max_blocks));
   *nblocks = g;
 #define F(LD)                                                                                                 \
   hipLaunchKernelGGL(k_edge_enc_bwd_r32<LD>, dim3(g), dim3(R32_NT), 0, s, E, f, (const float*)ebar, w, eps, \

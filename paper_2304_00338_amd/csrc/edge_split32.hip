@@ -418,7 +418,7 @@ hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& t, const void* e_in, voi
                               const MlpW& w, float eps, float* agg, float* slots, hipStream_t s) {
   if (t.n_tiles <= 0) return hipSuccess;
   if (t.n_edges <= 0 || !w.S1 || !w.S2) return hipErrorInvalidValue;
-  const int g = split_blocks(t.n_tiles, X3_NW, kSplitBlocks);
+  const int g = unit_blocks(t.n_tiles, X3_NW, kSplitBlocks);
 #define F(LD)                                                                                                     \
   hipLaunchKernelGGL(k_edge_fwd_x3<LD>, dim3(g), dim3(X3_NT), 0, s, t, (const float*)e_in, (float*)e_out, write_e, \
                      (const float*)Pn, w, eps, agg, slots)
@@ -438,7 +438,7 @@ hipError_t launch_edge_bwd_x3(int lat, const EdgeTiles& t, const void* e, const 
   if (t.n_edges <= 0 || part.stride < 2LL * lat * lat + 4 * lat || !w.S1 || !w.S2 || !w.S1t || !w.S2t)
     return hipErrorInvalidValue;
   const int nw = lat == 128 ? EdgeBwd<128>::NW : EdgeBwd<160>::NW;
-  const int g = split_blocks(t.n_tiles, nw, std::min(kSplitPartBlocks, part.max_blocks));
+  const int g = unit_blocks(t.n_tiles, nw, std::min(kSplitPartBlocks, part.max_blocks));
   *nblocks = g;
 #define F(LD)                                                                                                  \
   hipLaunchKernelGGL(k_edge_bwd_x3<LD>, dim3(g), dim3(EdgeBwd<LD>::NT), 0, s, t, (const float*)e, ebar_in, have_ebar,    \

@@ -42,8 +42,11 @@ k_edge_bwd_w160(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* ebar_i
   __shared__ __align__(16) Lds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_rot(S.W1, W1p, tid);
-  stage_rot(S.W2, W2p, tid);
+  Stage160 s1, s2;
+  s1.load(W1p, tid);
+  s2.load(W2p, tid);
+  s1.store_rot(S.W1, tid);
+  s2.store_rot(S.W2, tid);
   if (tid < L) {
     S.b2[tid] = b2[tid];
     S.g[tid] = gamma[tid];
@@ -379,8 +382,11 @@ k_edge_fwd_w160(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
   __shared__ __align__(16) FwdLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_w(S.W1, W1p, tid);
-  stage_w(S.W2, W2p, tid);
+  Stage160 s1, s2;
+  s1.load(W1p, tid);
+  s2.load(W2p, tid);
+  s1.store_pad(S.W1, tid);
+  s2.store_pad(S.W2, tid);
   if (tid < L) {
     S.b1[tid] = b1[tid];
     S.b2[tid] = b2[tid];
@@ -632,9 +638,7 @@ hipError_t launch_edge_bwd_w160(const EdgeTiles& t, const void* a1, const void* 
   *nblocks = 0;
   if (t.n_tiles <= 0) return hipSuccess;
   if (!w.W1p || !w.W2p || part.stride < 4 * 160) return hipErrorInvalidValue;
-  const int64_t need = (t.n_tiles + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, std::min(256, part.max_blocks));
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks(t.n_tiles, NW, std::min(256, part.max_blocks));
   *nblocks = g;
   hipLaunchKernelGGL(k_edge_bwd_w160, dim3(g), dim3(NT), 0, s, t, (const bf16*)a1, (const bf16*)ebar_in, have_ebar,
                      (bf16*)ebar_out, aggbar, (const bf16*)w.W1p, (const bf16*)w.W2p, w.b2,
@@ -658,9 +662,7 @@ hipError_t launch_edge_fwd_w160(const EdgeTiles& t, const void* e_in, void* e_ou
                                 const MlpW& w, float eps, float* agg, float* slots, void* a1_out, hipStream_t s) {
   if (t.n_tiles <= 0) return hipSuccess;
   if (!w.W1p || !w.W2p) return hipErrorInvalidValue;
-  const int64_t need = (t.n_tiles + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, 512);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks(t.n_tiles, NW, 512);
   hipLaunchKernelGGL(k_edge_fwd_w160, dim3(g), dim3(NT), 0, s, t, (const bf16*)e_in, (bf16*)e_out, write_e,
                      (const bf16*)Pn, (const bf16*)w.W1p, (const bf16*)w.W2p, w.b1, w.b2, w.gamma, w.beta, eps, agg,
                      slots, (bf16*)a1_out);

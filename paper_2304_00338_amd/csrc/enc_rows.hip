@@ -35,7 +35,9 @@ struct __attribute__((aligned(16))) EncLds {
 };
 
 __device__ __forceinline__ void stage_enc(EncLds& S, const MlpW& w, int tid) {
-  stage_weights<D>(S.W2, (const bf16*)w.W2p, tid);
+  WeightStage<D> w2;
+  w2.load(w.W2p, tid);
+  w2.store(S.W2, tid);
   if (tid < D) {
     S.W1[tid] = float4{w.W1f[tid * KE], w.W1f[tid * KE + 1], w.W1f[tid * KE + 2], w.W1f[tid * KE + 3]};
     S.b1[tid] = w.b1[tid];
@@ -317,9 +319,7 @@ static constexpr int kEncBlocks = 256;
 
 hipError_t launch_edge_enc_rows(int64_t E, const float* efeat, const MlpW& w, float eps, void* e_out, hipStream_t s) {
   if (E <= 0) return hipSuccess;
-  const int64_t need = (((E + 15) >> 4) + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, kEncBlocks);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((E + 15) >> 4, NW, kEncBlocks);
   hipLaunchKernelGGL(k_edge_enc_rows, dim3(g), dim3(NT), 0, s, E, efeat, w, eps, (bf16*)e_out);
   return hipGetLastError();
 }

@@ -44,7 +44,9 @@ struct __attribute__((aligned(16))) EncLds {
 };
 
 __device__ __forceinline__ void stage_enc(EncLds& S, const MlpW& w, int tid) {
-  stage_rot(S.W2, (const bf16*)w.W2p, tid);
+  Stage160 w2;
+  w2.load(w.W2p, tid);
+  w2.store_rot(S.W2, tid);
   if (tid < L) {
     S.W1[tid] = float4{w.W1f[tid * KE], w.W1f[tid * KE + 1], w.W1f[tid * KE + 2], w.W1f[tid * KE + 3]};
     S.b1[tid] = w.b1[tid];
@@ -464,7 +466,9 @@ k_node_enc_bwd_w160(int64_t N, const float* __restrict__ x_in, const float* __re
   __shared__ __align__(16) NodeEncLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_rot(S.W2, (const bf16*)w.W2p, tid);
+  Stage160 w2;
+  w2.load(w.W2p, tid);
+  w2.store_rot(S.W2, tid);
   if (tid < L) {
     const float* wr = w.W1f + tid * KN;
     S.W1[0][tid] = float4{wr[0], wr[1], wr[2], wr[3]};
@@ -782,9 +786,7 @@ static constexpr int kEncBlocks160 = 256;
 hipError_t launch_edge_enc_w160(int64_t E, const float* efeat, const MlpW& w, float eps, void* e_out, hipStream_t s) {
   if (E <= 0) return hipSuccess;
   if (!w.W2p) return hipErrorInvalidValue;
-  const int64_t need = (((E + 15) >> 4) + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, kEncBlocks160);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((E + 15) >> 4, NW, kEncBlocks160);
   hipLaunchKernelGGL(k_edge_enc_w160, dim3(g), dim3(NT), 0, s, E, efeat, w, eps, (bf16*)e_out);
   return hipGetLastError();
 }

@@ -95,6 +95,19 @@ int grid_for(int64_t n_tiles, int max_blocks);
 // no more partial copies than the work needs.
 int part_grid(int64_t n_tiles, int max_blocks);
 
+// Blocks of nw waves for n units of one wave each: as many as the fullest XCD
+// needs (from 8 blocks on the units are dealt to the XCDs in eighths, see
+// unit_range), at most `most`.  Rounding the blocks down to a multiple of 8
+// instead left a few units for a second round, which doubled the time of
+// inputs of about one round (184 tiles: fp32 edge forward 26 -> 16 us, reverse
+// 113 -> 66 us; 17,800 nodes: fp32 node forward 49 -> 30 us).
+inline int unit_blocks(int64_t n, int nw, int most) {
+  const int64_t need = (n + nw - 1) / nw;
+  if (need < 8) return (int)need;
+  const int64_t g = 8 * (((n + 7) / 8 + nw - 1) / nw);
+  return (int)(g < most ? g : most & ~7);
+}
+
 hipError_t launch_pack(int prec, const float* params, void* pack, const PackList& L, hipStream_t s);
 // Entries of mode 4 / 5 (n^2 + 1 floats at dst: the fragments, then the scale's exponent).
 hipError_t launch_pack_split(const float* params, void* pack, const PackList& L, hipStream_t s);

@@ -31,18 +31,26 @@ struct __attribute__((aligned(16))) NodeLds {
   __attribute__((aligned(16))) float bt[D];
 };
 
-__device__ __forceinline__ void stage_node_mlp(NodeLds& S, const MlpW& w, int tid, bool beta) {
-  stage_weights<D2>(S.W1, (const bf16*)w.W1p, tid);
-  stage_weights<D>(S.W2, (const bf16*)w.W2p, tid);
-  if (tid < D) {
-    S.b1[tid] = w.b1[tid];
-    S.b2[tid] = w.b2[tid];
-    S.g[tid] = w.gamma[tid];
-    S.bt[tid] = beta ? w.beta[tid] : 0.f;
-  }
-}
-
 __device__ __forceinline__ f32x4 lds4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
+struct NodeStage {
+  WeightStage<D2> w1;
+  WeightStage<D> w2;
+  __device__ __forceinline__ void load(const MlpW& w, int tid) {
+    w1.load(w.W1p, tid);
+    w2.load(w.W2p, tid);
+  }
+  __device__ __forceinline__ void store(NodeLds& S, const MlpW& w, int tid, bool beta) const {
+    w1.store(S.W1, tid);
+    w2.store(S.W2, tid);
+    if (tid < D) {
+      S.b1[tid] = w.b1[tid];
+      S.b2[tid] = w.b2[tid];
+      S.g[tid] = w.gamma[tid];
+      S.bt[tid] = beta ? w.beta[tid] : 0.f;
+    }
+  }
+};
 
 // Row addressing: a unit's 16 rows are contiguous, so every access is a
 // wave-uniform base (unit u's first row, kept in scalar registers) plus the
@@ -107,13 +115,12 @@ k_node_fwd_rows(int64_t N, const float* h_in, const float* __restrict__ agg, Mlp
   __shared__ NodeLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_node_mlp(S, w, tid, true);
+  NodeStage st;
+  st.load(w, tid);
   const AOff<D2> A1(i, q);
   const AOff<D> A2(i, q);
-  __syncthreads();
   const Rows rw{N, (N + 15) >> 4, i, q};
   const UnitRange ur = unit_range(rw.nu, wv);
-  if (ur.t >= ur.end) return;
   struct In {
     f32x4 h[8], a[8];
   };
@@ -150,6 +157,9 @@ k_node_fwd_rows(int64_t N, const float* h_in, const float* __restrict__ agg, Mlp
   In A, B;
   int64_t u = ur.t;
   load(u, A);
+  st.store(S, w, tid, true);
+  __syncthreads();
+  if (u >= ur.end) return;
   for (;;) {
     load(u + ur.stride, B);
     unit(A, u);
@@ -173,13 +183,12 @@ k_emit_rows(int64_t N, const float* __restrict__ h, MlpW nx, bf16* __restrict__ 
   __shared__ EmitLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_weights<D>(S.Ws, (const bf16*)nx.W1sp, tid);
-  stage_weights<D>(S.Wr, (const bf16*)nx.W1rp, tid);
+  WeightStage<D> ws, wr;
+  ws.load(nx.W1sp, tid);
+  wr.load(nx.W1rp, tid);
   const AOff<D> AW(i, q);
-  __syncthreads();
   const Rows rw{N, (N + 15) >> 4, i, q};
   const UnitRange ur = unit_range(rw.nu, wv);
-  if (ur.t >= ur.end) return;
   struct In {
     f32x4 h[8];
   };
@@ -213,6 +222,10 @@ k_emit_rows(int64_t N, const float* __restrict__ h, MlpW nx, bf16* __restrict__ 
   In A, B;
   int64_t u = ur.t;
   load(u, A);
+  ws.store(S.Ws, tid);
+  wr.store(S.Wr, tid);
+  __syncthreads();
+  if (u >= ur.end) return;
   for (;;) {
     load(u + ur.stride, B);
     unit(A, u);
@@ -238,10 +251,10 @@ k_node_bwd_rows(int64_t N, const float* __restrict__ h, const float* __restrict_
   __shared__ NodeLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_node_mlp(S, w, tid, false);
+  NodeStage st;
+  st.load(w, tid);
   const AOff<D2> A1(i, q);
   const AOff<D> A2(i, q);
-  __syncthreads();
   const Rows rw{N, (N + 15) >> 4, i, q};
   const UnitRange ur = unit_range(rw.nu, wv);
   float2 dga = {0.f, 0.f}, dbe = {0.f, 0.f};
@@ -357,10 +370,12 @@ k_node_bwd_rows(int64_t N, const float* __restrict__ h, const float* __restrict_
                                                           0);
     if (ok) store_row(aggbar + b, lo, acc);
   };
-  if (ur.t < ur.end) {
-    In A, B;
-    int64_t u = ur.t;
-    load(u, A);
+  In A, B;
+  int64_t u = ur.t;
+  load(u, A);
+  st.store(S, w, tid, false);
+  __syncthreads();
+  if (u < ur.end) {
     for (;;) {
       unit(A, B, u, u + ur.stride);
       u += ur.stride;
@@ -507,11 +522,7 @@ using namespace dev;
 static constexpr int kNodeBlocks = 256;
 
 static int node_grid(int64_t N, int max_blocks) {
-  const int64_t units = (N + 15) >> 4;
-  const int64_t need = (units + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, max_blocks);
-  if (g >= 8) g &= ~7;
-  return g;
+  return unit_blocks((N + 15) >> 4, NW, max_blocks);
 }
 
 hipError_t launch_node_fwd_rows(int64_t N, const float* h_in, const float* agg, const MlpW& w, float eps,

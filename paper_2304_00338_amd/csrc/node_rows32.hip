@@ -484,9 +484,7 @@ hipError_t launch_node_srcsum_r32(int lat, int64_t N, const int32_t* rowptr, con
                                   float* S_out, hipStream_t s) {
   if (N <= 0) return hipSuccess;
   if ((lat != 128 && lat != 160) || !w.F1st || !w.F1rt) return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, kNodeRows32Blocks);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) / 16, R32_NW, kNodeRows32Blocks);
 #define F(L)                                                                                                    \
   hipLaunchKernelGGL(k_node_srcsum_r32<L>, dim3(g), dim3(R32_NT), 0, s, N, rowptr, rev, zbar, R, hbar_part, w, \
                      hbar_out, S_out)
@@ -498,9 +496,7 @@ hipError_t launch_node_srcsum_r32(int lat, int64_t N, const int32_t* rowptr, con
 hipError_t launch_decoder_r32(int lat, int64_t N, const float* h, const MlpW& w, float* out, hipStream_t s) {
   if (N <= 0) return hipSuccess;
   if ((lat != 128 && lat != 160) || !w.F1) return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, kNodeRows32Blocks);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) / 16, R32_NW, kNodeRows32Blocks);
 #define F(L) hipLaunchKernelGGL(k_decoder_r32<L>, dim3(g), dim3(R32_NT), 0, s, N, h, w, out)
   MGN_BY_WIDTH(lat, F);
 #undef F
@@ -512,9 +508,7 @@ hipError_t launch_decoder_bwd_r32(int lat, int64_t N, const float* h, const floa
   *nblocks = 0;
   if (N <= 0) return hipSuccess;
   if ((lat != 128 && lat != 160) || !w.F1 || !w.F1t || part.stride < 5LL * lat + 4) return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, std::min(kNodeRows32Blocks, part.max_blocks));
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) / 16, R32_NW, std::min(kNodeRows32Blocks, part.max_blocks));
   *nblocks = g;
 #define F(L) hipLaunchKernelGGL(k_decoder_bwd_r32<L>, dim3(g), dim3(R32_NT), 0, s, N, h, gout, w, hbar, dz1s, part)
   MGN_BY_WIDTH(lat, F);
@@ -528,9 +522,7 @@ hipError_t launch_node_enc_bwd_r32(int lat, int64_t N, const float* x, const flo
   if (N <= 0) return hipSuccess;
   if ((lat != 128 && lat != 160) || !w.F2 || !w.F2t || part.stride < (int64_t)(NK + 4) * lat)
     return hipErrorInvalidValue;
-  const int64_t need = ((N + 15) / 16 + R32_NW - 1) / R32_NW;
-  int g = (int)std::min<int64_t>(need, std::min(kNodeRows32Blocks, part.max_blocks));
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) / 16, R32_NW, std::min(kNodeRows32Blocks, part.max_blocks));
   *nblocks = g;
   float* a1s = streams;
   float* dz2s = streams + (size_t)N * lat;

@@ -322,7 +322,7 @@ using namespace dev;
 // two blocks per CU
 static constexpr int kNodeSplitBlocks = 512;
 static int node_blocks(int64_t N, int most) {
-  return split_blocks((N + 31) / 32, X3_NW, std::min(kNodeSplitBlocks, most));
+  return unit_blocks((N + 31) / 32, X3_NW, std::min(kNodeSplitBlocks, most));
 }
 
 hipError_t launch_node_fwd_x3(int lat, int64_t N, const float* h_in, const float* agg, const MlpW& w, const MlpW* nx,

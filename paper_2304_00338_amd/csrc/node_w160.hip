@@ -42,9 +42,13 @@ struct __attribute__((aligned(16))) NodeLds {
 };
 
 __device__ __forceinline__ void stage_node(NodeLds& S, const MlpW& w, int tid, bool beta) {
-  stage_rot(S.W1h, (const bf16*)w.W1p, tid);
-  stage_rot(S.W1a, (const bf16*)w.W1ap, tid);
-  stage_rot(S.W2, (const bf16*)w.W2p, tid);
+  Stage160 s1, s2, s3;
+  s1.load(w.W1p, tid);
+  s2.load(w.W1ap, tid);
+  s3.load(w.W2p, tid);
+  s1.store_rot(S.W1h, tid);
+  s2.store_rot(S.W1a, tid);
+  s3.store_rot(S.W2, tid);
   if (tid < L) {
     S.b1[tid] = w.b1[tid];
     S.b2[tid] = w.b2[tid];
@@ -539,8 +543,11 @@ k_emit_w160(int64_t N, const float* __restrict__ h, MlpW nx, bf16* __restrict__ 
   __shared__ __align__(16) EmitLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_rot(S.Ws, (const bf16*)nx.W1sp, tid);
-  stage_rot(S.Wr, (const bf16*)nx.W1rp, tid);
+  Stage160 s1, s2;
+  s1.load((const bf16*)nx.W1sp, tid);
+  s2.load((const bf16*)nx.W1rp, tid);
+  s1.store_rot(S.Ws, tid);
+  s2.store_rot(S.Wr, tid);
   __syncthreads();
   const int64_t nu = (N + 15) >> 4;
   const UnitRange ur = unit_range(nu, wv);
@@ -592,8 +599,11 @@ k_srcsum_w160(int64_t N, const int32_t* __restrict__ rowptr, const int32_t* __re
   __shared__ __align__(16) EmitLds S;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  stage_rot(S.Ws, (const bf16*)w.W1sp, tid);
-  stage_rot(S.Wr, (const bf16*)w.W1rp, tid);
+  Stage160 s1, s2;
+  s1.load((const bf16*)w.W1sp, tid);
+  s2.load((const bf16*)w.W1rp, tid);
+  s1.store_rot(S.Ws, tid);
+  s2.store_rot(S.Wr, tid);
   __syncthreads();
   const int64_t nu = (N + 15) >> 4;
   const UnitRange ur = unit_range(nu, wv);
@@ -661,9 +671,7 @@ hipError_t launch_node_bwd_w160(int64_t N, const float* h, const float* agg, con
   *nblocks = 0;
   if (N <= 0) return hipSuccess;
   if (!w.W1p || !w.W1ap || !w.W2p || part.stride < 3 * 160 * 160 + 4 * 160) return hipErrorInvalidValue;
-  const int64_t need = (((N + 15) >> 4) + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, std::min(kNodeBlocks160, part.max_blocks));
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) >> 4, NW, std::min(kNodeBlocks160, part.max_blocks));
   *nblocks = g;
   hipLaunchKernelGGL(k_node_bwd_w160, dim3(g), dim3(NT), 0, s, N, h, agg, hbar_in, w, eps, hbar_part, aggbar,
                      (bf16*)a1, (bf16*)dz2, (bf16*)dz1, part);
@@ -688,9 +696,7 @@ hipError_t launch_node_fwd_w160(int64_t N, const float* h_in, const float* agg, 
                                 float* h_out, hipStream_t s) {
   if (N <= 0) return hipSuccess;
   if (!w.W1p || !w.W1ap || !w.W2p) return hipErrorInvalidValue;
-  const int64_t need = (((N + 15) >> 4) + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, kNodeBlocks160);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) >> 4, NW, kNodeBlocks160);
   hipLaunchKernelGGL(k_node_fwd_w160, dim3(g), dim3(NT), 0, s, N, h_in, agg, w, eps, h_out);
   return hipGetLastError();
 }
@@ -698,9 +704,7 @@ hipError_t launch_node_fwd_w160(int64_t N, const float* h_in, const float* agg, 
 hipError_t launch_emit_w160(int64_t N, const float* h, const MlpW& next_edge, void* P, hipStream_t s) {
   if (N <= 0) return hipSuccess;
   if (!next_edge.W1sp || !next_edge.W1rp) return hipErrorInvalidValue;
-  const int64_t need = (((N + 15) >> 4) + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, kNodeBlocks160);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) >> 4, NW, kNodeBlocks160);
   hipLaunchKernelGGL(k_emit_w160, dim3(g), dim3(NT), 0, s, N, h, next_edge, (bf16*)P);
   return hipGetLastError();
 }
@@ -711,9 +715,7 @@ hipError_t launch_srcsum_w160(int64_t N, const int32_t* rowptr, const int32_t* r
   *nblocks = 0;
   if (N <= 0) return hipSuccess;
   if (!w.W1sp || !w.W1rp || part.stride < 2 * 160 * 160) return hipErrorInvalidValue;
-  const int64_t need = (((N + 15) >> 4) + NW - 1) / NW;
-  int g = (int)std::min<int64_t>(need, kNodeBlocks160);
-  if (g >= 8) g &= ~7;
+  const int g = unit_blocks((N + 15) >> 4, NW, kNodeBlocks160);
   hipLaunchKernelGGL(k_srcsum_w160, dim3(g), dim3(NT), 0, s, N, rowptr, rev, (const bf16*)zbar, R, hbar_part, w,
                      hbar_out, (bf16*)S_buf);
   const int gw = grid_for((N + TM - 1) / TM, std::min(512, part.max_blocks));

@@ -38,16 +38,31 @@ __device__ __forceinline__ bf16* wchunk_w(bf16* W, int R, int C) {
   return W + R * LD + ((C ^ wswz(R)) << 3);
 }
 
-// Stage the row-permuted [D][LD] bf16 matrix src into LDS in the swizzled
-// layout (all threads of the block take part; a barrier must follow).
-template <int LD>
-__device__ __forceinline__ void stage_weights(bf16* dst, const bf16* src, int tid) {
-  constexpr int CPR = LD / 8;  // 16-byte chunks per row
-  for (int idx = tid; idx < D * CPR; idx += NT) {
-    const int row = idx / CPR, c = idx % CPR;
-    *reinterpret_cast<uint4*>(wchunk_w<LD>(dst, row, c)) = *reinterpret_cast<const uint4*>(src + row * LD + c * 8);
+// Staging of the row-permuted [D][LD] bf16 matrix src into LDS in the
+// swizzled layout (all threads of the block take part; a barrier must
+// follow).  A kernel loads all of its matrices, and its first unit's inputs,
+// before it stores any: written as a copy loop, every 8 KB waited for the
+// 8 KB before them, and that chain of latencies was up to half of a launch
+// on a small input (11,260 edges: edge forward 21 -> 13.5 us; 1,935 nodes: node
+// forward 14 -> 12 us, node products 9 -> 7.6 us).
+template <int LD = D>
+struct WeightStage {
+  static constexpr int CPR = LD / 8;  // 16-byte chunks per row
+  static constexpr int N = D * CPR / NT;
+  static_assert(D * CPR % NT == 0, "");
+  uint4 r[N];
+  __device__ __forceinline__ void load(const void* src, int tid) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] = reinterpret_cast<const uint4*>(src)[tid + NT * j];
   }
-}
+  __device__ __forceinline__ void store(bf16* dst, int tid) const {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int idx = tid + NT * j;
+      *reinterpret_cast<uint4*>(wchunk_w<LD>(dst, idx / CPR, idx % CPR)) = r[j];
+    }
+  }
+};
 
 // The 0/1 operand that adds a B fragment (run s: features 32s + 8q + j) into
 // the C fragment of output block ob = 2s + h: A[m][k] = 1 iff k = (m/4)*8 +

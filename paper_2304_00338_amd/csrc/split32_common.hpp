@@ -558,15 +558,4 @@ __device__ __forceinline__ void split_row(RowPieces<LD>& r, const float* x, bool
 
 }  // namespace dev
 
-// Blocks for n units of one wave each: as many as the fullest XCD needs (the
-// units are dealt to the XCDs in eighths, see block_range), at most `most`.
-// Rounding n / nw down to a multiple of 8 instead left a few units for a second
-// round, which doubled the time of inputs of about one round (184 tiles: edge
-// forward 26 -> 16 us, reverse 113 -> 66 us; 17,800 nodes: node forward 49 -> 30
-// us).
-inline int split_blocks(int64_t n, int nw, int most) {
-  const int64_t g = 8 * (((n + 7) / 8 + nw - 1) / nw);
-  return (int)std::min<int64_t>(g, most & ~7);
-}
-
 }  // namespace mgn

@@ -41,13 +41,31 @@ __device__ __forceinline__ int rot(int R, int C) {
   p = p >= CPR ? p - CPR : p;
   return R * L + p * 8;
 }
-// Copy a row-major [160][160] bf16 matrix into LDS in the rotated layout.
-__device__ __forceinline__ void stage_rot(bf16* dst, const bf16* __restrict__ src, int tid) {
-  for (int idx = tid; idx < L * CPR; idx += NT) {
-    const int row = idx / CPR, c = idx % CPR;
-    *reinterpret_cast<uint4*>(dst + rot(row, c)) = *reinterpret_cast<const uint4*>(src + row * L + c * 8);
+// Staging of a row-major [160][160] bf16 matrix into LDS, in the rotated
+// layout or in rows of stride LW: all of a kernel's matrices are loaded before
+// any is stored (see WeightStage).
+struct Stage160 {
+  static constexpr int N = (L * CPR + NT - 1) / NT;
+  uint4 r[N];
+  __device__ __forceinline__ void load(const void* src, int tid) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] = reinterpret_cast<const uint4*>(src)[min(tid + NT * j, L * CPR - 1)];
   }
-}
+  template <class F>
+  __device__ __forceinline__ void put(bf16* dst, int tid, F&& at) const {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int idx = tid + NT * j;
+      if (idx < L * CPR) *reinterpret_cast<uint4*>(dst + at(idx / CPR, idx % CPR)) = r[j];
+    }
+  }
+  __device__ __forceinline__ void store_rot(bf16* dst, int tid) const {
+    put(dst, tid, [](int row, int c) { return rot(row, c); });
+  }
+  __device__ __forceinline__ void store_pad(bf16* dst, int tid) const {
+    put(dst, tid, [](int row, int c) { return row * LW + c * 8; });
+  }
+};
 // Per-lane parts of the fragment addresses, so that every read is one of
 // five per-lane offsets plus an immediate.
 // A fragment of output block ob at K step s of W x: row 16 ob + i, chunk
@@ -80,15 +98,6 @@ struct RotOff {
     return cat8(lds_tr(p0), lds_tr(p1));
   }
 };
-
-// Copy a row-major [160][160] bf16 matrix into LDS rows of stride LW.
-__device__ __forceinline__ void stage_w(bf16* dst, const bf16* __restrict__ src, int tid) {
-  constexpr int CPR = L / 8;
-  for (int idx = tid; idx < L * CPR; idx += NT) {
-    const int row = idx / CPR, c = idx % CPR;
-    *reinterpret_cast<uint4*>(dst + row * LW + c * 8) = *reinterpret_cast<const uint4*>(src + row * L + c * 8);
-  }
-}
 
 // C-layout fragment of output block ob from the lane's five bf16 runs.
 __device__ __forceinline__ f32x4 run_block5(const uint4 (&runs)[NS], int ob) {
