@@ -396,74 +396,59 @@ __global__ void __launch_bounds__(LD * 4) k_enc_bwd(int64_t M, const float* __re
 }
 
 // ----------------------------------------------------------- reduce
-// grad[...] += sum over the nblocks partial rows.  A block takes 16
-// consecutive entries; its 16 lane groups each sum every 16th partial row
-// (group g: rows g, g+16, ...) in row order, 8 loads in flight, and the 16
-// group sums are added in group order: a fixed order for any launch.
-constexpr int kRedCols = 16, kRedGroups = 16;
-__global__ void __launch_bounds__(256) k_reduce(Partials part, int nblocks, int64_t src, int32_t rows, int32_t cols,
-                                                float* __restrict__ grad, int64_t dst, int64_t dst_ld) {
-  __shared__ float red[kRedGroups][kRedCols];
-  const int64_t total = (int64_t)rows * cols;
-  const int c = threadIdx.x % kRedCols, gr = threadIdx.x / kRedCols;
-  const int64_t idx = (int64_t)blockIdx.x * kRedCols + c;
-  float s = 0.f;
-  if (idx < total) {
-    const float* p = part.buf + src + idx;
+// grad[...] += sum over the nblocks partial rows.  A block takes 64
+// consecutive entries, four per lane; its 16 lane groups each sum every 16th
+// partial row (group g: rows g, g+16, ...) in row order, 8 loads in flight, and
+// the 16 group sums are added in group order: a fixed order for any launch.
+// Bound by reading the partials: with one entry per lane a wave's load was
+// four pieces of 64 bytes, and an MP step's 112 MB of partials (32^3 mesh, width
+// 128, bf16) took R0 us; with 16 bytes per lane R1 us.
+constexpr int kRedCols = 64, kRedGroups = 16;
+
+__device__ __forceinline__ void reduce_entries(const float* part, int64_t stride, int nblocks, int64_t total,
+                                               int64_t idx0, int cols, float* grad, int64_t ld) {
+  __shared__ __align__(16) float red[kRedGroups][kRedCols];
+  const int c = 4 * (threadIdx.x % (kRedCols / 4)), gr = threadIdx.x / (kRedCols / 4);
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  if (idx0 + c < total) {  // up to three floats past the entries are read: still the partial row's
+    const float* p = part + idx0 + c;
     int b = gr;
     for (; b + 7 * kRedGroups < nblocks; b += 8 * kRedGroups) {
-      float v[8];
+      f32x4 v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(b + u * kRedGroups) * part.stride];
+      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(p + (size_t)(b + u * kRedGroups) * stride);
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; b < nblocks; b += kRedGroups) s += p[(size_t)b * part.stride];
+    for (; b < nblocks; b += kRedGroups) s += *reinterpret_cast<const f32x4*>(p + (size_t)b * stride);
   }
-  red[gr][c] = s;
+  *reinterpret_cast<f32x4*>(&red[gr][c]) = s;
   __syncthreads();
-  if (gr == 0 && idx < total) {
+  const int64_t idx = idx0 + threadIdx.x;
+  if (threadIdx.x < kRedCols && idx < total) {
     float t = 0.f;
 #pragma unroll
-    for (int g = 0; g < kRedGroups; ++g) t += red[g][c];
+    for (int g = 0; g < kRedGroups; ++g) t += red[g][threadIdx.x];
     const int64_t r = idx / cols, cc = idx % cols;
-    grad[dst + r * dst_ld + cc] += t;
+    grad[r * ld + cc] += t;
   }
+}
+
+__global__ void __launch_bounds__(256) k_reduce(Partials part, int nblocks, int64_t src, int32_t rows, int32_t cols,
+                                                float* __restrict__ grad, int64_t dst, int64_t dst_ld) {
+  reduce_entries(part.buf + src, part.stride, nblocks, (int64_t)rows * cols, (int64_t)blockIdx.x * kRedCols, cols,
+                 grad + dst, dst_ld);
 }
 
 // The jobs of a batch one after the other over the launch's blocks; each
 // entry is summed exactly as in k_reduce.
 __global__ void __launch_bounds__(256) k_reduce_batch(Partials part, int64_t region_floats, ReduceBatch b,
                                                       float* __restrict__ grad) {
-  __shared__ float red[kRedGroups][kRedCols];
   int k = 0;
   while (k + 1 < b.n && (int64_t)blockIdx.x >= b.j[k + 1].blk0) ++k;
   const ReduceJob& J = b.j[k];
-  const int64_t total = (int64_t)J.rows * J.cols;
-  const int c = threadIdx.x % kRedCols, gr = threadIdx.x / kRedCols;
-  const int64_t idx = ((int64_t)blockIdx.x - J.blk0) * kRedCols + c;
-  float s = 0.f;
-  if (idx < total) {
-    const float* p = part.buf + J.region * region_floats + J.src + idx;
-    int bl = gr;
-    for (; bl + 7 * kRedGroups < J.nblocks; bl += 8 * kRedGroups) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(bl + u * kRedGroups) * part.stride];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; bl < J.nblocks; bl += kRedGroups) s += p[(size_t)bl * part.stride];
-  }
-  red[gr][c] = s;
-  __syncthreads();
-  if (gr == 0 && idx < total) {
-    float t = 0.f;
-#pragma unroll
-    for (int g = 0; g < kRedGroups; ++g) t += red[g][c];
-    const int64_t r = idx / J.cols, cc = idx % J.cols;
-    grad[J.dst + r * J.ld + cc] += t;
-  }
+  reduce_entries(part.buf + J.region * region_floats + J.src, part.stride, J.nblocks, (int64_t)J.rows * J.cols,
+                 ((int64_t)blockIdx.x - J.blk0) * kRedCols, J.cols, grad + J.dst, J.ld);
 }
 
 }  // namespace dev
@@ -522,6 +507,7 @@ hipError_t launch_node_enc_bwd(int prec, int lat, int64_t N, const float* node_i
 hipError_t launch_reduce(const Partials& part, int nblocks, int64_t src, int32_t rows, int32_t cols, float* grad,
                          int64_t dst, int64_t dst_ld, hipStream_t s) {
   if (nblocks <= 0 || rows <= 0 || cols <= 0) return hipSuccess;
+  if (((src | part.stride) & 3) != 0 || src + (int64_t)rows * cols > part.stride) return hipErrorInvalidValue;
   const int64_t total = (int64_t)rows * cols;
   const int64_t g = (total + kRedCols - 1) / kRedCols;
   hipLaunchKernelGGL(k_reduce, dim3((unsigned)g), dim3(256), 0, s, part, nblocks, src, rows, cols, grad, dst, dst_ld);
@@ -534,6 +520,9 @@ hipError_t launch_reduce_batch(const Partials& part, int64_t region_floats, Redu
   if (b.n > kMaxReduceJobs) return hipErrorInvalidValue;
   int64_t blocks = 0;
   for (int k = 0; k < b.n; ++k) {
+    if (((b.j[k].src | part.stride | region_floats) & 3) != 0 ||
+        b.j[k].src + (int64_t)b.j[k].rows * b.j[k].cols > part.stride)
+      return hipErrorInvalidValue;
     b.j[k].blk0 = blocks;
     blocks += ((int64_t)b.j[k].rows * b.j[k].cols + kRedCols - 1) / kRedCols;
   }
