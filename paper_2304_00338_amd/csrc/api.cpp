@@ -589,6 +589,8 @@ struct Run {
     t.senders = g.senders;
     t.receivers = g.receivers;
     t.n_edges = g.n_edges;
+    t.n_nodes = N;
+    t.n_long = g.n_long;
     return t;
   }
   Partials part() const {

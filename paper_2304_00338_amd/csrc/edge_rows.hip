@@ -4,7 +4,8 @@
 // new messages of its in-edges).
 //
 // Work split.  Each of the 8 waves of a block runs its own persistent loop
-// over tiles; the only block barrier is the one after the weights are
+// over tiles or the steps of runs (edge_walk.hpp; below, a tile is either); the
+// only block barrier is the one after the weights are
 // staged in LDS.  A tile is two 16-row blocks in the lane layout of
 // rows_common.hpp.
 //
@@ -17,8 +18,7 @@
 // Node sums: the wave stages each 16-row half of the messages in its own
 // LDS area and sums every in-segment in ascending row order from 0.0, so a
 // node's aggregate does not depend on where its segment sits in a tile.
-#include "rows_common.hpp"
-#include "launch.hpp"
+#include "edge_walk.hpp"
 
 namespace mgn {
 namespace dev {
@@ -36,31 +36,29 @@ struct __attribute__((aligned(16))) RowsLds {
 };
 
 
-// In-segment node sums over one staged 16-row half [lo_row, lo_row + 16) of
-// a tile (rows past the tile's end are never inside a segment).  For a tile
-// of whole segments node j's rows are [rp(j) - base, rp(j+1) - base) with
-// rp(j) held by lane j of segraw; a chunk tile (chunk) is the single segment
-// [0, n).  j is the first node whose sum is still open and carry its partial
-// sum (features 2*lane, 2*lane+1), added in ascending row order; close(j,
-// sum) is called for every node whose segment ends inside this half.
+// In-segment node sums over one staged 16-row half [lo_row, lo_row + 16) of a
+// step of n rows: bit r of ends is set where row r ends a segment.  carry is
+// the open segment's partial sum (features 2*lane, 2*lane+1), added in
+// ascending row order; close(r, sum) is called for every segment that ends in
+// this half (r its last row).
 template <class F>
-__device__ __forceinline__ void seg_pass(const float* stage, int lane, int segraw, int base, bool chunk, int n,
-                                         int nv, int lo_row, int& j, float2& carry, F&& close) {
-  const int hi_row = lo_row + 16;
-  while (j < nv) {
-    const int a = chunk ? 0 : __builtin_amdgcn_readlane(segraw, j) - base;
-    const int b = chunk ? n : __builtin_amdgcn_readlane(segraw, j + 1) - base;
-    const int u0 = max(a, lo_row), u1 = min(b, hi_row);
-    for (int u = u0; u < u1; ++u) {
+__device__ __forceinline__ void seg_pass(const float* stage, int lane, uint32_t ends, int n, int lo_row, float2& carry,
+                                         F&& close) {
+  int u = lo_row;
+  auto add_to = [&](int end) {
+    for (; u < end; ++u) {
       const float2 v = *reinterpret_cast<const float2*>(stage + (u - lo_row) * RW_LDM + 2 * lane);
       carry.x += v.x;
       carry.y += v.y;
     }
-    if (b > hi_row) break;
-    close(j, carry);
+  };
+  for (uint32_t m = (ends >> lo_row) & 0xffffu; m; m &= m - 1) {
+    const int b = lo_row + __builtin_ctz(m);
+    add_to(b + 1);
+    close(b, carry);
     carry = float2{0.f, 0.f};
-    ++j;
   }
+  add_to(min(n, lo_row + 16));
 }
 
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -76,21 +74,9 @@ k_edge_fwd_rows(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
 
   // XCD-contiguous tile ranges: the node products gathered by one XCD's
   // waves then mostly share that XCD's L2.
-  const UnitRange ur = unit_range(tl.n_tiles, wv);
-  int64_t t = ur.t;
-  const int64_t stride = ur.stride, tend = ur.end;
+  const UnitRange ur = unit_range(walk_units(tl), wv);
 
   const bf16x8 sel0 = select_frag(0, i, q), sel1 = select_frag(1, i, q);
-  auto desc = [&](int64_t tt) -> int4 {
-    const bool ok = tt < tend;
-    const int4 v = tile_desc(tl.tiles, ok ? tt : tend - 1);
-    int4 r;
-    r.x = ok ? v.x : 0;
-    r.y = ok ? v.y : 0;
-    r.z = ok ? v.z : 0;
-    r.w = ok ? v.w : 0;
-    return r;
-  };
   // Every global load below is unconditional, from an index clamped into
   // its array (so the compiler's in-order wait counts stay exact and a wait
   // never covers a later prefetch): rows past a tile's end, and the tiles
@@ -125,7 +111,7 @@ k_edge_fwd_rows(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
   float* stage = S.stage[wv];
 
   // One half (rows rb*16 .. +16) of tile d0 with its streams in H.
-  auto half = [&](HalfF& H, int4 d0, int rb, int segraw, bool chunk, int nv, int& j, float2& carry) {
+  auto half = [&](HalfF& H, int4 d0, int rb, uint32_t ends, int rcv, float2& carry) {
     const int n = tile_rows(d0);
     // ---- z1 = b1 + P_s + P_r + W1e e
     f32x4 acc[8];
@@ -213,15 +199,16 @@ k_edge_fwd_rows(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
       }
     }
     wave_lds_sync();
-    seg_pass(stage, lane, segraw, d0.z, chunk, n, nv, rb * 16, j, carry, [&](int jj, float2 v) {
-      float* dst = !chunk ? agg + (size_t)(d0.x + jj) * D : slots + (size_t)(-1 - d0.y) * D;
+    seg_pass(stage, lane, ends, n, rb * 16, carry, [&](int r, float2 v) {
+      float* dst = d0.y >= 0 ? agg + (size_t)__builtin_amdgcn_readlane(rcv, r) * D : slots + (size_t)(-1 - d0.y) * D;
       *reinterpret_cast<float2*>(dst + 2 * lane) = v;
     });
     wave_lds_sync();
   };
 
   // issue order = use order, so each wait covers only older requests
-  int4 d0 = desc(t), d1 = desc(t + stride);
+  EdgeSteps es;
+  int4 d0 = es.first(tl, ur.t, ur.stride, ur.end), d1 = es.next(tl);
   int sc[2], rc[2], sn[2], rn[2];
   load_sr(d0, sc, rc);
   HalfF A, B;
@@ -234,20 +221,21 @@ k_edge_fwd_rows(EdgeTiles tl, const bf16* __restrict__ e_in, bf16* __restrict__ 
     S.g[tid] = w.gamma[tid];
     S.bt[tid] = w.beta[tid];
   }
+  if (tl.run) zero_share<D>(tl, (int64_t)blockIdx.x * NW + wv, (int64_t)gridDim.x * NW, lane, agg);
   __syncthreads();
-  for (; t < tend; t += stride) {
-    const bool chunk = d0.y < 0;
-    const int nv = chunk ? 1 : d0.y - d0.x;
-    // in-segment starts of the tile's nodes (lane j: rowptr of node j)
-    const int segraw = tl.rowptr[min(d0.x + lane, max(d0.x, d0.y))];
-    const int4 d2 = desc(t + 2 * stride);
+  float2 carry = {0.f, 0.f};  // the open segment's sum
+  const int64_t n_steps = ur.t < ur.end ? (ur.end - ur.t + ur.stride - 1) / ur.stride * walk_steps(tl) : 0;
+  for (int64_t st = 0; st < n_steps; ++st) {
+    const int4 d2 = es.next(tl);
+    // lanes 0 .. 31: the step's rows
+    const int rcv = (q & 1) ? rc[1] : rc[0];
+    const uint32_t ends = segment_ends(lane & 31, tile_rows(d0), rcv, d0.y);
     load_sr(d1, sn, rn);
     issue_half(d0, 1, sc[1], rc[1], B);
-    float2 carry = {0.f, 0.f};
-    int j = 0;  // next node whose sum is open
-    half(A, d0, 0, segraw, chunk, nv, j, carry);
+    half(A, d0, 0, ends, rcv, carry);
     issue_half(d1, 0, sn[0], rn[0], A);
-    half(B, d0, 1, segraw, chunk, nv, j, carry);
+    half(B, d0, 1, ends, rcv, carry);
+    if (!tl.run && d0.y > d0.x) zero_empty<D>(d0.x, d0.y, tl.rowptr, lane, agg);
     d0 = d1;
     d1 = d2;
 #pragma unroll
@@ -362,34 +350,24 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
   // (and gradient wave 4 + k for the e rows and the receiver sums) takes
   // tile tb + k of every round pair; all waves run the same number of
   // rounds (a row wave past the range runs empty tiles).
-  const int G = gridDim.x;
+  const int G = gridDim.x, n_steps = walk_steps(tl);
+  const int64_t n_units = walk_units(tl);
   int64_t tb, stride, tend;
   if ((G & 7) == 0) {
     const int x = blockIdx.x & 7, per = G >> 3;
-    const int64_t chunk = (tl.n_tiles + 7) >> 3;
+    const int64_t chunk = (n_units + 7) >> 3;
     const int64_t lo = x * chunk;
-    tend = min(tl.n_tiles, lo + chunk);
+    tend = min(n_units, lo + chunk);
     tb = lo + (int64_t)(blockIdx.x >> 3) * FB_RW;
     stride = (int64_t)per * FB_RW;
   } else {
     tb = (int64_t)blockIdx.x * FB_RW;
     stride = (int64_t)G * FB_RW;
-    tend = tl.n_tiles;
+    tend = n_units;
   }
   const bool row_wave = wv < FB_RW;
   const int k = row_wave ? wv : wv - FB_RW;  // the tile slot this wave follows
 
-  const int64_t tlast = max(tend - 1, (int64_t)0);
-  auto desc = [&](int64_t tt) -> int4 {
-    const bool ok = tt < tend;
-    const int4 v = tile_desc(tl.tiles, ok ? tt : tlast);
-    int4 r;
-    r.x = ok ? v.x : 0;
-    r.y = ok ? v.y : 0;
-    r.z = ok ? v.z : 0;
-    r.w = ok ? v.w : 0;
-    return r;
-  };
   // Every global load is unconditional from a clamped index (see the
   // forward kernel); rows past a tile's end (and the rows of an empty tile)
   // read row 0 or the tile's last row, and are never stored or summed.
@@ -437,31 +415,25 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
       }
     };
     // Per-receiver sums of zbar (as stored) over the staged rows of row
-    // wave k's half rb of tile d, each in ascending row order from 0.0 and
-    // carried into the next half while its segment is open: nodes d.x + j
-    // of a tile of whole segments (rp(j) in lane j of segraw), or the single
-    // segment of a chunk tile, summed into its slot.
-    auto recv_sums = [&](int4 d, int rb, int segraw, bool chunk, int nv, int& j, float2& carry) {
+    // wave k's half rb of step d, each in ascending row order from 0.0 and
+    // carried on while its segment is open (bit r of ends: row r ends one), to
+    // its receiver's row of R or a chunk's slot.  rcv: row lane's receiver.
+    auto recv_sums = [&](int4 d, int rb, uint32_t ends, int rcv, float2& carry) {
       const bf16* zs = S.st[1] + 16 * k * FB_LD;
       uint32_t zr[16];  // the 16 rows' values of this lane's two features, read at once
 #pragma unroll
       for (int r = 0; r < 16; ++r) zr[r] = *reinterpret_cast<const uint32_t*>(zs + r * FB_LD + 2 * lane);
-      const int n = tile_rows(d);
-      const int lo_row = rb * 16, hi_row = lo_row + 16;
-      while (j < nv) {
-        const int a = chunk ? 0 : __builtin_amdgcn_readlane(segraw, j) - d.z;
-        const int b = chunk ? n : __builtin_amdgcn_readlane(segraw, j + 1) - d.z;
-        const int u0 = max(a, lo_row), u1 = min(b, hi_row);
-        for (int u = u0; u < u1; ++u) {
-          const uint32_t v = zr[u - lo_row];
-          carry.x += __uint_as_float(v << 16);
-          carry.y += __uint_as_float(v & 0xffff0000u);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        // (rows past the end are zero)
+        carry.x += __uint_as_float(zr[r] << 16);
+        carry.y += __uint_as_float(zr[r] & 0xffff0000u);
+        if ((ends >> (16 * rb + r)) & 1u) {
+          float* dst = d.y >= 0 ? R + (size_t)__builtin_amdgcn_readlane(rcv, 16 * rb + r) * D
+                                : slots + (size_t)(-1 - d.y) * D;
+          *reinterpret_cast<float2*>(dst + 2 * lane) = carry;
+          carry = float2{0.f, 0.f};
         }
-        if (b > hi_row) break;
-        float* dst = !chunk ? R + (size_t)(d.x + j) * D : slots + (size_t)(-1 - d.y) * D;
-        *reinterpret_cast<float2*>(dst + 2 * lane) = carry;
-        carry = float2{0.f, 0.f};
-        ++j;
       }
     };
     auto load_e = [&](int4 d, int rb, uint4 (&v)[4]) {
@@ -469,33 +441,42 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
 #pragma unroll
       for (int s = 0; s < 4; ++s) v[s] = *reinterpret_cast<const uint4*>(xp + 32 * s);
     };
+    if (tl.run) zero_share<D>(tl, (int64_t)blockIdx.x * FB_RW + k, (int64_t)gridDim.x * FB_RW, lane, R);
     if (tb < tend) {
-      int4 d0 = desc(tb + k), d1 = desc(tb + k + stride);
+      EdgeSteps es;
+      int4 d0 = es.first(tl, tb + k, stride, tend), d1 = es.next(tl);
+      auto load_rcv = [&](int4 d) {  // of row lane
+        return tl.receivers[min(max(d.z + min(lane & 31, tile_rows(d) - 1), 0), lastE)];
+      };
       uint4 ev[4];
+      int rcv = load_rcv(d0);
       load_e(d0, 0, ev);
-      for (; tb < tend; tb += stride) {
-        const bool chunk = d0.y < 0;
-        const int nv = chunk ? 1 : d0.y - d0.x;
-        // in-segment starts of the tile's nodes (lane j: rowptr of node j)
-        const int segraw = tl.rowptr[min(d0.x + lane, max(d0.x, d0.y))];
-        float2 carry = {0.f, 0.f};
-        int j = 0;  // next node whose sum is open
+      float2 carry = {0.f, 0.f};  // the open segment's sum
+      for (; tb < tend; tb += stride)
+        for (int st = 0; st < n_steps; ++st) {
+          int rcv_n = 0;
+          uint32_t ends = 0;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          __syncthreads();  // staging free
-          stage_runs(S.st[3], ev, rb * 16 + i < tile_rows(d0));
-          __syncthreads();  // staging full
-          recv_sums(d0, rb, segraw, chunk, nv, j, carry);
-          products();
-          // the next round's e rows, in flight while the row waves finish it
-          if (rb == 0)
-            load_e(d0, 1, ev);
-          else
-            load_e(d1, 0, ev);
+          for (int rb = 0; rb < 2; ++rb) {
+            __syncthreads();  // staging free
+            stage_runs(S.st[3], ev, rb * 16 + i < tile_rows(d0));
+            __syncthreads();  // staging full
+            if (rb == 0) ends = segment_ends(lane & 31, tile_rows(d0), rcv, d0.y);
+            recv_sums(d0, rb, ends, rcv, carry);
+            products();
+            // the next round's e rows, in flight while the row waves finish it
+            if (rb == 0) {
+              load_e(d0, 1, ev);
+              rcv_n = load_rcv(d1);
+            } else {
+              load_e(d1, 0, ev);
+            }
+          }
+          if (!tl.run && d0.y > d0.x) zero_empty<D>(d0.x, d0.y, tl.rowptr, lane, R);
+          d0 = d1;
+          d1 = es.next(tl);
+          rcv = rcv_n;
         }
-        d0 = d1;
-        d1 = desc(tb + k + 2 * stride);
-      }
     }
     // weight gradients straight from the owning wave; db1 / db2 from the
     // ones column
@@ -685,7 +666,8 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
   };
 
   if (tb < tend) {
-    int4 d0 = desc(tb + k), d1 = desc(tb + k + stride);
+    EdgeSteps es;
+    int4 d0 = es.first(tl, tb + k, stride, tend), d1 = es.next(tl);
     int rc0[2], rn[2];
     load_recv(d0, rc0);
     load_recv(d1, rn);
@@ -693,9 +675,10 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
     load_half(d0, 0, A);
     f32x4 ag[8];
     load_ag(rc0[0], ag);
-    for (; tb < tend; tb += stride) {
+    for (; tb < tend; tb += stride)
+    for (int st = 0; st < n_steps; ++st) {
       // issue order = use order, so each wait covers only older requests
-      const int4 d2 = desc(tb + k + 2 * stride);
+      const int4 d2 = es.next(tl);
       load_half(d0, 1, B);
       round(A, ag, rc0[1], d0, 0);
       load_half(d1, 0, A);
@@ -731,15 +714,12 @@ using namespace dev;
 
 static constexpr int kRowsBlocks = 256;
 
-static int rows_grid(int64_t n_tiles, int max_blocks) {
-  return unit_blocks(n_tiles, NW, max_blocks);
-}
-
-hipError_t launch_edge_fwd_rows(const EdgeTiles& t, const void* e_in, void* e_out, int write_e, const void* Pn,
+hipError_t launch_edge_fwd_rows(const EdgeTiles& tl, const void* e_in, void* e_out, int write_e, const void* Pn,
                                 const MlpW& w, float eps, float* agg, float* slots, void* a1_out, hipStream_t s) {
-  if (t.n_tiles <= 0) return hipSuccess;
-  if (t.n_edges <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_edge_fwd_rows, dim3(rows_grid(t.n_tiles, kRowsBlocks)), dim3(NT), 0, s, t, (const bf16*)e_in,
+  if (tl.n_tiles <= 0) return hipSuccess;
+  if (tl.n_edges <= 0) return hipErrorInvalidValue;
+  const EdgeTiles t = plan_runs(tl, NW * kRowsBlocks);
+  hipLaunchKernelGGL(k_edge_fwd_rows, dim3(unit_blocks(walk_n(t), NW, kRowsBlocks)), dim3(NT), 0, s, t, (const bf16*)e_in,
                      (bf16*)e_out, write_e, (const bf16*)Pn, w, eps, agg, slots, (bf16*)a1_out);
   return hipGetLastError();
 }
@@ -748,14 +728,16 @@ hipError_t launch_edge_fwd_rows(const EdgeTiles& t, const void* e_in, void* e_ou
 
 static constexpr int kFusedBlocks = 256;
 
-hipError_t launch_edge_bwd_fused(const EdgeTiles& t, const void* a1, const void* e, const void* ebar_in,
+hipError_t launch_edge_bwd_fused(const EdgeTiles& tl, const void* a1, const void* e, const void* ebar_in,
                                  int have_ebar, void* ebar_out, const float* aggbar, const MlpW& w, float eps,
                                  void* zbar, float* R, float* slots, const Partials& part, int* nblocks,
                                  hipStream_t s) {
   *nblocks = 0;
-  if (t.n_tiles <= 0) return hipSuccess;
-  if (t.n_edges <= 0 || part.stride < 33280) return hipErrorInvalidValue;
-  const int g = unit_blocks(t.n_tiles, FB_RW, std::min(kFusedBlocks, part.max_blocks));
+  if (tl.n_tiles <= 0) return hipSuccess;
+  if (tl.n_edges <= 0 || part.stride < 33280) return hipErrorInvalidValue;
+  const int most = std::min(kFusedBlocks, part.max_blocks);
+  const EdgeTiles t = plan_runs(tl, FB_RW * most);
+  const int g = unit_blocks(walk_n(t), FB_RW, most);
   *nblocks = g;
   if (have_ebar)
     hipLaunchKernelGGL(k_edge_bwd_fused<true>, dim3(g), dim3(FB_NT), 0, s, t, (const bf16*)a1, (const bf16*)e,

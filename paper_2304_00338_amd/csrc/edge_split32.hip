@@ -3,7 +3,7 @@
 // each node sums the new messages of its in-edges), with one wave per
 // receiver-aligned tile of at most 32 edges.  The products run as split fp16
 // products on weights that stream through LDS (split32_common.hpp).
-#include "launch.hpp"
+#include "edge_walk.hpp"
 #include "split32_common.hpp"
 
 namespace mgn {
@@ -17,14 +17,6 @@ struct __attribute__((aligned(16))) EdgeFwdLds {
   __attribute__((aligned(16))) float vec[4][LD];  // b1, b2, gamma, beta
   __attribute__((aligned(16))) float stage[X3_NW][SR * SL];
 };
-
-// The tile's rows that end a segment (bit per row).  Rows of a tile are
-// sorted by receiver; rcv: the lane's row's receiver.
-__device__ __forceinline__ uint32_t segment_ends(int row, int n, int rcv, bool chunk) {
-  const int nx = __shfl(rcv, min(row + 1, 31));
-  const bool e = row < n && (row == n - 1 || (!chunk && nx != rcv));
-  return (uint32_t)__ballot(e);
-}
 
 // Forward: e' = e + m (when write_e), agg = receiver sums of m, with
 // m = LN(W2 relu(b1 + P_s + P_r + W1e e) + b2) (the node products P = [W1s
@@ -47,7 +39,7 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int f0 = 8 * hh;  // the lane's first feature
   const u32x4 *W1 = (const u32x4*)w.S1, *W2 = (const u32x4*)w.S2;
-  const BlockRange br = block_range(tl.n_tiles);
+  const BlockRange br = block_range(walk_units(tl));
   if (br.tb >= br.tend) return;
   gemm_x3_start<LD>(W1, S.w, tid);
   for (int f = tid; f < LD; f += X3_NT) {
@@ -57,18 +49,19 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
     S.vec[3][f] = w.beta[f];
   }
   const int lastE = (int)(tl.n_edges - 1);
-  // tile t's descriptor, {0, 0, 0, 0} (no rows) past the range
-  auto desc = [&](int64_t t) -> int4 {
-    const bool ok = t < br.tend;
-    const int4 v = tile_desc(tl.tiles, ok ? t : br.tend - 1);
-    return ok ? v : make_int4(0, 0, 0, 0);
-  };
   auto erow = [&](int4 d) { return min(max(d.z + min(row, tile_rows(d) - 1), 0), lastE); };
-  int4 d = desc(br.tb + wv);
+  EdgeSteps es;
+  int4 d = es.first(tl, br.tb + wv, br.stride, br.tend);
   int snd = tl.senders[erow(d)], rcv = tl.receivers[erow(d)];
+  if (tl.run) zero_share<LD>(tl, (int64_t)blockIdx.x * X3_NW + wv, (int64_t)gridDim.x * X3_NW, lane, agg);
   __syncthreads();
-  for (int64_t t = br.tb; t < br.tend; t += br.stride) {
-    const int4 dn = desc(t + br.stride + wv);
+  float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};  // the open segment's sum
+  const int n_steps = walk_steps(tl);
+  for (int64_t t = br.tb; t < br.tend; t += br.stride)
+  for (int st = 0; st < n_steps; ++st) {
+    const int4 dn = es.next(tl);
+    // formed per step: kept across steps, what depends on them spills
+    const int lane = (tid & 63) + opaque_zero(), row = lane & 31, hh = lane >> 5, f0 = 8 * hh;
     const int n = tile_rows(d);
     const TileRow<LD> tr(d, lastE, row, hh);
     const bool chunk = d.y < 0;
@@ -119,8 +112,8 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
     }
     // ---- receiver sums, SR rows at a time, and e_out = e + m: read and
     // written as whole rows here, where the messages lie row by row
-    const uint32_t ends = segment_ends(row, n, rcv, chunk);
-    float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}}, tot[2] = {{0.f, 0.f}, {0.f, 0.f}};
+    const uint32_t ends = segment_ends(row, n, rcv, d.y);
+    float2 tot[2] = {{0.f, 0.f}, {0.f, 0.f}};
     float* stage = S.stage[wv];
 #pragma unroll
     for (int r0 = 0; r0 < 32; r0 += Lds::SR) {
@@ -147,7 +140,8 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
       });
       wave_lds_sync();
     }
-    if (!chunk && d.y > d.x) zero_empty<LD>(d, tl.rowptr, lane, agg);
+    if (n < 32 || (ends >> 31)) carry[0] = carry[1] = float2{0.f, 0.f};  // rows past the end
+    if (!tl.run && !chunk && d.y > d.x) zero_empty<LD>(d.x, d.y, tl.rowptr, lane, agg);
     d = dn;
     snd = snd_n;
     rcv = rcv_n;
@@ -168,7 +162,7 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
 // At width 160 that does not fit, and the block has four waves of 512.
 //   Measured per launch: 434,558 edges at width 128 1.11 -> 0.57 ms (fp32 MFMA
 // version, dW1e included, -> this; its dW1e pass takes 0.11 ms), the eight-patch
-// batch (0.9M edges) at width 160 2.62 -> 1.78 ms.  With its loads and stores
+// batch (0.9M edges) at width 160 2.62 -> 1.57 ms.  With its loads and stores
 // taken away it still takes 0.49 ms of 0.62: the arithmetic of the phases that
 // the eight waves enter together is what bounds it, not memory.
 // Partials per block: db1 at LD^2, dW2, db2, dgamma, dbeta.
@@ -202,7 +196,7 @@ k_edge_bwd_x3(EdgeTiles tl, const float* __restrict__ e_in, const float* ebar_in
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int f0 = 8 * hh;  // the lane's first feature
   const u32x4 *W1 = (const u32x4*)w.S1, *W2 = (const u32x4*)w.S2, *W2t = (const u32x4*)w.S2t, *W1t = (const u32x4*)w.S1t;
-  const BlockRange br = block_range<NW>(tl.n_tiles);
+  const BlockRange br = block_range<NW>(walk_units(tl));
   gemm_x3_start<LD, NT>(W1, S.w, tid);
   for (int f = tid; f < LD; f += NT) {
     S.vec[0][f] = w.b1[f];
@@ -210,22 +204,23 @@ k_edge_bwd_x3(EdgeTiles tl, const float* __restrict__ e_in, const float* ebar_in
     S.vec[2][f] = w.gamma[f];
   }
   const int lastE = (int)(tl.n_edges - 1);
-  const int64_t tlast = max(br.tend - 1, (int64_t)0);
-  auto desc = [&](int64_t t) -> int4 {
-    const bool ok = t < br.tend;
-    const int4 v = tile_desc(tl.tiles, ok ? t : tlast);
-    return ok ? v : make_int4(0, 0, 0, 0);
-  };
   auto erow = [&](int4 d) { return min(max(d.z + min(row, tile_rows(d) - 1), 0), lastE); };
   DwAcc<LD, NW> dw2;
   dw2.clear();
   ColSumX3<LD> db2, dga, dbe;
   float2 db1[2] = {{0.f, 0.f}, {0.f, 0.f}};
-  int4 d = desc(br.tb + wv);
+  EdgeSteps es;
+  int4 d = es.first(tl, br.tb + wv, br.stride, br.tend);
   int snd = tl.senders[erow(d)], rcv = tl.receivers[erow(d)];
+  if (tl.run) zero_share<LD>(tl, (int64_t)blockIdx.x * NW + wv, (int64_t)gridDim.x * NW, lane, R);
   __syncthreads();
-  for (int64_t t = br.tb; t < br.tend; t += br.stride) {
-    const int4 dn = desc(t + br.stride + wv);
+  float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};  // the open segment's sum
+  const int n_steps = walk_steps(tl);
+  for (int64_t t = br.tb; t < br.tend; t += br.stride)
+  for (int st = 0; st < n_steps; ++st) {
+    const int4 dn = es.next(tl);
+    // formed per step: kept across steps, what depends on them spills
+    const int lane = (tid & 63) + opaque_zero(), row = lane & 31, hh = lane >> 5, f0 = 8 * hh;
     const int n = tile_rows(d);
     const TileRow<LD> tr(d, lastE, row, hh);
     const bool chunk = d.y < 0, live = row < n;
@@ -306,8 +301,7 @@ k_edge_bwd_x3(EdgeTiles tl, const float* __restrict__ e_in, const float* ebar_in
 #pragma unroll
     for (int v = 0; v < Z::KL; ++v) g[v] = (mask[v >> 5] >> (v & 31)) & 1u ? acc[v >> 4][v & 15] : 0.f;
     // ---- zbar's rows and their receiver sums
-    const uint32_t ends = segment_ends(row, n, rcv, chunk);
-    float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};
+    const uint32_t ends = segment_ends(row, n, rcv, d.y);
     float* stage = S.stage[wv];
 #pragma unroll
     for (int r0 = 0; r0 < 32; r0 += K::SR) {
@@ -325,7 +319,8 @@ k_edge_bwd_x3(EdgeTiles tl, const float* __restrict__ e_in, const float* ebar_in
       });
       wave_lds_sync();
     }
-    if (!chunk && d.y > d.x) zero_empty<LD>(d, tl.rowptr, lane, R);
+    if (n < 32 || (ends >> 31)) carry[0] = carry[1] = float2{0.f, 0.f};  // rows past the end
+    if (!tl.run && !chunk && d.y > d.x) zero_empty<LD>(d.x, d.y, tl.rowptr, lane, R);
     // ---- ebar_out = ebar_in + W1e^T zbar
     gemm_x3<LD, NT>(acc, g, W1t, W1, S.w, Z::NC & 1, tid);
     {
@@ -414,11 +409,12 @@ using namespace dev;
 // two blocks per CU
 static constexpr int kSplitBlocks = 512;
 
-hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& t, const void* e_in, void* e_out, int write_e, const void* Pn,
+hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& tl, const void* e_in, void* e_out, int write_e, const void* Pn,
                               const MlpW& w, float eps, float* agg, float* slots, hipStream_t s) {
-  if (t.n_tiles <= 0) return hipSuccess;
-  if (t.n_edges <= 0 || !w.S1 || !w.S2) return hipErrorInvalidValue;
-  const int g = unit_blocks(t.n_tiles, X3_NW, kSplitBlocks);
+  if (tl.n_tiles <= 0) return hipSuccess;
+  if (tl.n_edges <= 0 || !w.S1 || !w.S2) return hipErrorInvalidValue;
+  const EdgeTiles t = plan_runs(tl, X3_NW * kSplitBlocks);
+  const int g = unit_blocks(walk_n(t), X3_NW, kSplitBlocks);
 #define F(LD)                                                                                                     \
   hipLaunchKernelGGL(k_edge_fwd_x3<LD>, dim3(g), dim3(X3_NT), 0, s, t, (const float*)e_in, (float*)e_out, write_e, \
                      (const float*)Pn, w, eps, agg, slots)
@@ -430,15 +426,17 @@ hipError_t launch_edge_fwd_x3(int lat, const EdgeTiles& t, const void* e_in, voi
 // one block per CU
 static constexpr int kSplitPartBlocks = 256;
 
-hipError_t launch_edge_bwd_x3(int lat, const EdgeTiles& t, const void* e, const float* ebar_in, int have_ebar,
+hipError_t launch_edge_bwd_x3(int lat, const EdgeTiles& tl, const void* e, const float* ebar_in, int have_ebar,
                               float* ebar_out, const void* Pn, const float* aggbar, const MlpW& w, float eps,
                               void* zbar, float* R, float* slots, const Partials& part, int* nblocks, hipStream_t s) {
   *nblocks = 0;
-  if (t.n_tiles <= 0) return hipSuccess;
-  if (t.n_edges <= 0 || part.stride < 2LL * lat * lat + 4 * lat || !w.S1 || !w.S2 || !w.S1t || !w.S2t)
+  if (tl.n_tiles <= 0) return hipSuccess;
+  if (tl.n_edges <= 0 || part.stride < 2LL * lat * lat + 4 * lat || !w.S1 || !w.S2 || !w.S1t || !w.S2t)
     return hipErrorInvalidValue;
   const int nw = lat == 128 ? EdgeBwd<128>::NW : EdgeBwd<160>::NW;
-  const int g = unit_blocks(t.n_tiles, nw, std::min(kSplitPartBlocks, part.max_blocks));
+  const int most = std::min(kSplitPartBlocks, part.max_blocks);
+  const EdgeTiles t = plan_runs(tl, nw * most);
+  const int g = unit_blocks(walk_n(t), nw, most);
   *nblocks = g;
 #define F(LD)                                                                                                  \
   hipLaunchKernelGGL(k_edge_bwd_x3<LD>, dim3(g), dim3(EdgeBwd<LD>::NT), 0, s, t, (const float*)e, ebar_in, have_ebar,    \

@@ -356,19 +356,6 @@ __device__ __forceinline__ void seg_sums(const float* stage, int lane, uint32_t 
   }
 }
 
-// Zero rows of dst for the tile's nodes without in-edges.
-template <int LD>
-__device__ __forceinline__ void zero_empty(int4 d, const int32_t* __restrict__ rowptr, int lane, float* dst) {
-  const int v = min(d.x + lane, d.y - 1);
-  uint64_t m = __ballot(lane < d.y - d.x && rowptr[v] == rowptr[v + 1]);
-  while (m) {
-    const int j = __builtin_ctzll(m);
-    m &= m - 1;
-    float* q = dst + (size_t)(d.x + j) * LD;
-    for (int f = lane; f < LD; f += 64) q[f] = 0.f;
-  }
-}
-
 // Stores the lane's KL values of a row; p points at feature 8 hh of it.
 template <int LD, class F>
 __device__ __forceinline__ void store_row_x3(float* p, F&& get) {
