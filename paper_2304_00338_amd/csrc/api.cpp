@@ -37,7 +37,7 @@ struct Off {
 
 struct PackOff {
   int64_t W1 = -1, W1t = -1, W2 = -1, W2t = -1, W1p = -1, W2p = -1;
-  int64_t F1 = -1, F2 = -1, F1t = -1, F2t = -1;  // fp32 edge MLPs (encoder: W2): fragment-major W1e, W2, transposes
+  int64_t F1 = -1, F2 = -1, F1t = -1, F2t = -1;  // fp32 encoders' W2 and decoder's W1: fragment-major, and transposes
   // fp32 split products: two-piece fp16 fragments (edge MLPs: W1e, W2 and their transposes)
   int64_t S1 = -1, S2 = -1, S1t = -1, S2t = -1;
   int64_t S1a = -1, S1at = -1, S1s = -1, S1r = -1;  // node MLPs: agg block (S1: h block); edge MLPs: sender, receiver block
@@ -163,6 +163,7 @@ Model make_model(int m, int lat, bool fp32 = false) {
   M.p_node.resize(m);
   if (fp32) {
     // fp32 row-layout and split-product kernels: fragment copies only
+    add_split(M, M.enc_edge.W2, D, D, 4, M.p_enc_edge.S2);
     add_frag(M, M.enc_edge.W2, D, D, 2, M.p_enc_edge.F2);
     add_frag(M, M.enc_edge.W2, D, D, 3, M.p_enc_edge.F2t);
     add_split(M, M.enc_node.W2, D, D, 4, M.p_enc_node.S2);
@@ -641,7 +642,7 @@ struct Run {
         LAUNCH(K_EDGE_ENC, launch_edge_enc_rows(E, efeat, W(M.enc_edge, M.p_enc_edge), eps, e_enc(), s));
       else
         LAUNCH(K_EDGE_ENC, prec == MGN_FP32
-                               ? launch_edge_enc_r32(D, E, efeat, W(M.enc_edge, M.p_enc_edge), eps, e_enc(), s)
+                               ? launch_edge_enc_x3(D, E, efeat, W(M.enc_edge, M.p_enc_edge), eps, e_enc(), s)
                                : launch_edge_enc_w160(E, efeat, W(M.enc_edge, M.p_enc_edge), eps, e_enc(), s));
     }
     for (int l = 0; l < m; ++l) {

@@ -1,11 +1,13 @@
-// Edge phase of one MGN message-passing step in fp32 (Sec. 2.1: every edge
-// latent is updated by the edge MLP from itself and its two end nodes, then
-// each node sums the new messages of its in-edges), with one wave per
-// receiver-aligned tile, at kernel width LD = 128 or 160 (latent 150 padded
-// with zero columns).
-//
-// The lane layout and the product routine (gemm32) are those of
-// rows32_common.hpp.
+// Reverse of the fp32 edge encoder e = LN(W2 relu(W1 f + b1) + b2) (Sec. 2.1: the
+// edge features are encoded to the latent width by an MLP with LayerNorm), at
+// kernel width LD = 128 or 160 (latent 150 padded with zero columns), one wave
+// per 16-edge unit.  The lane layout and the product routine (gemm32) are those
+// of rows32_common.hpp.  The first layer (K = 4) runs on VALU as one fma chain per
+// feature from b1, k = 0..3, as in the forward (enc_split32.hip); the second layer
+// is gemm32 on the fragment-major W2 and its transpose from L2.
+//   The same reverse on split fp16 products with 32-edge units took 0.34 ms
+// instead of 0.50 at 434,558 edges and width 128, but 36 us instead of 26 at 11,260
+// edges (a longer chain per unit) and as long at width 160 (spills).
 #include "rows32_common.hpp"
 #include "w160_common.hpp"
 
@@ -15,14 +17,6 @@ namespace dev {
 
 constexpr int B32_ROWS = 16 * R32_NW;
 
-// ========================================================= edge encoder
-// The edge encoder e = LN(W2 relu(W1 f + b1) + b2) (Sec. 2.1: the edge
-// features are encoded to the latent width by an MLP with LayerNorm) in this
-// row layout, forward and reverse.  The first layer (K = 4) runs on VALU as
-// one fma chain per feature from b1, k = 0..3, identical in both kernels, so
-// the reverse recomputes the forward's values bitwise; the second layer is
-// gemm32 on the fragment-major W2 (in LDS in the forward, from L2 in the
-// reverse, whose LDS holds the staged rows).
 constexpr int EK = 4;  // edge input features
 
 // z[s] = b1[f0 + s] + W1[f0 + s] . x, the lane's KL features (w1 holds each
@@ -58,71 +52,6 @@ __device__ __forceinline__ void stage_enc_vec(EncVec32<LD>& V, const MlpW& w, in
     V.b2[f] = w.b2[f];
     V.g[f] = w.gamma[f];
     V.bt[f] = w.beta[f];
-  }
-}
-
-template <int LD>
-struct __attribute__((aligned(16))) EncFwd32Lds {
-  EncVec32<LD> V;
-  __attribute__((aligned(16))) float w2[LD * LD];  // fragment-major W2
-};
-
-// Forward: one wave per 16-edge unit, no block barrier in the loop; the
-// next unit's inputs are in flight while one is computed.
-template <int LD>
-__global__ void __launch_bounds__(R32_NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_edge_enc_r32(int64_t E, const float* __restrict__ f_in, MlpW w, float eps, float* __restrict__ e_out) {
-  typedef R32<LD> Z;
-  __shared__ __align__(16) EncFwd32Lds<LD> S;
-  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int idx = tid; idx < LD * LD / 4; idx += R32_NT)
-    reinterpret_cast<f32x4*>(S.w2)[idx] = reinterpret_cast<const f32x4*>(w.F2)[idx];
-  stage_enc_vec<LD>(S.V, w, tid);
-  __syncthreads();
-  const int64_t nu = (E + 15) >> 4;
-  const UnitRange ur = unit_range<R32_NW>(nu, wv);
-  if (ur.t >= ur.end) return;
-  const int f0 = Z::KL * g;
-  // rows clamped into [0, E): rows past E read row E - 1 and store nothing
-  auto load = [&](int64_t u) { return *reinterpret_cast<const float4*>(f_in + min(u * 16 + i, E - 1) * EK); };
-  float4 fa = load(ur.t);
-  for (int64_t u = ur.t; u < ur.end; u += ur.stride) {
-    const float4 fn = load(u + ur.stride);
-    // LDS reads through an opaque reference: otherwise the loop-invariant
-    // weight reads are hoisted out of the loop into (far too many) registers
-    const EncFwd32Lds<LD>& L = fresh(S);
-    float a1[Z::KL];
-    enc_z1_r32<LD>(L.V.w1, L.V.b1, fa, f0, a1);
-#pragma unroll
-    for (int s = 0; s < Z::KL; ++s) a1[s] = relu(a1[s]);
-    f32x4 acc[Z::NOB];
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = *reinterpret_cast<const f32x4*>(L.V.b2 + f0 + 4 * ob);
-    gemm32<LD>(acc, a1, L.w2, lane);
-    // ---- LayerNorm over the row's DR real features (padded ones are 0)
-    float sm = 0.f;
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sm += acc[ob][r];
-    const float mean = sum_q(sm) * (1.0f / Z::DR);
-    float sq = 0.f;
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float dlt = acc[ob][r] - mean;
-        acc[ob][r] = dlt;
-        if (Z::DR == LD || f0 + 4 * ob + r < Z::DR) sq += dlt * dlt;
-      }
-    const float rstd = __builtin_amdgcn_rsqf(sum_q(sq) * (1.0f / Z::DR) + eps);
-#pragma unroll
-    for (int ob = 0; ob < Z::NOB; ++ob)
-      acc[ob] = *reinterpret_cast<const f32x4*>(L.V.g + f0 + 4 * ob) * (acc[ob] * rstd) +
-                *reinterpret_cast<const f32x4*>(L.V.bt + f0 + 4 * ob);
-    if (u * 16 + i < E) store_row32<LD>(e_out + (size_t)(u * 16 + i) * LD + f0, acc);
-    fa = fn;
   }
 }
 
@@ -393,18 +322,6 @@ k_edge_enc_bwd_r32(int64_t E, const float* __restrict__ f_in, const float* __res
 using namespace dev;
 
 static constexpr int kRows32Blocks = 256;
-
-hipError_t launch_edge_enc_r32(int lat, int64_t E, const float* f, const MlpW& w, float eps, void* e_out,
-                               hipStream_t s) {
-  if (E <= 0) return hipSuccess;
-  if (!w.F2) return hipErrorInvalidValue;
-  const int g = unit_blocks((E + 15) / 16, R32_NW, kRows32Blocks);
-#define F(LD) \
-  hipLaunchKernelGGL(k_edge_enc_r32<LD>, dim3(g), dim3(R32_NT), 0, s, E, f, w, eps, (float*)e_out)
-  MGN_BY_WIDTH(lat, F);
-#undef F
-  return hipGetLastError();
-}
 
 hipError_t launch_edge_enc_bwd_r32(int lat, int64_t E, const float* f, const void* ebar, const MlpW& w, float eps,
                                    const Partials& part, int* nblocks, hipStream_t s) {

@@ -269,7 +269,7 @@ hipError_t launch_node_enc(int prec, int lat, int64_t N, const float* x, const M
   const int g = grid_for((N + TM - 1) / TM, kFwdBlocks);
   if (!g) return hipSuccess;
   const MlpW nn = nx ? *nx : w;
-  // bf16 (fp32 runs on launch_node_enc_r32)
+  // bf16 (fp32 runs on launch_node_enc_x3)
   if (prec != MGN_BF16) return hipErrorInvalidValue;
 #define F(LD)                                                                                                        \
   if (nx)                                                                                                            \

@@ -157,10 +157,6 @@ hipError_t launch_pack_split(const float* params, void* pack, const PackList& L,
 // widths.
 hipError_t launch_node_enc(int prec, int lat, int64_t N, const float* node_in, const MlpW& w, const MlpW* next_edge,
                            float eps, float* h_out, void* P_out, hipStream_t s);
-// fp32 edge encoder in the row layout (width 128 or 160; needs the
-// fragment-major W2 and, for the reverse, its transpose): e = LN(W2 relu(W1
-// f + b1) + b2), and all encoder parameter gradients from ebar as per-block
-// partials in the encoder's parameter order.
 // fp32 node phase (width 128 or 160; needs the node MLP's S1, S1a, S2 and,
 // with nx, the next edge MLP's S1s, S1r):
 // h_out = h + LN(W2 relu(W1 [h, agg] + b1) + b2), and with nx the next
@@ -198,7 +194,10 @@ hipError_t launch_node_enc_x3(int lat, int64_t N, const float* x, const MlpW& w,
                                float* h_out, float* P_out, hipStream_t s);
 hipError_t launch_node_enc_bwd_r32(int lat, int64_t N, const float* x, const float* ybar, const MlpW& w, float eps,
                                    float* gin, float* streams, const Partials& part, int* nblocks, hipStream_t s);
-hipError_t launch_edge_enc_r32(int lat, int64_t E, const float* f, const MlpW& w, float eps, void* e_out,
+// fp32 edge encoder (width 128 or 160; the forward needs S2, the reverse F2 and
+// F2t): e = LN(W2 relu(W1 f + b1) + b2), and all encoder parameter gradients from
+// ebar as per-block partials in the encoder's parameter order.
+hipError_t launch_edge_enc_x3(int lat, int64_t E, const float* f, const MlpW& w, float eps, void* e_out,
                                hipStream_t s);
 hipError_t launch_edge_enc_bwd_r32(int lat, int64_t E, const float* f, const void* ebar, const MlpW& w, float eps,
                                    const Partials& part, int* nblocks, hipStream_t s);

@@ -1,13 +1,9 @@
-// Node phase of one MGN message-passing step in fp32 (Sec. 2.1: every node
-// latent is updated by the node MLP from itself and the sum of its incoming
-// edge messages, with LayerNorm and a residual), in the fp32 row layout of
-// rows32_common.hpp at kernel width LD = 128 or 160 (latent 150 padded with
-// zero columns): one wave per 16-node unit, the four lanes of a node holding
-// its contiguous row, every product on gemm32 from fragment-major weights.
-//
-// The first layer acts on the concatenation [h, agg]; it is evaluated as
-// (b1 + W1h h) + W1a agg with the two column blocks of W1 (the same linear
-// map, in this summation order in the forward and the reverse's recompute).
+// fp32 node-level kernels around the MP steps (Sec. 2.1): sender-side sums of the
+// edge reverse, the decoder and its reverse, and the node encoder's reverse, in
+// the fp32 row layout of rows32_common.hpp at kernel width LD = 128 or 160 (latent
+// 150 padded with zero columns): one wave per 16-node unit, the four lanes of a
+// node holding its contiguous row, every product on gemm32 from fragment-major
+// weights.
 #include "rows32_common.hpp"
 
 namespace mgn {
@@ -183,7 +179,7 @@ k_decoder_r32(int64_t N, const float* __restrict__ h_in, MlpW w, float* __restri
 
 // Decoder reverse from gout = dL/dout [N][4]: hbar = W1^T dz1 (written),
 // dz1 = (W2^T gout) where z1 > 0; the dz1 rows go to dz1s for dW1 = sum
-// dz1^T h (launch_wgrad_r32); db1, dW2 = sum gout a1^T and db2 = sum gout
+// dz1^T h (launch_wgrad_x3); db1, dW2 = sum gout a1^T and db2 = sum gout
 // as column sums, written per block in the decoder's parameter order after
 // W1: [LD] db1, [4][LD] dW2, [4] db2.
 template <int LD>
@@ -319,7 +315,7 @@ __device__ __forceinline__ void node_enc_z1(const NodeEncVec<LD>& V, float4 xa, 
 // Reverse from ybar = dL/dh0: the forward recomputed (z1 bitwise), the
 // LayerNorm reverse, dz1 = (W2^T dz2) where z1 > 0, gin = W1^T dz1 (when gin
 // is given, [N][8]); the a1 and dz2 rows go to a1s / dz2s for dW2 (by
-// launch_wgrad_r32); dW1 = sum dz1 x^T, db1, db2, dgamma, dbeta as column
+// launch_wgrad_x3); dW1 = sum dz1 x^T, db1, db2, dgamma, dbeta as column
 // sums, written per block in the encoder's parameter order with W2 left out:
 // [LD][8] dW1, [LD] db1, then [LD] db2, dgamma, dbeta.
 template <int LD>
