@@ -43,7 +43,7 @@ struct PackOff {
   int64_t S1a = -1, S1at = -1, S1s = -1, S1r = -1;  // node MLPs: agg block (S1: h block); edge MLPs: sender, receiver block
   int64_t W1sp = -1, W1rp = -1;  // edge MLPs: row-permuted sender / receiver column blocks of W1
   int64_t W1ap = -1;             // node MLPs at width 160: row-permuted agg column block of W1
-  int64_t F1st = -1, F1rt = -1;  // fp32 sender sums: edge MLPs' W1 sender / receiver blocks, transposed
+  int64_t S1st = -1, S1rt = -1;  // edge MLPs: their transposes (sender sums)
 };
 
 struct Model {
@@ -176,8 +176,8 @@ Model make_model(int m, int lat, bool fp32 = false) {
       add_split(M, M.edge[i].W2, D, D, 5, M.p_edge[i].S2t);
       add_split(M, M.edge[i].W1 + D, 3 * D, D, 4, M.p_edge[i].S1s);
       add_split(M, M.edge[i].W1 + 2 * D, 3 * D, D, 4, M.p_edge[i].S1r);
-      add_frag(M, M.edge[i].W1 + D, 3 * D, D, 3, M.p_edge[i].F1st);
-      add_frag(M, M.edge[i].W1 + 2 * D, 3 * D, D, 3, M.p_edge[i].F1rt);
+      add_split(M, M.edge[i].W1 + D, 3 * D, D, 5, M.p_edge[i].S1st);
+      add_split(M, M.edge[i].W1 + 2 * D, 3 * D, D, 5, M.p_edge[i].S1rt);
       add_split(M, M.node[i].W1, 2 * D, D, 4, M.p_node[i].S1);
       add_split(M, M.node[i].W1 + D, 2 * D, D, 4, M.p_node[i].S1a);
       add_split(M, M.node[i].W2, D, D, 4, M.p_node[i].S2);
@@ -572,8 +572,8 @@ struct Run {
     w.F2 = p.F2 >= 0 ? (const float*)P(p.F2) : nullptr;
     w.F1t = p.F1t >= 0 ? (const float*)P(p.F1t) : nullptr;
     w.F2t = p.F2t >= 0 ? (const float*)P(p.F2t) : nullptr;
-    w.F1st = p.F1st >= 0 ? (const float*)P(p.F1st) : nullptr;
-    w.F1rt = p.F1rt >= 0 ? (const float*)P(p.F1rt) : nullptr;
+    w.S1st = p.S1st >= 0 ? P(p.S1st) : nullptr;
+    w.S1rt = p.S1rt >= 0 ? P(p.S1rt) : nullptr;
     w.W1f = params + o.W1;
     w.W2f = params + o.W2;
     w.b1 = params + o.b1;
@@ -828,7 +828,7 @@ struct Run {
         // now), then dW1s = sum S h^T and dW1r = sum R h^T from the rows, and
         // dW1e
         float* Sv = (float*)(ws + c.L.nstr);
-        LAUNCH(K_SRCSUM, launch_node_srcsum_r32(D, N, g.rowptr, g.rev, (const float*)zbar, R, hb_part,
+        LAUNCH(K_SRCSUM, launch_node_srcsum_x3(D, N, g.rowptr, g.receivers, g.rev, (const float*)zbar, R, hb_part,
                                                 W(oe, M.p_edge[l]), hb_cur, Sv, s));
         wq.n = 0;
         wgrad(Sv, h_l(k, l), N, 4, 0);

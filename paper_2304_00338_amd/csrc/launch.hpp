@@ -24,8 +24,6 @@ struct MlpW {
   const float* F2;   // decoder's W1 and the encoders' W2, and of their transposes
   const float* F1t;
   const float* F2t;
-  const float* F1st;  // fp32 edge MLPs: transposed sender / receiver blocks of W1
-  const float* F1rt;
   const void* S1;    // fp32 split products (pack modes 4, 5): two-piece fp16
   const void* S2;    // fragments of the MLP's W1 (edge: W1e) and W2, and of their
   const void* S1t;   // transposes
@@ -34,6 +32,8 @@ struct MlpW {
   const void* S1at;
   const void* S1s;   // edge MLPs: W1's sender and receiver blocks
   const void* S1r;
+  const void* S1st;  // and their transposes
+  const void* S1rt;
   const float* W1f;  // float32 first-layer weights (encoders: K = 4 / 8 on VALU)
   const float* W2f;  // float32 second-layer weights (decoder: 4 outputs on VALU)
   const float* b1;
@@ -170,12 +170,12 @@ hipError_t launch_node_fwd_x3(int lat, int64_t N, const float* h_in, const float
 hipError_t launch_node_bwd_x3(int lat, int64_t N, const float* h, const float* agg, const float* hbar_in,
                                const MlpW& w, float eps, float* hbar_part, float* aggbar, float* streams,
                                const Partials& part, int* nblocks, hipStream_t s);
-// fp32 sender-side sums in the row layout (needs the edge MLP's F1st, F1rt):
-// S = sum of zbar over each node's out-edges (through rev, in edge order)
-// into S_out ([N][lat]), hbar_out = hbar_part + W1s^T S + W1r^T R.
-hipError_t launch_node_srcsum_r32(int lat, int64_t N, const int32_t* rowptr, const int32_t* rev, const float* zbar,
-                                  const float* R, const float* hbar_part, const MlpW& w, float* hbar_out,
-                                  float* S_out, hipStream_t s);
+// fp32 sender-side sums (needs the edge MLP's S1st, S1rt): S = sum of zbar over
+// each node's out-edges (through rev, in edge order) into S_out ([N][lat]),
+// hbar_out = hbar_part + W1s^T S + W1r^T R.
+hipError_t launch_node_srcsum_x3(int lat, int64_t N, const int32_t* rowptr, const int32_t* receivers,
+                                 const int32_t* rev, const float* zbar, const float* R, const float* hbar_part,
+                                 const MlpW& w, float* hbar_out, float* S_out, hipStream_t s);
 // fp32 decoder in the row layout (needs the decoder's fragment-major F1 and,
 // for the reverse, F1t): out = W2 relu(W1 h + b1) + b2 ([N][4]); the
 // reverse writes hbar = W1^T dz1, the dz1 rows (for dW1 by launch_wgrad_x3)

@@ -1,7 +1,7 @@
 // Node phase of one MGN message-passing step in fp32 (Sec. 2.1: every node
 // latent is updated by the node MLP from itself and the sum of its incoming
-// edge messages, with LayerNorm and a residual) and the node encoder's
-// forward, on the split fp16 products of split32_common.hpp: one wave per
+// edge messages, with LayerNorm and a residual), the sender sums of the edge
+// reverse and the node encoder's forward, on the split fp16 products of split32_common.hpp: one wave per
 // 32-node unit, four waves per block, two blocks per CU.
 //   Bound by the latency of a unit's chain of products where there are fewer
 // units than waves (32,768 nodes are one unit per SIMD); reading every weight
@@ -315,6 +315,135 @@ k_node_enc_x3(int64_t N, const float* __restrict__ x_in, MlpW w, MlpW nx, float 
   }
 }
 
+// Sender-side sums and the node gradient through the edge MLP's sender and
+// receiver blocks: S_v = sum of zbar over the reverses of v's in-edges (the
+// out-edges of v), added in edge order from 0.0; hbar_out = hbar_part + W1s^T S +
+// W1r^T R.  The rows of S go to S_out (fp32 [N][LD]) for the weight gradients dW1s =
+// sum S h^T, dW1r = sum R h^T.
+//   Bound by the gather of E rows.  A wave reads whole rows (its unit's reversed
+// edge ids are one contiguous piece of rev), RB in flight, and hands each node's
+// sum to the node's two lanes through LDS, SN nodes at a time; with a quarter of
+// a row per lane, as before, every 16-byte access of a wave spanned 64 cache
+// lines.  Measured per launch (fp32 MFMA version -> this): 434,558 edges and 32,768
+// nodes at width 128 90 -> 75 us (reading the rows takes 47 at the copy rate; more
+// rows in flight made no difference), the eight-patch batch at width 160 203 -> 187
+// us, 11,260 edges 21.0 -> 20.8 us (ids and bounds requested per pass: 22.5).
+template <int LD>
+struct __attribute__((aligned(16))) SrcSumLds {
+  static constexpr int SN = LD == 128 ? 16 : 8;  // (two blocks share the LDS)
+  static constexpr int SL = LD + 4;
+  u32x4 w[2][X3<LD>::CH];
+  __attribute__((aligned(16))) float stage[X3_NW][SN * SL];
+};
+
+template <int LD>
+__global__ void __launch_bounds__(X3_NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_node_srcsum_x3(int64_t N, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ receivers,
+                 const int32_t* __restrict__ rev, const float* __restrict__ zbar, const float* R,
+                 const float* hbar_part, MlpW w, float* hbar_out, float* S_out) {
+  typedef X3<LD> Z;
+  typedef SrcSumLds<LD> Lds;
+  constexpr int RB = LD == 128 ? 32 : 16;  // rows in flight
+  constexpr int NP = LD / 2;               // feature pairs of a row
+  __shared__ Lds S;
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const u32x4 *Ws = (const u32x4*)w.S1st, *Wr = (const u32x4*)w.S1rt;
+  const BlockRange br = block_range((N + 31) >> 5);
+  if (br.tb >= br.tend) return;
+  gemm_x3_start<LD>(Ws, S.w, tid);
+  const int ws = weight_exp<LD>(Ws), wr = weight_exp<LD>(Wr);
+  __syncthreads();
+  for (int64_t t = br.tb; t < br.tend; t += br.stride) {
+    const int lane = (tid & 63) + opaque_zero(), row = lane & 31, hh = lane >> 5;
+    const int64_t v0 = min((t + wv) * 32, N);  // the unit's first node (N: no unit)
+    const bool live = t + wv < br.tend && v0 + row < N;
+    const size_t o = (size_t)min(v0 + row, N - 1) * LD + 8 * hh;
+    float* st = S.stage[wv];
+    float x[Z::KL];
+    // the first edges of every SN nodes; no edges past the range
+    const int rp = t + wv < br.tend ? rowptr[min(v0 + min(lane, 32 / Lds::SN) * Lds::SN, N)] : 0;
+    const int ulast = __builtin_amdgcn_readlane(rp, 32 / Lds::SN) - 1;
+    // reversed edge ids and receivers of the next 64 rows, requested a batch ahead
+    int id = 0, rc = 0;
+    auto ids = [&](int b) {
+      if (b <= ulast) {
+        id = rev[min(b + lane, ulast)];
+        rc = receivers[min(b + lane, ulast)];
+      }
+    };
+    ids(__builtin_amdgcn_readlane(rp, 0));
+    load_row_x3<LD>(x, R + o);
+    const int er = row_exp<LD>(x);
+#pragma unroll 1
+    for (int p = 0; p < 32 / Lds::SN; ++p) {
+      const int lo = __builtin_amdgcn_readlane(rp, p), hi = __builtin_amdgcn_readlane(rp, p + 1), last = hi - 1;
+      const int va = (int)v0 + p * Lds::SN;
+#pragma unroll
+      for (int u = 0; u < Lds::SN; ++u) {  // nodes without edges
+        *reinterpret_cast<float2*>(st + u * Lds::SL + 2 * lane) = float2{0.f, 0.f};
+        if (NP > 64 && lane < NP - 64) *reinterpret_cast<float2*>(st + u * Lds::SL + 2 * (lane + 64)) = float2{0.f, 0.f};
+      }
+      float2 c0 = {0.f, 0.f}, c1 = {0.f, 0.f};
+      for (int b = lo; b < hi; b += RB) {
+        float2 z0[RB], z1[RB];
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+          const float* q = zbar + (size_t)__builtin_amdgcn_readlane(id, u) * LD;
+          z0[u] = *reinterpret_cast<const float2*>(q + 2 * lane);
+          if (NP > 64) z1[u] = *reinterpret_cast<const float2*>(q + 2 * (lane < NP - 64 ? lane + 64 : lane));
+        }
+        // row u ends its node's segment
+        const int nx = __shfl(rc, min(lane + 1, 63));
+        const uint64_t ends = __ballot(b + lane == last || (b + lane < last && nx != rc));
+        const int node = rc - va;
+        ids(min(b + RB, hi));
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+          c0.x += z0[u].x;
+          c0.y += z0[u].y;
+          if (NP > 64) {
+            c1.x += z1[u].x;
+            c1.y += z1[u].y;
+          }
+          if ((ends >> u) & 1u) {
+            float* q = st + __builtin_amdgcn_readlane(node, u) * Lds::SL;
+            *reinterpret_cast<float2*>(q + 2 * lane) = c0;
+            if (NP > 64 && lane < NP - 64) *reinterpret_cast<float2*>(q + 2 * (lane + 64)) = c1;
+            c0 = c1 = float2{0.f, 0.f};
+          }
+        }
+      }
+      wave_lds_sync();
+      if (row / Lds::SN == p) load_row_x3<LD>(x, st + (row % Lds::SN) * Lds::SL + 8 * hh);
+      wave_lds_sync();
+    }
+    if (live) store_row_x3<LD>(S_out + o, [&](int v) { return x[v]; });
+    // both products add into one accumulator at one scale (see node_z1_x3)
+    f32x16 acc[Z::NOB];
+    const int T = min(row_exp<LD>(x) + ws, er + wr);
+    gemm_raw<LD, X3_NT, false>(acc, [&](int ks) { return split8(x + 8 * ks, T - ws); }, Ws, Wr, S.w, 0, tid,
+                               [&](int ks) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(R + o + 16 * ks + 4 * j);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[8 * ks + 4 * j + r] = u[r];
+      }
+    });
+    gemm_raw<LD, X3_NT, true>(acc, [&](int ks) { return split8(x + 8 * ks, T - wr); }, Wr, Ws, S.w, Z::NC & 1, tid,
+                              [&](int ks) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(hbar_part + o + 16 * ks + 4 * j);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[8 * ks + 4 * j + r] = u[r];
+      }
+    });
+    scale_acc<LD>(acc, -T);
+    if (live) store_row_x3<LD>(hbar_out + o, [&](int v) { return x[v] + acc[v >> 4][v & 15]; });
+  }
+}
+
 }  // namespace dev
 
 using namespace dev;
@@ -357,6 +486,20 @@ hipError_t launch_node_bwd_x3(int lat, int64_t N, const float* h, const float* a
 #define F(L)                                                                                                      \
   hipLaunchKernelGGL(k_node_bwd_x3<L>, dim3(g), dim3(X3_NT), 0, s, N, h, agg, hbar_in, w, eps, hbar_part, aggbar, \
                      a1s, dz2s, dz1s, part)
+  MGN_BY_WIDTH(lat, F);
+#undef F
+  return hipGetLastError();
+}
+
+hipError_t launch_node_srcsum_x3(int lat, int64_t N, const int32_t* rowptr, const int32_t* receivers,
+                                 const int32_t* rev, const float* zbar, const float* R, const float* hbar_part,
+                                 const MlpW& w, float* hbar_out, float* S_out, hipStream_t s) {
+  if (N <= 0) return hipSuccess;
+  if ((lat != 128 && lat != 160) || !w.S1st || !w.S1rt) return hipErrorInvalidValue;
+  const int g = node_blocks(N, kNodeSplitBlocks);
+#define F(L)                                                                                                       \
+  hipLaunchKernelGGL(k_node_srcsum_x3<L>, dim3(g), dim3(X3_NT), 0, s, N, rowptr, receivers, rev, zbar, R, hbar_part, \
+                     w, hbar_out, S_out)
   MGN_BY_WIDTH(lat, F);
 #undef F
   return hipGetLastError();

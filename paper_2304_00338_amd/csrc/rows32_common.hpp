@@ -1,4 +1,4 @@
-// The fp32 row layout shared by the fp32 sender sums, decoder and encoder reverses, at kernel
+// The fp32 row layout shared by the fp32 decoder and encoder reverses, at kernel
 // width LD = 128 or 160 (latent 150 padded with zero columns).
 //
 // Lane layout.  Lane l (i = l & 15, g = l >> 4) holds row i of a 16-row
