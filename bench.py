@@ -41,27 +41,26 @@ def log(*a):
 # waves' three 128 x 128 products (W2 a1 recomputed, W2^T dz2, W1e^T zbar),
 # the gradient waves' dW2 = dz2^T a1 and dW1e = zbar^T e, and their ones
 # columns (8 MFMAs per 64-row round and gradient wave, 4 waves).
-# fp32 row-layout kernels (v_mfma_f32_16x16x4_f32, 2,048 flop each): the
-# forward's two 128 x 128 products (W1e e, W2 a1); the fused backward's four
-# (W1e e and W2 a1 recomputed, W2^T dz2, W1e^T zbar), dW2 and dW1e, and the
-# ones columns of db2 / db1 (64 MFMAs per 64-row round and wave, 4 waves).
+# fp32 kernels: every product is three fp16 products (v_mfma_f32_32x32x16_f16)
+# of two-piece operands: the forward's W1e e and W2 a1; the reverse's four (W1e e
+# and W2 a1 recomputed, W2^T dz2, W1e^T zbar) and dW2 (dW1e is a pass of its own).
 MFMA_FLOP_PER_EDGE = {"bf16": {"edge_fwd": 2 * 128 * 128 * 2 + 24 * 16384 // 16,
                                "edge_bwd": 5 * 2 * 128 * 128 + 4 * 8 * 16384 // 64},
-                      "fp32": {"edge_fwd": 2 * 2 * 128 * 128,
-                               "edge_bwd": 6 * 2 * 128 * 128 + 4 * 64 * 2048 // 64}}
-MFMA_PEAK_BF16_TFLOPS = 2500.0
-MFMA_PEAK_FP32_TFLOPS = 157.3
+                      "fp32": {"edge_fwd": 3 * 2 * 2 * 128 * 128,
+                               "edge_bwd": 3 * 5 * 2 * 128 * 128}}
+MFMA_PEAK_TFLOPS = 2500.0  # 16-bit, dense
 
 
 def edge_bwd_split_roofline(prec, D, N, E, m, avg_ms):
     """Position of the edge backward at latent width D (one launch per MP
     block) against both roofs: algorithmic bytes and executed MFMA flop per
     launch, each divided by the average launch time.
-    fp32 (row-layout kernel at width 160): per edge e, the incoming edge
+    fp32 (width 160): per edge e, the incoming edge
     gradient (not in the last block), the outgoing one and z-bar (fp32),
     sender / receiver ids; per node P, the gathered aggregate gradient and
     R; 5 products of D x D per edge (the recomputed W1e e and W2 a1, W2^T
-    dz2, W1e^T zbar and the dW2 accumulation; dW1e is a separate pass).
+    dz2, W1e^T zbar and the dW2 accumulation; dW1e is a separate pass), each
+    as three fp16 products.
     bf16 (row-per-wave kernel): per edge the saved a1, the incoming edge
     gradient (not in the last block), the outgoing one, zbar and dz2 (bf16),
     the receiver id; per node the gathered aggregate gradient and R (fp32);
@@ -70,20 +69,18 @@ def edge_bwd_split_roofline(prec, D, N, E, m, avg_ms):
         per_edge = [D * 2 + (D * 2 if l < m - 1 else 0) + 3 * D * 2 + 4 for l in range(m)]
         per_node = 2 * D * 4
         flop = 6.0 * D * D * E
-        peak = MFMA_PEAK_BF16_TFLOPS
     else:
         per_edge = [D * 4 + (D * 4 if l < m - 1 else 0) + D * 4 + D * 4 + 8 for l in range(m)]
         per_node = 2 * D * 4 + D * 4 + D * 4
-        flop = 10.0 * D * D * E
-        peak = MFMA_PEAK_FP32_TFLOPS
+        flop = 3 * 10.0 * D * D * E
     nbytes = float(np.mean(per_edge)) * E + N * per_node
     gbs = nbytes / (avg_ms * 1e-3) / 1e9
     tfs = flop / (avg_ms * 1e-3) / 1e12
     return {"kernel": "edge_bwd", "avg_launch_ms": round(avg_ms, 4),
             "hbm": {"algorithmic_bytes_per_launch": int(nbytes), "achieved_gbs": round(gbs, 1),
                     "frac": round(gbs / HBM_PEAK_GBS, 4)},
-            "mfma": {"flop_per_launch": int(flop), "achieved_tflops": round(tfs, 1), "peak_tflops": peak,
-                     "frac": round(tfs / peak, 4)}}
+            "mfma": {"flop_per_launch": int(flop), "achieved_tflops": round(tfs, 1), "peak_tflops": MFMA_PEAK_TFLOPS,
+                     "frac": round(tfs / MFMA_PEAK_TFLOPS, 4)}}
 
 
 def kernel_bytes(kind, N, E, n_tiles, prec, have_ebar=True, write_e=True, keep_a1=True, method=False):
@@ -153,7 +150,7 @@ def step_bytes(kind, N, E, n_tiles, prec, m, method=False):
 
 # Device sources of each profiled kernel: its own file and the device
 # headers it includes (launch.hpp only declares host launchers).
-KERNEL_SOURCES = {"edge_bwd": ("edge_rows.hip", "rows_common.hpp", "dev_common.hpp")}
+KERNEL_SOURCES = {"edge_bwd": ("edge_rows.hip", "edge_walk.hpp", "rows_common.hpp", "dev_common.hpp")}
 # The kernel symbol a profiled kernel kind runs as on the benchmark patch
 # (bf16): the fp32 kernel of the same kind must not be taken for it.
 KERNEL_SYMBOL = {"edge_bwd": "k_edge_bwd_fused", "edge_fwd": "k_edge_fwd_rows"}
@@ -246,7 +243,7 @@ def summarize_profile(d, kernel):
             if mops.get(k):
                 tf = mops[k] * 512 / 1e12
                 rate = tf / (avg_ms[k] * 1e-3)
-                print(f"| {k} | {tf:.3f} | {rate:.0f} | {100 * rate / MFMA_PEAK_BF16_TFLOPS:.1f} |")
+                print(f"| {k} | {tf:.3f} | {rate:.0f} | {100 * rate / MFMA_PEAK_TFLOPS:.1f} |")
     # wave-state counters (passes of at most four counters each): per-launch
     # averages, as fractions of the waves' lifetime (SQ_WAVE_CYCLES)
     sq = {}
@@ -502,14 +499,14 @@ def mesh_run(mgn, M, g, m, prec, scheme="euler", reps=5, warmup=2, profile=False
 
 
 def mfma_roofline(prof, prec, E, reps):
-    """The dominant kernel of a profiled fwd+bwd run placed against the MFMA
-    roof of its precision: executed MFMA flop per launch (per-edge count of
+    """The dominant kernel of a profiled fwd+bwd run placed against the 16-bit
+    MFMA roof: executed MFMA flop per launch (per-edge count of
     MFMA_FLOP_PER_EDGE times E) / its average launch time."""
     dom = max(prof, key=lambda k: prof[k][0])
     tot, cnt = prof[dom]
     avg = tot / cnt
     fpe = MFMA_FLOP_PER_EDGE[prec].get(dom)
-    peak = MFMA_PEAK_FP32_TFLOPS if prec == "fp32" else MFMA_PEAK_BF16_TFLOPS
+    peak = MFMA_PEAK_TFLOPS
     r = {"bound": "mfma", "kernel": dom, "avg_launch_ms": round(avg, 4), "launches_per_step": cnt // reps,
          "peak": peak, "unit": "TFLOP/s"}
     if fpe is not None:
@@ -878,8 +875,8 @@ def main():
         fl = MFMA_FLOP_PER_EDGE[args.precision][dom] * E
         out["mfma"] = {"kernel": dom, "executed_flop_per_launch": fl,
                        "achieved_tflops": round(fl / (avg_ms * 1e-3) / 1e12, 1),
-                       "peak_tflops": MFMA_PEAK_BF16_TFLOPS,
-                       "frac": round(fl / (avg_ms * 1e-3) / 1e12 / MFMA_PEAK_BF16_TFLOPS, 4)}
+                       "peak_tflops": MFMA_PEAK_TFLOPS,
+                       "frac": round(fl / (avg_ms * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS, 4)}
     out["train_step"] = train_steps(S, args)
     if not args.no_relabelled:
         out["c3_relabelled"] = c3_relabelled(S, args)

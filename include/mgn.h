@@ -54,7 +54,7 @@ extern "C" {
 #define MGN_ERR_NOMEM (-7)     /* host allocation failed */
 
 /* ---- enums ----------------------------------------------------------- */
-#define MGN_FP32 0 /* fp32 MFMA, fp32 latent streams */
+#define MGN_FP32 0 /* fp32 latent streams, products at fp32 accuracy */
 #define MGN_BF16 1 /* bf16 MFMA operands, bf16 edge-latent stream, fp32
                       accumulation, LayerNorm statistics, sums and node state */
 
