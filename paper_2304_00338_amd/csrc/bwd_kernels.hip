@@ -479,7 +479,7 @@ hipError_t launch_decoder_bwd(int prec, int lat, int64_t N, const float* h, cons
 hipError_t launch_node_srcsum(int prec, int lat, int64_t N, const int32_t* rowptr, const int32_t* rev,
                               const void* zbar, const float* R, const float* h, const float* hbar_part, const MlpW& w,
                               float* hbar_out, const Partials& part, int* nblocks, hipStream_t s) {
-  // bf16 at width 128 (fp32 runs on launch_node_srcsum_r32, bf16 at width
+  // bf16 at width 128 (fp32 runs on launch_node_srcsum_x3, bf16 at width
   // 160 on launch_srcsum_w160)
   *nblocks = 0;
   if (prec != MGN_BF16 || lat != 128) return hipErrorInvalidValue;
