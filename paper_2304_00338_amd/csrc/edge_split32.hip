@@ -40,6 +40,8 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
   const int f0 = 8 * hh;  // the lane's first feature
   const u32x4 *W1 = (const u32x4*)w.S1, *W2 = (const u32x4*)w.S2;
   const BlockRange br = block_range(walk_units(tl));
+  // the nodes are dealt to all blocks, those without a run among them
+  if (tl.run) zero_share<LD>(tl, (int64_t)blockIdx.x * X3_NW + wv, (int64_t)gridDim.x * X3_NW, lane, agg);
   if (br.tb >= br.tend) return;
   gemm_x3_start<LD>(W1, S.w, tid);
   for (int f = tid; f < LD; f += X3_NT) {
@@ -53,7 +55,6 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
   EdgeSteps es;
   int4 d = es.first(tl, br.tb + wv, br.stride, br.tend);
   int snd = tl.senders[erow(d)], rcv = tl.receivers[erow(d)];
-  if (tl.run) zero_share<LD>(tl, (int64_t)blockIdx.x * X3_NW + wv, (int64_t)gridDim.x * X3_NW, lane, agg);
   __syncthreads();
   float2 carry[2] = {{0.f, 0.f}, {0.f, 0.f}};  // the open segment's sum
   const int n_steps = walk_steps(tl);

@@ -144,6 +144,28 @@ inline int unit_blocks(int64_t n, int nw, int most) {
   return (int)(g < most ? g : most & ~7);
 }
 
+// The units of block b of G with nw waves each: wave wv takes unit tb + wv of
+// every round, all waves run the same number of rounds; from 8 blocks on they go
+// to the XCDs round robin, so each XCD walks one contiguous eighth (see
+// unit_range).  In the last eighth a block may have none.
+struct BlockRange {
+  int64_t tb, stride, tend;
+};
+inline __host__ __device__ BlockRange block_units(int64_t n_units, int G, int b, int nw) {
+  BlockRange u;
+  if ((G & 7) == 0) {
+    const int64_t chunk = (n_units + 7) >> 3, lo = (b & 7) * chunk, hi = lo + chunk;
+    u.tend = n_units < hi ? n_units : hi;
+    u.tb = lo + (int64_t)(b >> 3) * nw;
+    u.stride = (int64_t)(G >> 3) * nw;
+  } else {
+    u.tb = (int64_t)b * nw;
+    u.stride = (int64_t)G * nw;
+    u.tend = n_units;
+  }
+  return u;
+}
+
 hipError_t launch_pack(int prec, const float* params, void* pack, const PackList& L, hipStream_t s);
 // Entries of mode 4 / 5 (n^2 + 1 floats at dst: the fragments, then the scale's exponent).
 hipError_t launch_pack_split(const float* params, void* pack, const PackList& L, hipStream_t s);

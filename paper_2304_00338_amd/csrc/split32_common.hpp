@@ -298,27 +298,10 @@ __device__ __forceinline__ float ln_x3(f32x16 (&z)[X3<LD>::NOB], int hh, float e
   return rstd;
 }
 
-// Block range of 32-row units (tiles): wave wv takes unit tb + wv of every
-// round, all waves run the same number of rounds; blocks go to the XCDs round
-// robin, so each XCD walks one contiguous eighth (see unit_range).
-struct BlockRange {
-  int64_t tb, stride, tend;
-};
+// Block range of 32-row units (tiles): see block_units.
 template <int NW = X3_NW>
 __device__ __forceinline__ BlockRange block_range(int64_t n_units) {
-  const int G = gridDim.x;
-  BlockRange u;
-  if ((G & 7) == 0) {
-    const int64_t chunk = (n_units + 7) >> 3, lo = (blockIdx.x & 7) * chunk;
-    u.tend = min(n_units, lo + chunk);
-    u.tb = lo + (int64_t)(blockIdx.x >> 3) * NW;
-    u.stride = (int64_t)(G >> 3) * NW;
-  } else {
-    u.tb = (int64_t)blockIdx.x * NW;
-    u.stride = (int64_t)G * NW;
-    u.tend = n_units;
-  }
-  return u;
+  return block_units(n_units, gridDim.x, blockIdx.x, NW);
 }
 
 // Receiver sums of a tile's rows.  The tile's rows [r0, r0 + SR) are staged

@@ -17,6 +17,16 @@ from paper_2304_00338_amd import mgn  # noqa: E402
 GAP = 200  # nodes without edges in the middle and at the end of the mesh
 
 
+def edgeless_mesh(shape, gap=1500):
+    """The mesh with gap nodes without edges before, in the middle of and after its nodes."""
+    M = synth.mesh(shape, 5)
+    n = M["pos"].shape[0]
+    lone = np.random.default_rng(4).random((3, gap, 3))
+    cells = M["cells"] + gap + gap * (M["cells"] >= n // 2)
+    pos = np.concatenate([lone[0], M["pos"][:n // 2], lone[1], M["pos"][n // 2:], lone[2]])
+    return cells, pos.astype(np.float32)
+
+
 def graphs(shape):
     """The mesh with the edgeless nodes, and the same with the hub's component
     (tetrahedra around an axis: the hub has 41 in-edges) after it."""
@@ -44,12 +54,13 @@ def test_runs_equal_tiles(prec, latent):
     x = rng.standard_normal((gb.n_nodes, 8)).astype(np.float32)
     w = rng.standard_normal((gb.n_nodes, 4)).astype(np.float32) / n0
     w[n0:] = 0  # the hub's component does not reach the loss
-    res = []
+    res = []  # (tests/test_edge_plan.py: the first graph is walked in runs, some blocks without any)
     for g in (ga, gb):
         dg = mgn.DeviceGraph(g)
         xi = torch.from_numpy(x[:g.n_nodes].copy()).cuda()
         wi = torch.from_numpy(w[:g.n_nodes].copy()).cuda()
         ctx = mgn.Context(m, g.n_nodes, g.n_edges, prec, save=True, latent=latent)
+        ctx.ws.fill_(255)  # NaN in every float: what is read is written first
         out = mgn.mgn_forward(ctx, dg, params, xi, dg.efeat, save=True)
         gp, gi = torch.zeros_like(params), torch.empty((g.n_nodes, 8), dtype=torch.float32, device="cuda")
         mgn.mgn_backward(ctx, wi, gp, gi)
@@ -63,3 +74,34 @@ def test_runs_equal_tiles(prec, latent):
     # the same fp32 terms in another grouping: at most about 500 additions in a
     # row, 500 * 2^-24 = 3e-5 of the sum of their magnitudes
     assert rel_l2(pa, pb) < 1e-4
+
+
+# 34^3, 35 x 33 x 34: the fp32 forward has blocks without a run (the last one; two);
+# 40^3: none; see tests/test_edge_plan.py
+@pytest.mark.parametrize("shape", [(34, 34, 34), (35, 33, 34), (40, 40, 40)])
+@pytest.mark.parametrize("prec,latent", [("fp32", 128), ("fp32", 150), ("bf16", 128)])
+def test_edgeless_nodes_get_zero_sums(shape, prec, latent):
+    """Nodes without edges at the start, in the middle and at the end of the
+    numbering: what the workspace held before is in no output or gradient."""
+    m = 2
+    cells, pos = edgeless_mesh(shape)
+    g = mgn.build_graph(cells, pos)
+    dg = mgn.DeviceGraph(g)
+    params = torch.from_numpy(synth.xavier_params(m, 5, latent, randomize_norm=True)).cuda()
+    rng = np.random.default_rng(7)
+    x = torch.from_numpy(rng.standard_normal((g.n_nodes, 8)).astype(np.float32)).cuda()
+    w = torch.from_numpy((rng.standard_normal((g.n_nodes, 4)) / g.n_nodes).astype(np.float32)).cuda()
+    res = []
+    for save, fill in ((True, 0), (True, 255), (False, 255)):  # 255: NaN in every float
+        ctx = mgn.Context(m, g.n_nodes, g.n_edges, prec, save=save, latent=latent)
+        ctx.ws.fill_(fill)
+        res.append([mgn.mgn_forward(ctx, dg, params, x, dg.efeat, save=save).cpu().numpy()])
+        if save:
+            gp, gi = torch.zeros_like(params), torch.empty((g.n_nodes, 8), dtype=torch.float32, device="cuda")
+            mgn.mgn_backward(ctx, w, gp, gi)
+            res[-1] += [gp.cpu().numpy(), gi.cpu().numpy()]
+        del ctx
+    for r in res[1:]:
+        for a, b in zip(res[0], r):
+            assert np.isfinite(b).all()
+            np.testing.assert_array_equal(a, b)
