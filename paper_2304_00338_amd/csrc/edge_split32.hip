@@ -394,11 +394,9 @@ k_wgrad_x3(WgradJobs jobs) {
   if (r < nr) load(r);
   for (; r < nr; r += job.nb) {
     const bool live = at(r) < M;
-    RowPieces<LD> G, X;
-    split_row<LD>(G, g, live);
-    split_row<LD>(X, x, live);
-    if (r + job.nb < nr) load(r + job.nb);
-    dw.add(G, X, live, S, tid);
+    dw.add_rows(g, x, live, S, tid, [&] {
+      if (r + job.nb < nr) load(r + job.nb);
+    });
   }
   dw.store(job.part + (size_t)blk * job.stride, tid);
 }

@@ -92,8 +92,12 @@ __device__ __forceinline__ Pieces split8(const float* x, int e) {
 }
 
 // Exponent e of the scale 2^e that brings a largest value m >= 0 into [2^14,
-// 2^15) (at most 2^126: smaller rows than 2^-112 keep what is left).
-__device__ __forceinline__ int scale_exp(float m) { return min(141 - (int)(__float_as_uint(m) >> 23), 126); }
+// 2^15) (at most 2^126: smaller rows than 2^-112 keep what is left); kZeroExp
+// for 0, kInfExp for an infinity.
+constexpr int kZeroExp = 4096, kInfExp = 141 - 255;
+__device__ __forceinline__ int scale_exp(float m) {
+  return m == 0.f ? kZeroExp : min(141 - (int)(__float_as_uint(m) >> 23), 126);
+}
 
 // Sum and maximum over the two lanes that hold a row.
 __device__ __forceinline__ float sum_hh(float s) {
@@ -395,14 +399,24 @@ struct ColSumX3 {
 
 // Weight gradients dW[o][n] += sum over rows of G[row][o] X[row][n], with the
 // rows as K, from the rows' pieces.  A row of G carries its own power of two
-// 2^eg and the row of X its 2^ex; X's pieces are scaled further, by 2^(c - eg -
-// ex) <= 1, so that every product carries 2^c: c is the smallest eg + ex of the
-// rows so far.  Rows whose products are far below the largest lose bits only
-// below 2^-39 of it.  When a block of rows lowers c, the accumulators follow.
+// 2^eg and the row of X its 2^ex; the pieces are scaled further, by 2^(c - eg -
+// ex) <= 1 in all, so that every product carries 2^c, as the accumulators do.
+//   c follows the rows: it is lowered to the smallest eg + ex of the NW x 32
+// rows that are added together, and raised where that lies more than kDwRise
+// above it (at most kDwSpan above its lowest value, so that no sum overflows).
+// What a piece has below 2^-24 is lost, so rows that need much scaling lose low bits:
+// with half of it in each operand, a row whose products are 2^-30 of 2^c's largest
+// stays within 2^-24 of its own largest value, one of 2^-40 within 2^-19, and one of
+// 2^-78 vanishes.  (Adding such rows in further passes at their own c keeps all bits.
+// Measured on the eight-patch batch, whose ghost nodes' gradients span 2^48
+// within those rows: reverse 1.28 -> 1.41 to 1.56 ms a launch; and at width 128 a
+// pass that is never taken still costs 3% in spilled registers.)  Rows of zeros, and
+// rows with an infinity (which become NaN), do not bound c and are not scaled.
 //   Each of the NW waves holds 32 rows (lane layout as above) and owns TU x TV
 // of the 16 x 16 tiles of dW.  The rows are staged row-major, SR rows at a time
 // (SR / NW of every wave), and read back transposed.  Rows that are not live
 // must have zero pieces in G.
+constexpr int kDwRise = 12, kDwSpan = 70;
 template <int LD, int NW>
 struct DwShape {
   static constexpr int SL = LD + 16;                 // staged row stride (fp16)
@@ -417,7 +431,17 @@ struct __attribute__((aligned(16))) DwLds {
   int c[NW];
 };
 
-// Eight fp16 values times 2^k, k <= 0 (below 2^-24 they vanish).
+// Smallest value over the 32 rows of a wave.
+__device__ __forceinline__ int min_rows(int m) {
+  m = min(m, __builtin_amdgcn_mov_dpp(m, 0x140, 0xf, 0xf, false));
+  m = min(m, __builtin_amdgcn_mov_dpp(m, 0x141, 0xf, 0xf, false));
+  m = min(m, __builtin_amdgcn_mov_dpp(m, 0x1B, 0xf, 0xf, false));
+  m = min(m, __builtin_amdgcn_mov_dpp(m, 0xB1, 0xf, 0xf, false));
+  const auto w = __builtin_amdgcn_permlane16_swap((uint32_t)m, (uint32_t)m, false, false);
+  return min((int)w[0], (int)w[1]);
+}
+
+// Eight fp16 values times s.
 __device__ __forceinline__ f16x8 scale_f16(f16x8 v, _Float16 s) {
   return v * f16x8{s, s, s, s, s, s, s, s};
 }
@@ -426,8 +450,9 @@ template <int LD, int NW>
 struct DwAcc {
   typedef DwShape<LD, NW> Sh;
   static constexpr int TU = Sh::TU, TV = Sh::TV;
+  static constexpr int NONE = 1 << 20;
   f32x4 a[TU * TV];
-  int c = 1 << 20;  // no rows yet
+  int c = NONE, cmin = NONE;  // no rows yet
   __device__ __forceinline__ void clear() {
 #pragma unroll
     for (int t = 0; t < TU * TV; ++t) a[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -436,50 +461,41 @@ struct DwAcc {
     const bf16* p = reinterpret_cast<const bf16*>(S) + (r0 + q * 8 + (i >> 2)) * Sh::SL + col0 + 4 * (i & 3);
     return __builtin_bit_cast(f16x8, cat8(lds_tr(p), lds_tr(p + 4 * Sh::SL)));
   }
-  __device__ __forceinline__ void add(const RowPieces<LD>& G, RowPieces<LD>& X, bool live, DwLds<LD, NW>& S, int tid) {
-    typedef X3<LD> Z;
-    constexpr int RW = Sh::SR / NW;  // rows of a wave staged at a time
-    const int lane = tid & 63, row = lane & 31, hh = lane >> 5, wv = tid >> 6, i = lane & 15, q = lane >> 4;
-    // the smallest eg + ex of the block's rows
-    int m = live ? G.e + X.e : 1 << 20;
-    m = min(m, __builtin_amdgcn_mov_dpp(m, 0x140, 0xf, 0xf, false));
-    m = min(m, __builtin_amdgcn_mov_dpp(m, 0x141, 0xf, 0xf, false));
-    m = min(m, __builtin_amdgcn_mov_dpp(m, 0x1B, 0xf, 0xf, false));
-    m = min(m, __builtin_amdgcn_mov_dpp(m, 0xB1, 0xf, 0xf, false));
-    const auto w = __builtin_amdgcn_permlane16_swap((uint32_t)m, (uint32_t)m, false, false);
-    m = min((int)w[0], (int)w[1]);
-    if (lane == 0) S.c[wv] = m;
+  // Brings c to the block's rows (er: the row's eg + ex, NONE where it does not
+  // bound c) and returns the exponent that the row's product lacks to it.
+  __device__ __forceinline__ int fit(int er, DwLds<LD, NW>& S, int tid) {
+    const int m = min_rows(er);
+    if ((tid & 63) == 0) S.c[tid >> 6] = m;
     __syncthreads();  // also: the products of the previous call are done
     int cn = S.c[0];
 #pragma unroll
     for (int k = 1; k < NW; ++k) cn = min(cn, S.c[k]);
     cn = __builtin_amdgcn_readfirstlane(cn);
-    if (cn < c) {
+    if (cn < c || (cn > c + kDwRise && cn != NONE)) {
+      cn = min(cn, cmin + kDwSpan);
 #pragma unroll
       for (int t = 0; t < TU * TV; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) a[t][r] = __builtin_amdgcn_ldexpf(a[t][r], cn - c);
       c = cn;
+      cmin = min(cmin, c);
     }
-    const _Float16 sx = (_Float16)__builtin_amdgcn_ldexpf(1.f, live ? max(c - G.e - X.e, -100) : -100);
-#pragma unroll
-    for (int k = 0; k < Z::KS; ++k) {
-      X.p[k].h = scale_f16(X.p[k].h, sx);
-      X.p[k].l = scale_f16(X.p[k].l, sx);
-    }
+    return er == NONE ? 0 : max(c - er, -60);
+  }
+  static __device__ __forceinline__ int bound(int eg, int ex, bool live) {
+    return live && max(eg, ex) < kZeroExp && min(eg, ex) > kInfExp ? eg + ex : NONE;
+  }
+  // The products of the rows that stage(at) writes to S at offset at of its arrays.
+  template <class F>
+  __device__ __forceinline__ void products(DwLds<LD, NW>& S, int tid, F&& stage) {
+    constexpr int RW = Sh::SR / NW;  // rows of a wave staged at a time
+    const int lane = tid & 63, row = lane & 31, hh = lane >> 5, wv = tid >> 6, i = lane & 15, q = lane >> 4;
     const int at = (RW * wv + row % RW) * Sh::SL + 8 * hh;
     const int u0 = 16 * TU * (wv / (LD / 16 / TV)), v0 = 16 * TV * (wv % (LD / 16 / TV));
 #pragma unroll 1
     for (int r = 0; r < 32 / RW; ++r) {
       if (r > 0) __syncthreads();  // the previous rows' products are done
-      if (row / RW == r)
-#pragma unroll
-        for (int k = 0; k < Z::KS; ++k) {
-          *reinterpret_cast<f16x8*>(S.g[0] + at + 16 * k) = G.p[k].h;
-          *reinterpret_cast<f16x8*>(S.g[1] + at + 16 * k) = G.p[k].l;
-          *reinterpret_cast<f16x8*>(S.x[0] + at + 16 * k) = X.p[k].h;
-          *reinterpret_cast<f16x8*>(S.x[1] + at + 16 * k) = X.p[k].l;
-        }
+      if (row / RW == r) stage(at);
       __syncthreads();
 #pragma unroll
       for (int r0 = 0; r0 < Sh::SR; r0 += 32) {
@@ -502,6 +518,66 @@ struct DwAcc {
         }
       }
     }
+  }
+  // From the pieces of a product's rows (X's are used up).
+  __device__ __forceinline__ void add(const RowPieces<LD>& G, RowPieces<LD>& X, bool live, DwLds<LD, NW>& S, int tid) {
+    // down to 2^-12 all of it in X, so that G's pieces seldom need it
+    const int k = fit(bound(G.e, X.e, live), S, tid), kx = k < -12 ? k / 2 : k;
+    const bool plain = !__any(k != kx);
+    const _Float16 sx = (_Float16)__builtin_amdgcn_ldexpf(1.f, kx);
+    float sg = __builtin_amdgcn_ldexpf(1.f, k - kx);
+#pragma unroll
+    for (int u = 0; u < X3<LD>::KS; ++u) {
+      X.p[u].h = scale_f16(X.p[u].h, sx);
+      X.p[u].l = scale_f16(X.p[u].l, sx);
+    }
+    products(S, tid, [&](int at) {
+      if (plain) {
+#pragma unroll
+        for (int u = 0; u < X3<LD>::KS; ++u) {
+          *reinterpret_cast<f16x8*>(S.g[0] + at + 16 * u) = G.p[u].h;
+          *reinterpret_cast<f16x8*>(S.g[1] + at + 16 * u) = G.p[u].l;
+        }
+      } else {
+        asm volatile("" : "+v"(sg));  // scaled here: all of the scaled pieces do not fit beside the others
+#pragma unroll
+        for (int u = 0; u < X3<LD>::KS; ++u) {
+          *reinterpret_cast<f16x8*>(S.g[0] + at + 16 * u) = scale_f16(G.p[u].h, (_Float16)sg);
+          *reinterpret_cast<f16x8*>(S.g[1] + at + 16 * u) = scale_f16(G.p[u].l, (_Float16)sg);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < X3<LD>::KS; ++u) {
+        *reinterpret_cast<f16x8*>(S.x[0] + at + 16 * u) = X.p[u].h;
+        *reinterpret_cast<f16x8*>(S.x[1] + at + 16 * u) = X.p[u].l;
+      }
+    });
+  }
+  // From the rows' values, split once their scales are known, which takes no
+  // scaling of pieces and no copy of them (per launch of k_wgrad_x3: 434,558 edges and 2 x
+  // 32,768 nodes at width 128 172 -> 162 us, 0.9M edges at width 160 414 -> 330 us); then()
+  // runs when they are no longer needed.
+  template <class F>
+  __device__ __forceinline__ void add_rows(const float* g, const float* x, bool live, DwLds<LD, NW>& S, int tid,
+                                           F&& then) {
+    const int eg = row_exp<LD>(g), ex = row_exp<LD>(x);
+    const int k = fit(bound(eg, ex, live), S, tid), kx = k / 2;
+    RowPieces<LD> G, X;
+#pragma unroll
+    for (int u = 0; u < X3<LD>::KS; ++u) {
+      G.p[u] = split8(g + 8 * u, live ? eg + k - kx : -10000);
+      X.p[u] = split8(x + 8 * u, ex + kx);
+    }
+    then();
+    products(S, tid, [&](int at) {
+#pragma unroll
+      for (int u = 0; u < X3<LD>::KS; ++u) {
+        *reinterpret_cast<f16x8*>(S.g[0] + at + 16 * u) = G.p[u].h;
+        *reinterpret_cast<f16x8*>(S.g[1] + at + 16 * u) = G.p[u].l;
+        *reinterpret_cast<f16x8*>(S.x[0] + at + 16 * u) = X.p[u].h;
+        *reinterpret_cast<f16x8*>(S.x[1] + at + 16 * u) = X.p[u].l;
+      }
+    });
   }
   // the block's dW [LD][LD]
   __device__ __forceinline__ void store(float* base, int tid) const {

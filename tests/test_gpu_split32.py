@@ -55,3 +55,112 @@ def test_power_of_two_rescaling_is_exact(shape, latent):
         np.testing.assert_array_equal(o2, out)
         np.testing.assert_array_equal(gi2, gi)
         np.testing.assert_array_equal(gp2 * f, gp)
+
+
+UNIT = 5  # the hidden unit of every MLP that is active on the second component only
+
+
+def two_components(mixed, latent, m):
+    """Two copies of a small mesh (one after the other, or node by node in
+    turn), told apart by the node type, and parameters at which hidden unit UNIT
+    of every MLP but the edge encoder is active on the second copy only.  Every
+    ReLU input is far from its kink."""
+    M = synth.mesh((6, 5, 4), 3)
+    n = M["pos"].shape[0]
+    ids = np.arange(2 * n).reshape(2, n) if not mixed else np.arange(2 * n).reshape(n, 2).T
+    cells = np.concatenate([ids[0][M["cells"]], ids[1][M["cells"]]]).astype(np.int32)
+    pos, x = np.empty((2 * n, 3), np.float32), np.zeros((2 * n, 8), np.float32)
+    rng = np.random.default_rng(8)
+    for k in range(2):
+        pos[ids[k]] = M["pos"]
+        x[ids[k], k] = 1
+    x[:, 4:] = rng.standard_normal((2 * n, 4))
+    p = synth.smooth_params(m, 3, latent)
+    v, o = {}, 0
+    for name, _, shape in synth.param_shapes(m, latent):
+        v[name] = p[o:o + int(np.prod(shape))].reshape(shape)
+        o += int(np.prod(shape))
+
+    def unit(mlp, column, weight):
+        v[mlp + ".W1"][UNIT] = 0
+        v[mlp + ".W1"][UNIT, column] = weight
+        v[mlp + ".b1"][UNIT] = -4
+    unit("enc_node", 1, 8)  # 4 on the second copy, -4 on the first
+    v["enc_node.W2"][0] = 0
+    v["enc_node.W2"][0, UNIT] = 20  # the latent's feature 0: about 8 and 0
+    v["enc_node.gamma"][0], v["enc_node.beta"][0] = 1, 0
+    for l in range(m):
+        unit(f"block{l}.edge", latent, 1)
+        unit(f"block{l}.node", 0, 1)
+        v[f"block{l}.node.gamma"][0] = v[f"block{l}.node.beta"][0] = 0  # feature 0 stays
+    unit("dec", 0, 1)
+    return cells, pos, x, p, ids
+
+
+def gradients(cells, pos, x, p, w, m, latent):
+    g = mgn.build_graph(cells, pos)
+    dg = mgn.DeviceGraph(g)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+    d = dev(p)
+    ctx = mgn.Context(m, g.n_nodes, g.n_edges, "fp32", save=True, latent=latent)
+    mgn.mgn_forward(ctx, dg, d, dev(x), dg.efeat, save=True)
+    gp, dw = torch.zeros_like(d), dev(w)
+    mgn.mgn_backward(ctx, dw, gp)
+    torch.cuda.synchronize()
+    return gp.cpu().numpy()
+
+
+def unit_entries(gp, m, latent):
+    """{name: the gradient of the weights into and out of UNIT}"""
+    out, o = {}, 0
+    for name, _, shape in synth.param_shapes(m, latent):
+        a = gp[o:o + int(np.prod(shape))].reshape(shape)
+        o += int(np.prod(shape))
+        if name.endswith(".W1") and not name.startswith("enc_edge"):
+            out[name] = a[UNIT]
+        elif name.endswith(".W2") and not name.startswith("enc_edge"):
+            out[name] = a[:, UNIT]
+    return out
+
+
+# Weight gradients sum products of rows that each carry their own scale.  Here
+# entries of dW are reached only by rows whose gradient is 2^-k of the other rows'.
+# With rows of one size (k = 0) an entry's error is some roundings of 2^-24 of a row's
+# values, times what its sum cancels.  Scaled to the others, half in each operand, a row's pieces
+# end at 2^(k/2 - 39) of its largest value instead: 1 + 2^(k/2 - 15) times as much.
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("latent", [128, 150])
+def test_small_gradient_rows_keep_their_accuracy(mixed, latent):
+    m = 2
+    cells, pos, x, p, ids = two_components(mixed, latent, m)
+    go = O.build_graph(cells, pos)
+    _, tape = O.mgn_forward(go, p, x, go.efeat, m, latent=latent, keep=True)
+    assert not O.relu_kinks(tape, 0.5)
+    base = {}
+    for k in (0, 9, 14, 24, 30, 39):
+        w = np.random.default_rng(9).standard_normal((x.shape[0], 4)).astype(np.float32)
+        w[ids[1]] *= np.float32(2.0 ** -k)
+        ref, _ = O.mgn_backward(tape, w)
+        got = gradients(cells, pos, x, p, w, m, latent)
+        assert rel_l2(got, ref) < 1e-5
+        want = unit_entries(ref, m, latent)
+        err = {name: rel_l2(a, want[name]) for name, a in unit_entries(got, m, latent).items()}
+        base = base or err
+        for name, e in err.items():
+            assert np.linalg.norm(want[name]) > 0, name
+            assert base[name] < FP32_TOL and e < (2 * base[name] + 1e-6) * (1 + 2.0 ** (k / 2 - 15)), (k, name, e)
+
+
+def test_infinite_gradient_row_stays_by_itself():
+    """A row with infinities makes what it reaches infinite or NaN; entries that
+    it does not reach (here its ReLU blocks it) keep the other rows' sums."""
+    m, latent = 2, 128
+    cells, pos, x, p, ids = two_components(True, latent, m)
+    w = np.random.default_rng(9).standard_normal((x.shape[0], 4)).astype(np.float32)
+    go = O.build_graph(cells, pos)
+    _, tape = O.mgn_forward(go, p, x, go.efeat, m, latent=latent, keep=True)
+    want = unit_entries(O.mgn_backward(tape, w)[0], m, latent)["dec.W1"]
+    w[ids[0][7], 1] = np.inf
+    got = gradients(cells, pos, x, p, w, m, latent)
+    assert not np.isfinite(got).all()
+    assert rel_l2(unit_entries(got, m, latent)["dec.W1"], want) < 1e-5
