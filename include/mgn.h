@@ -54,7 +54,20 @@ extern "C" {
 #define MGN_ERR_NOMEM (-7)     /* host allocation failed */
 
 /* ---- enums ----------------------------------------------------------- */
-#define MGN_FP32 0 /* fp32 latent streams, products at fp32 accuracy */
+/* MGN_FP32: fp32 streams, sums and statistics.  The latent-wide products split
+ * their operands into two fp16 numbers each (22 to 23 bits) and accumulate in
+ * fp32: a 128-term product is within 1.2e-7 of the exact one (relative 2-norm;
+ * fp32 multiply-adds: 2.0e-7).  Each row, and each weight matrix, has one scale,
+ * so this holds at any magnitude, but not at any spread:
+ *   - a value 2^-16 or more below the largest of its row (of one node's or
+ *     edge's latent or gradient) loses a bit per further factor of two, and so
+ *     does a weight from 2^-28 of its matrix's largest;
+ *   - a weight gradient adds up to 256 rows (edges or nodes next to each other
+ *     in the numbering) at one scale: a row whose contributions are 2^-30 or more
+ *     below the largest of these loses a bit per further factor of four.
+ * What is lost is small against the large values; it shows in results that
+ * only the small ones reach. */
+#define MGN_FP32 0
 #define MGN_BF16 1 /* bf16 MFMA operands, bf16 edge-latent stream, fp32
                       accumulation, LayerNorm statistics, sums and node state */
 

@@ -52,7 +52,8 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ params, 
 // value 16 ob + r of lane half oh and k = that of value 8 ks + t of half kh
 // (X3::feat) is element t of lane m + 32 kh, m = r % 4 + 8 (r / 4) + 4 oh, of the
 // fragments (ks, ob, piece), scaled by the power of two that brings the
-// largest |M| into [2^14, 2^15); its exponent follows the fragments.  Every block forms the maximum itself (a matrix is at
+// largest |M| into [2^14, 2^15); its exponent follows the fragments.  The low
+// pieces carry another 2^kLowExp.  Every block forms the maximum itself (a matrix is at
 // most 100 KB, read once from L2) and then writes its share: a separate
 // launch for the maxima would cost a small call more than the packing.
 __global__ void __launch_bounds__(1024) k_pack_split(const float* __restrict__ params, float* __restrict__ pack,
@@ -81,7 +82,7 @@ __global__ void __launch_bounds__(1024) k_pack_split(const float* __restrict__ p
     const _Float16 h = (_Float16)v;
     _Float16* q = dst + (int64_t)rest * 2 * 512 + l * 8 + t;
     q[0] = h;
-    q[512] = (_Float16)(v - (float)h);
+    q[512] = (_Float16)__builtin_amdgcn_ldexpf(v - (float)h, kLowExp);
   }
   if (blockIdx.x == 0 && tid == 0) *reinterpret_cast<int*>(pack + pe.dst + n) = e;
 }

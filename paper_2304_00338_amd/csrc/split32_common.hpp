@@ -6,17 +6,25 @@
 // largest value into [2^14, 2^15), and every value is split into two fp16
 // numbers, xh = fp16(s x) and xl = fp16(s x - xh), both rounded to nearest (the
 // difference is exact).  The weights are split the same way when they are
-// packed, with one power of two per matrix.  W x is the sum of wl xh, wh xl
-// and wh xh, added in that order per K step in the fp32 accumulator of
-// v_mfma_f32_32x32x16_f16 and scaled back by a power of two.
-//   Accuracy: s x - xh - xl is at most 2^-24 |s x|, or 2^-25 where xl is
-// subnormal, which is 2^-39 of the row's largest value; the dropped wl xl is
-// at most 2^-24 |w x|; and a sum of K = 128 takes 24 accumulations instead of
-// the fp32 instruction's 128.  Measured against float64 (relative 2-norm, K =
-// 128): 1.2e-7 for normal rows, 1.1e-7 after a ReLU, 0.8e-7 for rows whose
-// values span twelve binary orders, where 128 fp32 multiply-adds give 2.0e-7,
-// 1.4e-7 and 1.8e-7.  The scales keep this for rows of any magnitude.  Rows
-// with an infinity or NaN give NaN.
+// packed, with one power of two per matrix, wl times 2^12 so that it stays normal longer.
+// W x is the sum of (2^12 wl) (2^-12 xh), wh xl and wh xh, added in that order per K
+// step in the fp32 accumulator of v_mfma_f32_32x32x16_f16 and scaled back by
+// a power of two.
+//   Accuracy: two pieces hold 22 to 23 bits of a value.  xh + xl is within 2^-23 |s x| of s x (and within
+// 2^-25 where xl is subnormal, which is 2^-39 of the row's largest value); a
+// weight is held within 2^-23 of itself and 2^-51 of the matrix's largest;
+// the dropped wl xl is at most 2^-22 |w x|; and a sum of K = 128 takes 24
+// accumulations instead of the fp32 instruction's 128.  Measured against
+// float64 (relative 2-norm, K = 128): 1.2e-7 for normal rows, 1.1e-7 after a
+// ReLU, 0.8e-7 for rows whose values span twelve binary orders, where 128 fp32
+// multiply-adds give 2.0e-7, 1.4e-7 and 1.8e-7.  The scales keep this for rows and
+// matrices of any magnitude, and for weights down to 2^-28 of their matrix's largest (one
+// scale per matrix without the 2^12: 3e-6 at 2^-20, 5e-4 at 2^-28).  Within a row it holds down to about
+// 2^-16 of the largest value: a smaller one loses a bit per factor of two,
+// which shows where the larger ones meet weights as much smaller, or zeros.  (A separate
+// power of two per row of W, applied to the result where any row has one, cost more: edge
+// forward at 434,558 edges 189 -> 232 us, in spilled registers.)  Rows with an
+// infinity or NaN give NaN.
 //   What bounds it: three fp16 products are 3/16 of the fp32 instruction's MFMA
 // time.  Under a full load of random operands this card's 16-bit MFMAs sustain
 // 0.58 of their nominal rate (power), and a three-piece bf16 split, which
@@ -90,6 +98,15 @@ __device__ __forceinline__ Pieces split8(const float* x, int e) {
   }
   return p;
 }
+
+// Eight fp16 values times s.
+__device__ __forceinline__ f16x8 scale_f16(f16x8 v, _Float16 s) {
+  return v * f16x8{s, s, s, s, s, s, s, s};
+}
+
+// The weights' low pieces are packed times 2^kLowExp and meet xh times 2^-kLowExp:
+// a low piece is at most 2^3, so this is the largest factor that fits.
+constexpr int kLowExp = 12;
 
 // Exponent e of the scale 2^e that brings a largest value m >= 0 into [2^14,
 // 2^15) (at most 2^126: smaller rows than 2^-112 keep what is left); kZeroExp
@@ -167,6 +184,9 @@ __device__ __forceinline__ void gemm_raw(f32x16 (&acc)[X3<LD>::NOB], G&& get, co
   typedef X3<LD> Z;
   const int lane = tid & 63;
   const int ot = tid + opaque_zero();  // keeps the loads' addresses out of the callers' loops
+  // 2^-kLowExp as two fp16; opaque, or a second product of the same row would keep the scaled pieces
+  int low = (15 - kLowExp) << 10 | (15 - kLowExp) << 26;
+  asm volatile("" : "+s"(low));
   if (!ADD)
 #pragma unroll
   for (int ob = 0; ob < Z::NOB; ++ob)
@@ -182,12 +202,13 @@ __device__ __forceinline__ void gemm_raw(f32x16 (&acc)[X3<LD>::NOB], G&& get, co
       // apart (fragments of both at once do not fit in the registers)
       __builtin_amdgcn_sched_barrier(0);
       const Pieces b = get(2 * c + k);
+      const f16x8 bs = scale_f16(b.h, __builtin_bit_cast(f16x2, low)[0]);
       const f16x8* A = reinterpret_cast<const f16x8*>(buf[(par + c) & 1]) + k * Z::NOB * 128 + lane;
       f16x8 a[Z::NOB];
 #pragma unroll
       for (int ob = 0; ob < Z::NOB; ++ob) a[ob] = A[(2 * ob + 1) * 64];
 #pragma unroll
-      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ob], b.h, acc[ob], 0, 0, 0);
+      for (int ob = 0; ob < Z::NOB; ++ob) acc[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ob], bs, acc[ob], 0, 0, 0);
 #pragma unroll
       for (int ob = 0; ob < Z::NOB; ++ob) a[ob] = A[(2 * ob) * 64];
 #pragma unroll
@@ -439,11 +460,6 @@ __device__ __forceinline__ int min_rows(int m) {
   m = min(m, __builtin_amdgcn_mov_dpp(m, 0xB1, 0xf, 0xf, false));
   const auto w = __builtin_amdgcn_permlane16_swap((uint32_t)m, (uint32_t)m, false, false);
   return min((int)w[0], (int)w[1]);
-}
-
-// Eight fp16 values times s.
-__device__ __forceinline__ f16x8 scale_f16(f16x8 v, _Float16 s) {
-  return v * f16x8{s, s, s, s, s, s, s, s};
 }
 
 template <int LD, int NW>

@@ -97,17 +97,17 @@ def two_components(mixed, latent, m):
     return cells, pos, x, p, ids
 
 
-def gradients(cells, pos, x, p, w, m, latent):
+def outputs_and_gradients(cells, pos, x, p, w, m, latent):
     g = mgn.build_graph(cells, pos)
     dg = mgn.DeviceGraph(g)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
-    d = dev(p)
+    d, dw = dev(p), dev(w)
     ctx = mgn.Context(m, g.n_nodes, g.n_edges, "fp32", save=True, latent=latent)
-    mgn.mgn_forward(ctx, dg, d, dev(x), dg.efeat, save=True)
-    gp, dw = torch.zeros_like(d), dev(w)
+    out = mgn.mgn_forward(ctx, dg, d, dev(x), dg.efeat, save=True)
+    gp = torch.zeros_like(d)
     mgn.mgn_backward(ctx, dw, gp)
     torch.cuda.synchronize()
-    return gp.cpu().numpy()
+    return out.cpu().numpy(), gp.cpu().numpy()
 
 
 def unit_entries(gp, m, latent):
@@ -141,7 +141,7 @@ def test_small_gradient_rows_keep_their_accuracy(mixed, latent):
         w = np.random.default_rng(9).standard_normal((x.shape[0], 4)).astype(np.float32)
         w[ids[1]] *= np.float32(2.0 ** -k)
         ref, _ = O.mgn_backward(tape, w)
-        got = gradients(cells, pos, x, p, w, m, latent)
+        _, got = outputs_and_gradients(cells, pos, x, p, w, m, latent)
         assert rel_l2(got, ref) < 1e-5
         want = unit_entries(ref, m, latent)
         err = {name: rel_l2(a, want[name]) for name, a in unit_entries(got, m, latent).items()}
@@ -161,6 +161,47 @@ def test_infinite_gradient_row_stays_by_itself():
     _, tape = O.mgn_forward(go, p, x, go.efeat, m, latent=latent, keep=True)
     want = unit_entries(O.mgn_backward(tape, w)[0], m, latent)["dec.W1"]
     w[ids[0][7], 1] = np.inf
-    got = gradients(cells, pos, x, p, w, m, latent)
+    _, got = outputs_and_gradients(cells, pos, x, p, w, m, latent)
     assert not np.isfinite(got).all()
     assert rel_l2(unit_entries(got, m, latent)["dec.W1"], want) < 1e-5
+
+
+# A weight is held to 2^-23 of itself and to 2^-51 of its matrix's largest.  Here every
+# matrix of the MP blocks has columns 2^k above the others that meet only zeros
+# (a latent feature that is always 0, a hidden unit that is never active).  The others must
+# be as accurate as without them (k = 0), but for the second bound: for a weight
+# 2^-(k + 1) of the largest it is 2^(k - 27) times the first.
+@pytest.mark.parametrize("latent", [128, 150])
+def test_weights_far_below_their_matrix_largest(latent):
+    m, zero, dead = 2, 9, 5
+    M = synth.mesh((7, 6, 5), 3)
+    go = O.build_graph(M["cells"], M["pos"])
+    w = synth.loss_weights(M["pos"].shape[0], 3)
+    base = None
+    for k in (0, 16, 20, 24, 27, 30):
+        p = synth.smooth_params(m, 3, latent)
+        v, o = {}, 0
+        for name, _, shape in synth.param_shapes(m, latent):
+            v[name] = p[o:o + int(np.prod(shape))].reshape(shape)
+            o += int(np.prod(shape))
+        for mlp in ["enc_node", "enc_edge"] + [f"block{l}.{t}" for l in range(m) for t in ("edge", "node")]:
+            v[mlp + ".gamma"][zero] = v[mlp + ".beta"][zero] = 0
+            if mlp.startswith("block"):
+                v[mlp + ".W1"][:, zero::latent] *= 2.0 ** k
+            v[mlp + ".b1"][dead] = -6
+            v[mlp + ".W2"][:, dead] *= 2.0 ** k
+        ref, tape = O.mgn_forward(go, p, M["node_in"], go.efeat, m, latent=latent, keep=True)
+        assert not O.relu_kinks(tape, 0.5)
+        rg, _ = O.mgn_backward(tape, w)
+        out, got = outputs_and_gradients(M["cells"], M["pos"], M["node_in"], p, w, m, latent)
+        err = {"out": rel_l2(out, ref)}
+        o = 0
+        for name, kind, shape in synth.param_shapes(m, latent):
+            n = int(np.prod(shape))
+            if kind == "w" and not name.startswith("enc_edge"):
+                err[name] = rel_l2(got[o:o + n], rg[o:o + n])
+            o += n
+        base = base or err
+        for name, e in err.items():
+            assert base[name] < 1e-5 and e < (2 * base[name] + 2e-7) * (1 + 2.0 ** (k - 27)), (k, name, e, base[name])
+
