@@ -718,7 +718,7 @@ hipError_t launch_edge_fwd_rows(const EdgeTiles& tl, const void* e_in, void* e_o
                                 const MlpW& w, float eps, float* agg, float* slots, void* a1_out, hipStream_t s) {
   if (tl.n_tiles <= 0) return hipSuccess;
   if (tl.n_edges <= 0) return hipErrorInvalidValue;
-  const EdgeTiles t = plan_runs(tl, NW * kRowsBlocks);
+  const EdgeTiles t = a1_out ? tl : plan_runs(tl, NW * kRowsBlocks);  // (see plan_runs)
   hipLaunchKernelGGL(k_edge_fwd_rows, dim3(unit_blocks(walk_n(t), NW, kRowsBlocks)), dim3(NT), 0, s, t, (const bf16*)e_in,
                      (bf16*)e_out, write_e, (const bf16*)Pn, w, eps, agg, slots, (bf16*)a1_out);
   return hipGetLastError();

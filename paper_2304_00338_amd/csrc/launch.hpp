@@ -93,11 +93,14 @@ inline int64_t walk_rounds(int64_t n, int64_t k, int waves) {
 }
 // Tiles or runs for an edge kernel of that many waves, whichever leaves the
 // busiest wave the fewer steps (for the same number, tiles and then shorter
-// runs: neighbouring waves stay on neighbouring rows).  Measured with tiles and
-// with runs, per launch: 11.7M edges in bf16, 204 against 186 steps a wave, forward
-// 2.05 and 1.88 ms, reverse (408 against 372) 4.20 and 3.93 ms; 434,558 edges, reverse
-// (16 against 15) 189 and 181 us; 0.9M edges at width 160 in fp32, reverse 1.81 and
-// 1.57 ms.  Up to about four steps a wave tiles never take more.
+// runs: neighbouring waves stay on neighbouring rows).  Runs come from 9 steps a wave on
+// where a tile holds 27.8 of 32 rows (Kuhn mesh of a cube), from 17 at 30 rows (2D).
+// Measured per launch, tiles | runs, at 1.15M, 3.57M and 11.7M edges: bf16 forward
+// without saving 189 | 179, 585 | 542, 1929 | 1787 us, reverse 425 | 402, 1272 | 1185, 4274 | 4005
+// us; fp32 at 1.15M and 3.57M, width 128: forward 477 | 461, 1478 | 1423, reverse 1440 | 1397,
+// 4302 | 4196, width 160: 759 | 732, 2307 | 2173, 2452 | 2288, 7466 | 6917 us.  The bf16 forward
+// that saves a1 stays on tiles: it is bound by what it writes, and with runs takes
+// 233 | 240, 695 | 706 and 2339 | 2330 us and 8% more memory traffic.
 inline EdgeTiles plan_runs(EdgeTiles t, int waves) {
   t.run = 0;
   if (t.n_long > 0 || t.n_edges <= 0) return t;

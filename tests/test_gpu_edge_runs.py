@@ -66,6 +66,10 @@ def test_runs_equal_tiles(prec, latent):
         mgn.mgn_backward(ctx, wi, gp, gi)
         torch.cuda.synchronize()
         res.append((out[:n0].cpu().numpy(), gi[:n0].cpu().numpy(), gp.cpu().numpy()))
+        # a forward that saves nothing may walk differently
+        ctx = mgn.Context(m, g.n_nodes, g.n_edges, prec, latent=latent)
+        ctx.ws.fill_(255)
+        np.testing.assert_array_equal(mgn.mgn_forward(ctx, dg, params, xi, dg.efeat)[:n0].cpu().numpy(), res[-1][0])
         del ctx, dg
     (oa, ia, pa), (ob, ib, pb) = res
     assert np.isfinite(oa).all() and np.isfinite(pa).all()
