@@ -23,9 +23,9 @@ struct __attribute__((aligned(16))) EdgeFwdLds {
 // h, W1r h] of the block come from the node kernels).  Two blocks per CU, so
 // one block's loads, LayerNorm and barriers lie under the other's MFMAs; that
 // leaves 256 registers, hence e is read again for the residual.  Measured per
-// launch: 434,558 edges at width 128 0.360 -> 0.190 ms (fp32 MFMA version ->
+// launch: 434,558 edges at width 128 0.354 -> 0.189 ms (fp32 MFMA version ->
 // this; 0.125 ms without its memory traffic, which alone takes 0.095 ms at the
-// copy rate), the eight-patch batch at width 160 1.11 -> 0.52 ms.  Rows past a
+// copy rate), the eight-patch batch (0.68M edges) at width 160 0.92 -> 0.44 ms.  Rows past a
 // tile's end, and tiles past the block's range, read a valid row that is
 // never stored or summed.
 template <int LD>
@@ -161,11 +161,11 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
 // two per SIMD: in 256 registers a wave holds the pieces of a1 and dz2, one
 // product and an eighth of dW2 (ebar_in is read twice instead of being kept).
 // At width 160 that does not fit, and the block has four waves of 512.
-//   Measured per launch: 434,558 edges at width 128 1.11 -> 0.57 ms (fp32 MFMA
+//   Measured per launch: 434,558 edges at width 128 1.11 -> 0.56 ms (fp32 MFMA
 // version, dW1e included, -> this; its dW1e pass takes 0.11 ms), the eight-patch
-// batch (0.9M edges) at width 160 2.62 -> 1.57 ms.  With its loads and stores
-// taken away it still takes 0.49 ms of 0.62: the arithmetic of the phases that
-// the eight waves enter together is what bounds it, not memory.
+// batch (0.68M edges) at width 160 2.20 -> 1.36 ms.  At width 128, with its loads and
+// stores taken away, it still took 0.49 ms: the arithmetic of the phases that the
+// eight waves enter together is what bounds it, not memory.
 // Partials per block: db1 at LD^2, dW2, db2, dgamma, dbeta.
 template <int LD>
 struct EdgeBwd {

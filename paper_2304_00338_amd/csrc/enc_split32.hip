@@ -2,7 +2,7 @@
 // width by an MLP with LayerNorm), e = LN(W2 relu(W1 f + b1) + b2), on the split
 // fp16 products of split32_common.hpp: one wave per 32-edge unit, two blocks per
 // CU.  The first layer (K = 4) is one fma chain per feature from b1, k = 0..3, as in
-// the reverse (edge_rows32.hip), which so sees the same ReLU mask.
+// the reverse (enc_rows32.hip), which so sees the same ReLU mask.
 #include "launch.hpp"
 #include "split32_common.hpp"
 
@@ -19,8 +19,9 @@ struct __attribute__((aligned(16))) EdgeEncLds {
 };
 
 // Rows past E read row E - 1 and store nothing.  Measured per launch (fp32 MFMA
-// version -> this): 434,558 edges at width 128 176 -> 88 us (writing e alone takes 47
-// at the copy rate), 107k edges 55 -> 25 us, 0.9M edges at width 160 0.49 -> 0.21 ms.
+// version -> this): 434,558 edges at width 128 173 -> 85 us (writing e alone takes 47
+// at the copy rate), patches of 96k to 119k edges 55 -> 27 us, 0.68M
+// edges at width 160 0.39 -> 0.17 ms.
 template <int LD>
 __global__ void __launch_bounds__(X3_NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_edge_enc_x3(int64_t E, const float* __restrict__ f_in, MlpW w, float eps, float* __restrict__ e_out) {

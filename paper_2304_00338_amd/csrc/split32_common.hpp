@@ -430,7 +430,7 @@ struct ColSumX3 {
 // stays within 2^-24 of its own largest value, one of 2^-40 within 2^-19, and one of
 // 2^-78 vanishes.  (Adding such rows in further passes at their own c keeps all bits.
 // Measured on the eight-patch batch, whose ghost nodes' gradients span 2^48
-// within those rows: reverse 1.28 -> 1.41 to 1.56 ms a launch; and at width 128 a
+// within those rows: reverse 1.28 -> 1.41 to 1.56 ms a launch, 0.68M edges; and at width 128 a
 // pass that is never taken still costs 3% in spilled registers.)  Rows of zeros, and
 // rows with an infinity (which become NaN), do not bound c and are not scaled.
 //   Each of the NW waves holds 32 rows (lane layout as above) and owns TU x TV
@@ -571,7 +571,7 @@ struct DwAcc {
   }
   // From the rows' values, split once their scales are known, which takes no
   // scaling of pieces and no copy of them (per launch of k_wgrad_x3: 434,558 edges and 2 x
-  // 32,768 nodes at width 128 172 -> 162 us, 0.9M edges at width 160 414 -> 330 us); then()
+  // 32,768 nodes at width 128 172 -> 162 us, 0.68M edges at width 160 414 -> 330 us); then()
   // runs when they are no longer needed.
   template <class F>
   __device__ __forceinline__ void add_rows(const float* g, const float* x, bool live, DwLds<LD, NW>& S, int tid,
