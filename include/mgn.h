@@ -64,7 +64,8 @@ extern "C" {
  *     does a weight from 2^-28 of its matrix's largest;
  *   - a weight gradient adds up to 256 rows (edges or nodes next to each other
  *     in the numbering) at one scale: a row whose contributions are 2^-30 or more
- *     below the largest of these loses a bit per further factor of four.
+ *     below the largest of these loses a bit per further factor of four, and
+ *     from 2^-50 on it may count as zero.
  * What is lost is small against the large values; it shows in results that
  * only the small ones reach. */
 #define MGN_FP32 0

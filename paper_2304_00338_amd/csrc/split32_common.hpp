@@ -427,8 +427,8 @@ struct ColSumX3 {
 // above it (at most kDwSpan above its lowest value, so that no sum overflows).
 // What a piece has below 2^-24 is lost, so rows that need much scaling lose low bits:
 // with half of it in each operand, a row whose products are 2^-30 of 2^c's largest
-// stays within 2^-24 of its own largest value, one of 2^-40 within 2^-19, and one of
-// 2^-78 vanishes.  (Adding such rows in further passes at their own c keeps all bits.
+// stays within 2^-24 of its own largest value, one of 2^-40 within 2^-19, and from 2^-50
+// (add) or 2^-78 (add_rows) on they vanish.  (Adding such rows in further passes at their own c keeps all bits.
 // Measured on the eight-patch batch, whose ghost nodes' gradients span 2^48
 // within those rows: reverse 1.28 -> 1.41 to 1.56 ms a launch, 0.68M edges; and at width 128 a
 // pass that is never taken still costs 3% in spilled registers.)  Rows of zeros, and
@@ -496,7 +496,7 @@ struct DwAcc {
       c = cn;
       cmin = min(cmin, c);
     }
-    return er == NONE ? 0 : max(c - er, -60);
+    return er == NONE ? 0 : c - er;
   }
   static __device__ __forceinline__ int bound(int eg, int ex, bool live) {
     return live && max(eg, ex) < kZeroExp && min(eg, ex) > kInfExp ? eg + ex : NONE;

@@ -151,6 +151,25 @@ def test_small_gradient_rows_keep_their_accuracy(mixed, latent):
             assert base[name] < FP32_TOL and e < (2 * base[name] + 1e-6) * (1 + 2.0 ** (k / 2 - 15)), (k, name, e)
 
 
+@pytest.mark.parametrize("latent", [128, 150])
+def test_vanishing_gradient_rows_are_not_enlarged(latent):
+    """Rows so far below the others that their pieces end: what they alone reach
+    may get lost, but not come out larger than it is.  (Node by node in turn, so
+    that all of these rows meet the others in a block; of rows kept in one block and lost in
+    another a part of a sum would be left.)"""
+    m = 2
+    cells, pos, x, p, ids = two_components(True, latent, m)
+    go = O.build_graph(cells, pos)
+    _, tape = O.mgn_forward(go, p, x, go.efeat, m, latent=latent, keep=True)
+    for k in (50, 66, 94):
+        w = np.random.default_rng(9).standard_normal((x.shape[0], 4)).astype(np.float32)
+        w[ids[1]] *= np.float32(2.0 ** -k)
+        want = unit_entries(O.mgn_backward(tape, w)[0], m, latent)
+        _, got = outputs_and_gradients(cells, pos, x, p, w, m, latent)
+        for name, a in unit_entries(got, m, latent).items():
+            assert rel_l2(a, want[name]) < 1.1, (k, name)
+
+
 def test_infinite_gradient_row_stays_by_itself():
     """A row with infinities makes what it reaches infinite or NaN; entries that
     it does not reach (here its ReLU blocks it) keep the other rows' sums."""
