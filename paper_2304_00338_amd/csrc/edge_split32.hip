@@ -92,7 +92,7 @@ k_edge_fwd_x3(EdgeTiles tl, const float* e_in, float* e_out, int write_e, const 
 #pragma unroll
     for (int c = 0; c < Z::KL / 4; ++c)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) x[4 * c + r] = relu(acc[c >> 2][4 * (c & 3) + r] + p[c][r]);
+      for (int r = 0; r < 4; ++r) x[4 * c + r] = relu32(acc[c >> 2][4 * (c & 3) + r] + p[c][r]);
     // ---- z2 = b2 + W2 a1
     gemm_x3<LD>(acc, x, W2, W1, S.w, Z::NC & 1, tid);
 #pragma unroll
@@ -253,7 +253,7 @@ k_edge_bwd_x3(EdgeTiles tl, const float* __restrict__ e_in, const float* ebar_in
 #pragma unroll
       for (int v = 0; v < Z::KL; ++v) {
         const float z = acc[v >> 4][v & 15] + p[v >> 2][v & 3];
-        a1[v] = relu(z);
+        a1[v] = relu32(z);
         if (z > 0.f) mask[v >> 5] |= 1u << (v & 31);
       }
       // pinned: the compiler would keep every z1 instead, to compare it later

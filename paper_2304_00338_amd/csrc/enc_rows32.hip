@@ -159,7 +159,7 @@ k_edge_enc_bwd_r32(int64_t E, const float* __restrict__ f_in, const float* __res
 #pragma unroll
     for (int s = 0; s < Z::KL; ++s) {
       if (a1[s] > 0.f) mask |= 1ull << s;
-      a1[s] = relu(a1[s]);
+      a1[s] = relu32(a1[s]);
     }
     __syncthreads();  // every wave's products of the previous round are done
     stage_row(Y, a1, live);

@@ -59,7 +59,7 @@ k_edge_enc_x3(int64_t E, const float* __restrict__ f_in, MlpW w, float eps, floa
       z = __builtin_fmaf(wr.y, fx.y, z);
       z = __builtin_fmaf(wr.z, fx.z, z);
       z = __builtin_fmaf(wr.w, fx.w, z);
-      x[v] = relu(z);
+      x[v] = relu32(z);
     }
     fx = load(t + br.stride);
     gemm_x3<LD>(acc, x, W2, W2, S.w, par, tid);

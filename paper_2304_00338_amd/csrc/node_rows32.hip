@@ -63,7 +63,7 @@ k_decoder_r32(int64_t N, const float* __restrict__ h_in, MlpW w, float* __restri
     for (int ob = 0; ob < Z::NOB; ++ob)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float a1 = relu(acc[ob][r]);
+        const float a1 = relu32(acc[ob][r]);
 #pragma unroll
         for (int k = 0; k < DEC_OUT; ++k) o[k] += w2[k][f0 + 4 * ob + r] * a1;
       }
@@ -113,7 +113,7 @@ k_decoder_bwd_r32(int64_t N, const float* __restrict__ h_in, const float* __rest
 #pragma unroll
       for (int ob = 0; ob < Z::NOB; ++ob)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[ob][r] = live ? go[k] * relu(acc[ob][r]) : 0.f;
+        for (int r = 0; r < 4; ++r) p[ob][r] = live ? go[k] * relu32(acc[ob][r]) : 0.f;
       cw2[k].add(p, i);
       if (live && g == 0) db2[k] += go[k];
     }
@@ -250,7 +250,7 @@ k_node_enc_bwd_r32(int64_t N, const float* __restrict__ x_in, const float* __res
 #pragma unroll
     for (int s2 = 0; s2 < Z::KL; ++s2) {
       if (a1[s2] > 0.f) mask |= 1ull << s2;
-      a1[s2] = relu(a1[s2]);
+      a1[s2] = relu32(a1[s2]);
     }
     if (live) {
       float* p = a1s + orow;

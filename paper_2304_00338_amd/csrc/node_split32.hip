@@ -113,7 +113,7 @@ k_node_fwd_x3(int64_t N, const float* h_in, const float* __restrict__ agg, MlpW 
     float x[Z::KL];
     node_z1_x3<LD>(acc, x, h_in + o, agg + o, Wh, Wa, W2, S.vec[0], S.w, par, tid);
 #pragma unroll
-    for (int v = 0; v < Z::KL; ++v) x[v] = relu(acc[v >> 4][v & 15]);
+    for (int v = 0; v < Z::KL; ++v) x[v] = relu32(acc[v >> 4][v & 15]);
     // h again, for the residual, in the registers that a1 leaves
     gemm_x3<LD>(acc, x, W2, EMIT ? (const u32x4*)nx.S1s : Wh, S.w, par, tid, [&](int ks) {
 #pragma unroll
@@ -176,7 +176,7 @@ k_node_bwd_x3(int64_t N, const float* __restrict__ h_in, const float* __restrict
 #pragma unroll
     for (int v = 0; v < Z::KL; ++v) {
       const float z = acc[v >> 4][v & 15];
-      x[v] = relu(z);
+      x[v] = relu32(z);
       if (z > 0.f) mask[v >> 5] |= 1u << (v & 31);
     }
     // pinned: the compiler would keep every z1 instead, to compare it later
@@ -300,7 +300,7 @@ k_node_enc_x3(int64_t N, const float* __restrict__ x_in, MlpW w, MlpW nx, float 
       z = __builtin_fmaf(wb.y, xb.y, z);
       z = __builtin_fmaf(wb.z, xb.z, z);
       z = __builtin_fmaf(wb.w, xb.w, z);
-      x[v] = relu(z);
+      x[v] = relu32(z);
     });
     gemm_x3<LD>(acc, x, W2, EMIT ? (const u32x4*)nx.S1s : W2, S.N.w, par, tid);
     par += Z::NC;

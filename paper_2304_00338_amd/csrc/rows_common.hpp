@@ -114,6 +114,9 @@ __device__ __forceinline__ f32x4 run_block(const uint4 (&runs)[4], int ob) {
 // max(x, 0) as one integer max on the bit pattern (negative floats have the
 // sign bit set, so they compare below +0.0 as signed integers).
 __device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
+// The fp32 kernels' ReLU keeps every NaN; above, one with its sign set, as the
+// 16-bit matrix instructions give, becomes 0.
+__device__ __forceinline__ float relu32(float x) { return __builtin_elementwise_maximum(x, 0.f); }
 
 // Sum over the four lanes that hold the same row (q = 0..3).
 __device__ __forceinline__ float sum_rowlanes(float s) { return sum_q(s); }

@@ -109,3 +109,54 @@ def test_edgeless_nodes_get_zero_sums(shape, prec, latent):
         for a, b in zip(res[0], r):
             assert np.isfinite(b).all()
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["nan", "overflow"])
+@pytest.mark.parametrize("prec", ["fp32"])
+@pytest.mark.parametrize("latent", [128, 150])
+def test_component_without_finite_values_stays_apart(prec, latent, kind):
+    """A component of NaNs, or whose first edge activations overflow, beside a
+    finite one: rows past a tile's end are copies of its last row, and must not reach
+    the sums of the wave's next tile."""
+    m, unit = 2, 5
+    A, B = synth.mesh((7, 6, 6), 5), synth.mesh((16, 16, 16), 5)
+    na = A["pos"].shape[0]
+    g = mgn.build_graph(np.concatenate([A["cells"], B["cells"] + na]), np.concatenate([A["pos"], B["pos"]]))
+    dg = mgn.DeviceGraph(g)
+    # (the reverse's 1024 waves take the first component's tiles and then tiles of the second)
+    assert 1024 < g.schedule()[0].shape[0] <= 2048
+    p, v, o = synth.xavier_params(m, 5, latent, randomize_norm=True), {}, 0
+    for name, _, shape in synth.param_shapes(m, latent):
+        v[name] = p[o:o + int(np.prod(shape))].reshape(shape)
+        o += int(np.prod(shape))
+    # node type 1 sets latent feature 0 to about 10, from which the edge MLP's unit overflows
+    v["enc_node.W1"][unit] = [0, 8, 0, 0, 0, 0, 0, 0]
+    v["enc_node.b1"][unit] = -4
+    v["enc_node.W2"][0] = 0
+    v["enc_node.W2"][0, unit] = 20
+    v["enc_node.gamma"][0], v["enc_node.beta"][0] = 1, 0
+    v["block0.edge.W1"][unit] = 0
+    v["block0.edge.W1"][unit, latent] = 1e38
+    v["block0.edge.b1"][unit] = -3e38
+    params = torch.from_numpy(p).cuda()
+    rng = np.random.default_rng(8)
+    x = rng.standard_normal((g.n_nodes, 8)).astype(np.float32)
+    x[:, :4] = [1, 0, 0, 0]
+    w = torch.from_numpy((rng.standard_normal((g.n_nodes, 4)) / g.n_nodes).astype(np.float32)).cuda()
+    res = []
+    for bad in (False, True):
+        if bad and kind == "nan":
+            x[:na] = np.nan
+        elif bad:
+            x[:na, :4] = [0, 1, 0, 0]
+        ctx = mgn.Context(m, g.n_nodes, g.n_edges, prec, save=True, latent=latent)
+        out = mgn.mgn_forward(ctx, dg, params, torch.from_numpy(x).cuda(), dg.efeat, save=True)
+        gi = torch.empty((g.n_nodes, 8), dtype=torch.float32, device="cuda")
+        mgn.mgn_backward(ctx, w, torch.zeros_like(params), gi)
+        res.append((out.cpu().numpy(), gi.cpu().numpy()))
+        del ctx
+    if prec == "fp32":  # (a bf16 ReLU may take a NaN for negative)
+        assert not np.isfinite(res[1][0][:na]).any()
+    for a, b in zip(*res):
+        assert np.isfinite(a).all()
+        np.testing.assert_array_equal(a[na:], b[na:])
