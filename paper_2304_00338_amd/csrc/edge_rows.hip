@@ -425,7 +425,7 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
       for (int r = 0; r < 16; ++r) zr[r] = *reinterpret_cast<const uint32_t*>(zs + r * FB_LD + 2 * lane);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        // (rows past the end are zero)
+        // (rows past the end are zero where their copied row is finite)
         carry.x += __uint_as_float(zr[r] << 16);
         carry.y += __uint_as_float(zr[r] & 0xffff0000u);
         if ((ends >> (16 * rb + r)) & 1u) {
@@ -472,6 +472,7 @@ k_edge_bwd_fused(EdgeTiles tl, const bf16* __restrict__ a1_in, const bf16* __res
               load_e(d1, 0, ev);
             }
           }
+          if (tile_rows(d0) < 32) carry = float2{0.f, 0.f};  // rows past the end may be NaN
           if (!tl.run && d0.y > d0.x) zero_empty<D>(d0.x, d0.y, tl.rowptr, lane, R);
           d0 = d1;
           d1 = es.next(tl);

@@ -112,7 +112,7 @@ def test_edgeless_nodes_get_zero_sums(shape, prec, latent):
 
 
 @pytest.mark.parametrize("kind", ["nan", "overflow"])
-@pytest.mark.parametrize("prec", ["fp32"])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
 @pytest.mark.parametrize("latent", [128, 150])
 def test_component_without_finite_values_stays_apart(prec, latent, kind):
     """A component of NaNs, or whose first edge activations overflow, beside a
